@@ -17,8 +17,8 @@
 // exact in fp32, so the only rounding is inside the matrix core's 32-term sum:
 // see score_abs_bound().
 //
-// fp32 hidden states: plain fp64 arithmetic on the vector ALU (products of two
-// floats are exact in fp64).
+// fp32 hidden states: the same contraction on the fp64 matrix instructions (products of two
+// floats are exact in fp64): see "fp32 score tiles" below.
 #pragma once
 #include "common.hpp"
 
@@ -327,136 +327,283 @@ __global__ __launch_bounds__(WAVES * 64) void k_scores_ksplit(Geo g, const void*
   score_tile_ksplit<NB, KS, WAVES, TAIL, XN, false>(g, sm, b, tl, X, piv, pl2, l2sq, S, sh);
 }
 
-// fp32 hidden states, fp64 arithmetic on the vector ALU.  grid: tiles * (tile_rows / ROWS)
-// blocks of 256: a block owns ROWS (4 or 2) consecutive token rows of one sample and 8 pivots
-// at a time; its 4 waves split D (piece t of a row goes to wave (t / 64) % 4), so that small
-// batches -- the only ones this path is meant for -- still spread over the chip and a wave's
-// chain of dependent loads is a quarter as long.  The next pieces are requested before the
-// current ones are used.  The 4 partial sums of a dot product are added in wave order, each
-// wave's own sum is a fixed lane-strided order plus butterfly: a score depends only on the
-// two rows' bytes.  (Rows per block, measured on one 576-token image: 1, 2, 4, 8 rows give
-// 19.4, 15.6, 16.3, 26.8 us by events; 2 rows where 4 would leave compute units idle.)
-constexpr int kF32Piv = 8;
-template <int kF32Rows>
-__global__ __launch_bounds__(256) void k_scores_f32(Geo g, const void* __restrict__ X,
-                                                    const int* __restrict__ piv,
-                                                    float* __restrict__ S) {
-  // per wave: dot[ROWS][8], pp[8], xx[ROWS]
-  __shared__ double red[4][kF32Rows * kF32Piv + kF32Piv + kF32Rows];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// ---- fp32 score tiles ------------------------------------------------------------------------
+// fp32 hidden states: the contraction runs on the fp64 matrix instructions (the product of two
+// floats is exact in fp64, the sums are fp64 throughout).  A lane loads four consecutive elements
+// of its row; element e of every lane feeds the e-th of four matrix instructions (the order of D
+// inside an instruction is free as long as both operands agree).  The waves of a workgroup split D
+// and their partial sums are added in wave order, so a score is a function of the two rows' bytes.
+//
+// Many rows (k_scores_f32_t16): blocks of 16 rows by 16 pivots, v_mfma_f64_16x16x4 (64 cycles);
+// X is read once and a pivot piece serves all rows of the tile.  A compute unit takes in about
+// 35-50 GB/s from memory and the pivots' pieces queue with the rows' (every workgroup reads all of
+// them once), so the kernel runs at the speed of the unit with the most rows plus pivots: tiles of
+// up to 32 rows, the height chosen on the host so that the units share the rows evenly
+// (f32_tile_rows).  5780 rows of 2048 by 16 pivots: 74 us -> 20 us (47 MB of rows); the vector-ALU
+// kernel this replaces held 4 rows by 8 pivots per workgroup, read X once per 8 pivots and every
+// pivot once per 4 rows.
+constexpr int kF32Waves = 8;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <int NB, int RB>
+struct F32TileShared {
+  double part[kF32Waves][RB][NB][4][kWave];
+  double xx[kF32Waves][RB][kWave];
+};
+
+// grid: tiles of g.tile_rows <= 16*RB rows; 512 threads.  Result layout of the instruction: lane l,
+// slot r holds row (l >> 4) + 4 r, column l & 15.
+template <int NB, int RB>
+__global__ __launch_bounds__(kF32Waves * 64) void k_scores_f32_t16(
+    Geo g, const void* __restrict__ X, const int* __restrict__ piv,
+    const double* __restrict__ pl2, float* __restrict__ S) {
+  constexpr int kRing = NB * RB <= 2 ? 2 : 1;  // steps in flight
+  __shared__ F32TileShared<NB, RB> sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int b, tl;
-  const int parts = g.tile_rows / kF32Rows;
-  const int tile = blockIdx.x / parts;
-  if (!locate_tile(g, tile, b, tl)) return;
+  if (!locate_tile(g, blockIdx.x, b, tl)) return;
   const Sample sm = sample_of(g, b);
-  if (sm.k == 0) return;
-  const int n = sm.n, P = g.P;
-  const int j0 = tl * g.tile_rows + (blockIdx.x - tile * parts) * kF32Rows;  // block-uniform
-  if (j0 >= n) return;
-  const float* Xb = static_cast<const float*>(X) + (long)sm.xrow * g.ld;
-  const int pieces = g.D / 4;
-  const f32x4v* xr[kF32Rows];
+  const int n = sm.n, P = g.P, j0 = tl * g.tile_rows;
+  if (sm.k == 0 || j0 >= n) return;
+  const int rows = n - j0 < g.tile_rows ? n - j0 : g.tile_rows;
+  const int r16 = lane & 15, g4 = lane >> 4;
+  // A step is a 128-byte line of every row, two 16-byte pieces per lane.
+  const int pieces = g.D / 4;                // 16-byte pieces per row
+  const int steps = pieces / 8;              // whole steps
+  const int s0 = wave * steps / kF32Waves, cnt = (wave + 1) * steps / kF32Waves - s0;
+  const f32x4v* xr[RB];
 #pragma unroll
-  for (int r = 0; r < kF32Rows; ++r) {
-    const int j = j0 + r < n ? j0 + r : n - 1;  // rows past the end re-read the last; never stored
-    xr[r] = reinterpret_cast<const f32x4v*>(Xb + (long)j * g.ld);
+  for (int rb = 0; rb < RB; ++rb) {
+    int r = rb * 16 + r16;
+    r = j0 + (r < rows ? r : rows - 1);  // rows past the end re-read the last; never stored
+    xr[rb] = reinterpret_cast<const f32x4v*>(static_cast<const float*>(X) + ((long)sm.xrow + r) * g.ld);
   }
-  float* Sb = S + (long)P * sm.row0;
-  const f32x4v fz = {0.f, 0.f, 0.f, 0.f};
-  for (int i0 = 0; i0 < P; i0 += kF32Piv) {
-    const f32x4v* pr[kF32Piv];
+  const f32x4v* pr[NB];
 #pragma unroll
-    for (int q = 0; q < kF32Piv; ++q) {
-      const int i = i0 + q < P ? i0 + q : P - 1;
-      pr[q] = reinterpret_cast<const f32x4v*>(pivot_row(g, X, 4, sm, b, i, piv));
-    }
-    double dot[kF32Rows][kF32Piv], xx[kF32Rows], pp[kF32Piv];
+  for (int nb = 0; nb < NB; ++nb) {
+    const int i = nb * 16 + r16 < P ? nb * 16 + r16 : P - 1;  // columns past P: never stored
+    pr[nb] = reinterpret_cast<const f32x4v*>(pivot_row(g, X, 4, sm, b, i, piv));
+  }
+  f32x4v ra[kRing][RB][2], rp[kRing][NB][2];
+  auto load = [&](int slot, int s) {  // step s of this wave's share
+    const int t = (s0 + s) * 8 + g4;
 #pragma unroll
-    for (int r = 0; r < kF32Rows; ++r) {
-      xx[r] = 0.0;
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-      for (int q = 0; q < kF32Piv; ++q) dot[r][q] = 0.0;
-    }
+      for (int h = 0; h < 2; ++h) ra[slot][rb][h] = xr[rb][t + h * 4];
 #pragma unroll
-    for (int q = 0; q < kF32Piv; ++q) pp[q] = 0.0;
-    f32x4v xv[kF32Rows], pv[kF32Piv], xn[kF32Rows], pn[kF32Piv];
-    int t = tid;  // piece index: 256 apart per step
-    auto fetch = [&](int tt, f32x4v (&xo)[kF32Rows], f32x4v (&po)[kF32Piv]) {
-      const bool in = tt < pieces;
-      const int ts = in ? tt : 0;  // a piece past the end re-reads piece 0 and counts as zero
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int r = 0; r < kF32Rows; ++r) {
-        const f32x4v v = xr[r][ts];
-        xo[r] = in ? v : fz;
-      }
+      for (int h = 0; h < 2; ++h) rp[slot][nb][h] = pr[nb][t + h * 4];
+  };
+  // two chains per sum: a matrix instruction that adds to the previous one's result waits for it
+  f64x4 acc[RB][NB], acc_odd[RB][NB];
+  double xx[RB], xx_odd[RB];
 #pragma unroll
-      for (int q = 0; q < kF32Piv; ++q) {
-        const f32x4v v = pr[q][ts];
-        po[q] = in ? v : fz;
-      }
-    };
-    fetch(t, xv, pv);
-    for (; t < pieces; t += 256) {
-      fetch(t + 256, xn, pn);
+  for (int rb = 0; rb < RB; ++rb) {
+    xx[rb] = xx_odd[rb] = 0.0;
 #pragma unroll
-      for (int q = 0; q < kF32Piv; ++q) {
-        const double p0 = pv[q].x, p1 = pv[q].y, p2 = pv[q].z, p3 = pv[q].w;
-        pp[q] = fma(p0, p0, pp[q]);
-        pp[q] = fma(p1, p1, pp[q]);
-        pp[q] = fma(p2, p2, pp[q]);
-        pp[q] = fma(p3, p3, pp[q]);
+    for (int nb = 0; nb < NB; ++nb) acc[rb][nb] = acc_odd[rb][nb] = f64x4{0.0, 0.0, 0.0, 0.0};
+  }
+  auto use = [&](const f32x4v (&x)[RB][2], const f32x4v (&p)[NB][2]) {
 #pragma unroll
-        for (int r = 0; r < kF32Rows; ++r) {
-          dot[r][q] = fma(p0, (double)xv[r].x, dot[r][q]);
-          dot[r][q] = fma(p1, (double)xv[r].y, dot[r][q]);
-          dot[r][q] = fma(p2, (double)xv[r].z, dot[r][q]);
-          dot[r][q] = fma(p3, (double)xv[r].w, dot[r][q]);
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        double p0[NB], p1[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          p0[nb] = (double)p[nb][h][e];
+          p1[nb] = (double)p[nb][h][e + 1];
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          const double a0 = (double)x[rb][h][e], a1 = (double)x[rb][h][e + 1];
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            acc[rb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, p0[nb], acc[rb][nb], 0, 0, 0);
+            acc_odd[rb][nb] =
+                __builtin_amdgcn_mfma_f64_16x16x4f64(a1, p1[nb], acc_odd[rb][nb], 0, 0, 0);
+          }
+          xx[rb] = fma(a0, a0, xx[rb]);
+          xx_odd[rb] = fma(a1, a1, xx_odd[rb]);
         }
       }
+  };
 #pragma unroll
-      for (int r = 0; r < kF32Rows; ++r) {
-        const double x0 = xv[r].x, x1 = xv[r].y, x2 = xv[r].z, x3 = xv[r].w;
-        xx[r] = fma(x0, x0, xx[r]);
-        xx[r] = fma(x1, x1, xx[r]);
-        xx[r] = fma(x2, x2, xx[r]);
-        xx[r] = fma(x3, x3, xx[r]);
+  for (int u = 0; u < kRing; ++u)
+    if (u < cnt) load(u, u);
+  int s = 0;
+  for (; s + 2 * kRing <= cnt; s += kRing) {
+#pragma unroll
+    for (int u = 0; u < kRing; ++u) {
+      use(ra[u], rp[u]);
+      load(u, s + kRing + u);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kRing; ++u)
+    if (s + u < cnt) {
+      use(ra[u], rp[u]);
+      if (s + kRing + u < cnt) load(u, s + kRing + u);
+    }
+#pragma unroll
+  for (int u = 0; u < kRing - 1; ++u)
+    if (s + kRing + u < cnt) use(ra[u], rp[u]);
+  // the incomplete step of a row whose pieces are no multiple of eight belongs to the last wave
+  // (missing pieces: both operands zero, so that nothing meets what piece 0 holds)
+  if (wave == kF32Waves - 1 && steps * 8 < pieces) {
+    const f32x4v fz = {0.f, 0.f, 0.f, 0.f};
+    f32x4v x[RB][2], p[NB][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int t = steps * 8 + h * 4 + g4;
+      const bool in = t < pieces;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        x[rb][h] = xr[rb][in ? t : 0];
+        x[rb][h] = in ? x[rb][h] : fz;
       }
 #pragma unroll
-      for (int r = 0; r < kF32Rows; ++r) xv[r] = xn[r];
-#pragma unroll
-      for (int q = 0; q < kF32Piv; ++q) pv[q] = pn[q];
-    }
-    // the wave's sums, then the four waves' partials in wave order
-#pragma unroll
-    for (int r = 0; r < kF32Rows; ++r) {
-#pragma unroll
-      for (int q = 0; q < kF32Piv; ++q) {
-        const double d = wave_sum(dot[r][q]);
-        if (lane == 0) red[wave][r * kF32Piv + q] = d;
+      for (int nb = 0; nb < NB; ++nb) {
+        p[nb][h] = pr[nb][in ? t : 0];
+        p[nb][h] = in ? p[nb][h] : fz;
       }
-      const double x2 = wave_sum(xx[r]);
-      if (lane == 0) red[wave][kF32Rows * kF32Piv + kF32Piv + r] = x2;
+    }
+    use(x, p);
+  }
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sh.part[wave][rb][nb][r][lane] = acc[rb][nb][r] + acc_odd[rb][nb][r];
+    sh.xx[wave][rb][lane] = xx[rb] + xx_odd[rb];
+  }
+  __syncthreads();
+  float* Sb = S + (long)P * sm.row0;
+  for (int o = tid; o < RB * NB * 256; o += kF32Waves * 64) {
+    const int m = o & 15, rb = (o >> 4) % RB, i = o / (16 * RB);  // token row, pivot
+    const int src = (m & 3) * 16 + (i & 15);
+    double d = 0.0, x2 = 0.0;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {
+      d += sh.part[w][rb][i >> 4][m >> 2][src];
+      const double* q = sh.xx[w][rb];
+      x2 += (q[m] + q[16 + m]) + (q[32 + m] + q[48 + m]);
+    }
+    if (i < P && rb * 16 + m < rows) {
+      const double den = sqrt(pl2[b * g.Ppad + i]) * sqrt(x2);
+      Sb[(long)i * n + j0 + rb * 16 + m] = (float)(den > 0.0 ? d / den : 0.0) + 0.0f;
+    }
+  }
+}
+
+// Few rows (k_scores_f32_t4): tiles of 4 rows, so that one 576-token image gives more than a
+// hundred workgroups; v_mfma_f64_4x4x4 (four independent 4x4x4 blocks, 16 cycles).  PG = 4: the
+// blocks are four groups of four pivots; PG = 2 (at most 8 pivots): two groups of pivots times
+// two halves of a step's pieces.  Latency-bound (a chain of launch, pivot indices, rows, sums): eight
+// steps in flight per wave.  One 576-token image of 4096: 13.4 us on the vector ALU, 13.1 us here.
+// Operand layout: lane l holds row l & 3 of block (l >> 2) & 3, k = l >> 4; result: lane l holds
+// column l & 3 of block (l >> 2) & 3, row l >> 4.
+struct F32SmallShared {
+  double part[kF32Waves][kWave];
+  double xx[kF32Waves][kWave];
+};
+
+// grid: tiles of 4 rows; 512 threads.
+template <int PG>
+__global__ __launch_bounds__(kF32Waves * 64) void k_scores_f32_t4(
+    Geo g, const void* __restrict__ X, const int* __restrict__ piv,
+    const double* __restrict__ pl2, float* __restrict__ S) {
+  constexpr int kRing = 8, kHalves = 4 / PG, kStep = 4 * kHalves;  // pieces per step and row
+  __shared__ F32SmallShared sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int b, tl;
+  if (!locate_tile(g, blockIdx.x, b, tl)) return;
+  const Sample sm = sample_of(g, b);
+  if (sm.k == 0 || tl * 4 >= sm.n) return;
+  const int n = sm.n, P = g.P, j0 = tl * 4;
+  const int r4 = lane & 3, blk = (lane >> 2) & 3, pg = blk % PG;
+  const int col = (blk / PG) * 4 + (lane >> 4);  // the lane's piece inside a step
+  const int pieces = g.D / 4;
+  const int steps = pieces / kStep;  // whole steps
+  const int s0 = wave * steps / kF32Waves, cnt = (wave + 1) * steps / kF32Waves - s0;
+  const int jr = j0 + r4 < n ? j0 + r4 : n - 1;  // rows past the end re-read the last; never stored
+  const f32x4v* xr = reinterpret_cast<const f32x4v*>(static_cast<const float*>(X) +
+                                                     ((long)sm.xrow + jr) * g.ld);
+  const f32x4v* xs = xr + s0 * kStep + col;
+  // (the incomplete step at a row's end, as above)
+  const bool rest = wave == kF32Waves - 1 && steps * kStep < pieces;
+  const bool rest_in = steps * kStep + col < pieces;
+  const int t_rest = rest_in ? steps * kStep + col : 0;
+  float* Sb = S + (long)P * sm.row0;
+  for (int i0 = 0; i0 < P; i0 += 4 * PG) {
+    const int i = i0 + pg * 4 + r4 < P ? i0 + pg * 4 + r4 : P - 1;  // columns past P: never stored
+    const f32x4v* pr = reinterpret_cast<const f32x4v*>(pivot_row(g, X, 4, sm, b, i, piv));
+    const f32x4v* ps = pr + s0 * kStep + col;
+    f32x4v ra[kRing], rp[kRing];
+    auto load = [&](int slot, int s) {
+      ra[slot] = xs[s * kStep];
+      rp[slot] = ps[s * kStep];
+    };
+    double acc4[4] = {0.0, 0.0, 0.0, 0.0}, xx4[4] = {0.0, 0.0, 0.0, 0.0};  // independent chains
+    auto use = [&](const f32x4v& x, const f32x4v& p) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double a = (double)x[e];
+        acc4[e] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, (double)p[e], acc4[e], 0, 0, 0);
+        xx4[e] = fma(a, a, xx4[e]);
+      }
+    };
+#pragma unroll
+    for (int u = 0; u < kRing; ++u)
+      if (u < cnt) load(u, u);
+    int s = 0;
+    for (; s + 2 * kRing <= cnt; s += kRing) {
+#pragma unroll
+      for (int u = 0; u < kRing; ++u) {
+        use(ra[u], rp[u]);
+        load(u, s + kRing + u);
+      }
     }
 #pragma unroll
-    for (int q = 0; q < kF32Piv; ++q) {
-      const double p2 = wave_sum(pp[q]);
-      if (lane == 0) red[wave][kF32Rows * kF32Piv + q] = p2;
+    for (int u = 0; u < kRing; ++u)
+      if (s + u < cnt) {
+        use(ra[u], rp[u]);
+        if (s + kRing + u < cnt) load(u, s + kRing + u);
+      }
+#pragma unroll
+    for (int u = 0; u < kRing - 1; ++u)
+      if (s + kRing + u < cnt) use(ra[u], rp[u]);
+    if (rest) {
+      const f32x4v fz = {0.f, 0.f, 0.f, 0.f};
+      const f32x4v x = xr[t_rest], p = pr[t_rest];
+      use(rest_in ? x : fz, rest_in ? p : fz);
     }
+    const double acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
+    const double xx = (xx4[0] + xx4[1]) + (xx4[2] + xx4[3]);
+    sh.part[wave][lane] = acc;
+    sh.xx[wave][lane] = xx;
     __syncthreads();
-    if (tid < kF32Rows * kF32Piv) {
-      const int r = tid / kF32Piv, q = tid - r * kF32Piv;
-      double d = 0.0, p2 = 0.0, x2 = 0.0;
+    if (tid < 16 * PG) {
+      const int m = tid & 3, pi = tid >> 2;  // token row of the tile, pivot of this group
+      double d = 0.0, x2 = 0.0;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        d += red[w][r * kF32Piv + q];
-        p2 += red[w][kF32Rows * kF32Piv + q];
-        x2 += red[w][kF32Rows * kF32Piv + kF32Piv + r];
+      for (int w = 0; w < kF32Waves; ++w) {
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {
+          d += sh.part[w][(pi & 3) + 4 * ((pi >> 2) + PG * h) + 16 * m];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) x2 += sh.xx[w][m + 4 * (PG * h) + 16 * k];
+        }
       }
-      const double den = sqrt(p2) * sqrt(x2);
-      const double sc = den > 0.0 ? d / den : 0.0;
-      if (i0 + q < P && j0 + r < n) Sb[(long)(i0 + q) * n + j0 + r] = (float)sc + 0.0f;
+      if (i0 + pi < P && j0 + m < n) {
+        const double den = sqrt(pl2[b * g.Ppad + i0 + pi]) * sqrt(x2);
+        Sb[(long)(i0 + pi) * n + j0 + m] = (float)(den > 0.0 ? d / den : 0.0) + 0.0f;
+      }
     }
-    __syncthreads();  // red is reused by the next group of pivots
+    __syncthreads();  // part and xx are reused by the next group of pivots
   }
 }
 
