@@ -10,10 +10,11 @@
 // rows, on (fp64 score, index).  The stages depend on each other, so the walk is
 // a serial chain of LDS round trips; to keep it short the kernel speculates:
 //   1. the stage lists are staged in LDS (in groups that fit);
-//   2. the block walks the stages in fp32 order, 1024 list entries per step (one per
-//      thread; ranks by ballot + a prefix over the 16 wave counts), committing what
-//      that order says and noting each stage's last key taken and first key refused;
-//   3. the waves then look at the stages in parallel: a stage whose two keys are
+//   2. one wave walks the stages in fp32 order, 128 list entries at a time (ranks by
+//      ballots), committing what that order says, while the other waves move ahead of
+//      it along the later stages' lists, past entries that are taken already;
+//   3. the waves then look at the stages in parallel: a stage whose last key taken and
+//      first key refused are
 //      within 2*tau is uncertain, and its candidates within 2*tau of the boundary
 //      are queued (who was a candidate is known from the per-token owner stage);
 //   4. the waves re-score the queued (pivot, token) pairs in fp64, in parallel;
@@ -25,57 +26,50 @@
 #pragma once
 #include "common.hpp"
 
+#include <type_traits>
+
 namespace dart {
 
 constexpr int kRetThreads = 1024;  // 16 waves for staging, the band phase and the fp64 re-scoring
 constexpr int kRetWaves = kRetThreads / kWave;
-constexpr int kRetWords = kMaxN / 32;
-// List entries staged in LDS at a time.  Two layouts of the same LDS region: whole 8-byte
-// entries (one LDS read each) when the lists of the batch's largest sample fit kRetList of
-// them, else a 32-bit score image and a 16-bit token index per entry (6 bytes, two LDS reads:
-// measured 0.5 us slower on a 2880-token sample), so that the 32 lists of a 9216-token video
-// sample (17424 entries) or the 16 lists of a 16384-token sample at one ninth (15.6 K) are
-// still staged in one go instead of two (measured: -3 and -5 us).
-constexpr int kRetList = 12288;
-constexpr int kRetListPacked = 18432;
+// List entries staged in LDS at a time, as a 32-bit score image and a 16-bit token index each: the
+// 32 lists of a 9216-token video sample (17424 entries) or the 16 lists of a 16384-token sample at
+// one ninth (15.6 K) are staged in one go, and the walk reads the indices alone.
+constexpr int kRetList = 18432;
 constexpr int kRetQ = 1024;      // band candidates awaiting an fp64 score
 constexpr int kRetInFlight = 4;  // 16-byte pieces per row and lane in flight in the fp64 re-scoring
+// Quotas from which the host takes the walk of all waves together (k_retain's WIDE): wave 0 alone
+// takes about 0.25 us per stage and 0.1 us more for every 64 entries beyond 128, all waves 0.5 us
+// whatever the length (8 stages of quota 130 on 1500 tokens: 8.4 against 5.5 us; 16 of quota 19 on
+// 2880 tokens: 5.1 against 8.5).
+constexpr int kWideQuota = 64;
 constexpr unsigned char kOwnNone = 0xff, kOwnPivot = 0xfe;
-constexpr unsigned long long kNoKey = ~0ull;  // no list entry looks like this (index < 2^14)
 
 struct RetainShared {
-  union {
-    unsigned long long list[kRetList];
-    struct {
-      uint32_t lkey[kRetListPacked];        // score images of the staged entries
-      unsigned short lidx[kRetListPacked];  // their token indices (< kMaxN = 2^14)
-    } pk;
-  };
-  uint32_t R[kRetWords];
-  unsigned char owner[kMaxN];  // stage that took the token (kOwnPivot, kOwnNone)
-  double q_s64[kRetQ];
-  int q_idx[kRetQ];
-  unsigned char q_stage[kRetQ];
-  unsigned char q_taken[kRetQ];
+  // (what the walk touches comes first: within the 64 KiB that an LDS instruction's offset spans)
+  // who took the token: a stage, kOwnPivot, or kOwnNone (the token is not retained); the last
+  // kWave bytes stand for entries past a list's end (kOwnPivot: never a candidate)
+  __attribute__((aligned(16))) unsigned char owner[kMaxN + kWave];
   int st_off[kMaxP];  // offset of the stage's list inside the sample's list region
   int st_len[kMaxP];
-  // per stage: [0] last key taken, [1] first key refused (kNoKey: the walk met none)
+  // per stage: a list position at or before the last entry taken (where the walk began, every entry
+  // before being taken by earlier stages); then the last key taken and the first refused
+  int st_start[kMaxP];
   unsigned long long st_kab[kMaxP][2];
   int st_qlo[kMaxP], st_qhi[kMaxP];
   unsigned char st_unc[kMaxP];
   int wcnt[kRetWaves];
-  int qn, cnt, bad_first, fb_first, walk_taken;
+  int qn, cnt, bad_first, fb_first;
+  int walked;  // stages before this one are walked
+  int piv[kMaxP];     // the pivots that are tokens
+  double pl2[kMaxP];  // squared norms of the pivots, if given
+  unsigned short lidx[kRetList];  // token indices of the staged entries (< kMaxN = 2^14)
+  uint32_t lkey[kRetList];        // their score images
+  double q_s64[kRetQ];
+  int q_idx[kRetQ];
+  unsigned char q_stage[kRetQ];
+  unsigned char q_taken[kRetQ];
 };
-
-__device__ __forceinline__ bool bit_of(const uint32_t* R, uint32_t j) {
-  return (R[j >> 5] >> (j & 31)) & 1u;
-}
-__device__ __forceinline__ void set_bit(uint32_t* R, uint32_t j) {
-  atomicOr(&R[j >> 5], 1u << (j & 31));
-}
-__device__ __forceinline__ void clear_bit(uint32_t* R, uint32_t j) {
-  atomicAnd(&R[j >> 5], ~(1u << (j & 31)));
-}
 
 // (score, index) pairs compare lexicographically
 __device__ __forceinline__ bool pair_less(double sa, int ja, double sb, int jb) {
@@ -90,8 +84,8 @@ __device__ __forceinline__ bool pair_less(double sa, int ja, double sb, int jb) 
 // keep: packed, ascending per sample.  cu_keep_out (optional) [B+1].
 // scr_f64 [2*total_N] doubles: per-sample scratch at row0 (fallback sweep only).
 // COH: S, lists and piv were written, and keep will be read, by other workgroups of this
-// launch.  PACKED: the 6-byte layout of the staged lists (see kRetList).
-template <int DT, bool COH, bool PACKED = false>
+// launch.  WIDE: how the stages are walked (see kWideQuota).
+template <int DT, bool COH, bool WIDE>
 __device__ __forceinline__ void retain_body(
     const Geo& g, int b, const float* S, const unsigned long long* lists, const int* piv,
     const void* X, int* keep, int* cu_keep_out, double* scr_f64, float two_tau,
@@ -105,7 +99,6 @@ __device__ __forceinline__ void retain_body(
   }
   if (sm.k == 0) return;
   const int n = sm.n, P = g.P, k = sm.k;
-  const int words = (n + 31) >> 5;
   const int esz = DT == kBF16 ? 2 : 4;
   const long rowbytes = g.ld * esz;
   const unsigned char* Xb =
@@ -115,12 +108,6 @@ __device__ __forceinline__ void retain_body(
   int* sweep_idx = reinterpret_cast<int*>(scr_f64 + g.total_N + sm.row0);  // fallback sweep
 
   const Split sp(k, P, g.Pin);
-  constexpr int kCap = PACKED ? kRetListPacked : kRetList;  // staged entries at a time
-  // staged entry o in the form of the global lists (score image << 32 | index)
-  auto staged_entry = [&](int o) -> unsigned long long {
-    if (PACKED) return ((unsigned long long)sh.pk.lkey[o] << 32) | sh.pk.lidx[o];
-    return sh.list[o];
-  };
   // stage constants in the lanes of every wave: lane i holds stage i's quota, list
   // length and list offset (the offsets are the prefix sums of the lengths)
   int quota_v = 0, len_v = 0;
@@ -138,18 +125,18 @@ __device__ __forceinline__ void retain_body(
     const int first = __builtin_amdgcn_readfirstlane(first_any);  // block-uniform: keep it scalar
     group_base = __builtin_amdgcn_readfirstlane(__shfl(off_v, first, kWave));
     const int l0 = __builtin_amdgcn_readfirstlane(__shfl(len_v, first, kWave));
-    const int l0c = l0 < kCap ? l0 : kCap;
+    const int l0c = l0 < kRetList ? l0 : kRetList;
     // a later stage s joins the group while everything up to the end of its list fits; the
     // list ends grow with s, so the stages that fit are the lanes first+1 .. group_hi-1
     const int rel_end = off_v + len_v - group_base - l0 + l0c;  // staged entries through stage `lane`
-    const bool fits = lane > first && lane < P && rel_end <= kCap;
+    const bool fits = lane > first && lane < P && rel_end <= kRetList;
     const int extra = __builtin_amdgcn_readfirstlane(__popcll(__ballot(fits)));
     group_hi = first + 1 + extra;
     const int through = __builtin_amdgcn_readfirstlane(__shfl(rel_end, first + extra, kWave));
     staged_total = extra > 0 ? through : l0c;
   };
-  // a group moves in two halves of kStageLoads loads per thread (48 or 72 KiB in flight each)
-  constexpr int kStageLoads = kCap / kRetThreads / 2;
+  // a group moves in two halves of kStageLoads loads per thread (72 KiB in flight each)
+  constexpr int kStageLoads = kRetList / kRetThreads / 2;
   unsigned long long staged[kStageLoads];
   auto load_half = [&](int h) {
 #pragma unroll
@@ -163,12 +150,8 @@ __device__ __forceinline__ void retain_body(
     for (int u = 0; u < kStageLoads; ++u) {
       const int t = (h * kStageLoads + u) * kRetThreads + tid;
       if (t < staged_total) {
-        if (PACKED) {
-          sh.pk.lkey[t] = (uint32_t)(staged[u] >> 32);
-          sh.pk.lidx[t] = (unsigned short)staged[u];
-        } else {
-          sh.list[t] = staged[u];
-        }
+        sh.lkey[t] = (uint32_t)(staged[u] >> 32);
+        sh.lidx[t] = (unsigned short)staged[u];
       }
     }
   };
@@ -179,9 +162,13 @@ __device__ __forceinline__ void retain_body(
   load_half(0);
   int my_pivot = -1;
   if (tid < g.Pin) my_pivot = ld_dev<COH>(&piv[b * P + tid]);  // pivots from outside hold no slot
-  for (int t = tid; t < words; t += kRetThreads) sh.R[t] = 0u;
+  double my_pl2 = 0.0;
+  if (pl2 && tid < P) my_pl2 = ld_dev<COH>(&pl2[b * g.Ppad + tid]);
   for (int t = tid; t < (n + 3) / 4; t += kRetThreads)
     reinterpret_cast<uint32_t*>(sh.owner)[t] = 0xffffffffu;
+  if (tid < kWave) sh.owner[kMaxN + tid] = kOwnPivot;
+  if (tid < g.Pin) sh.piv[tid] = my_pivot < 0 ? 0 : (my_pivot < n ? my_pivot : n - 1);
+  if (pl2 && tid < P) sh.pl2[tid] = my_pl2;
   if (tid < P) {  // wave 0: its lanes hold the stage constants
     sh.st_len[tid] = len_v;
     sh.st_off[tid] = off_v;
@@ -192,11 +179,14 @@ __device__ __forceinline__ void retain_body(
     store_half(1);
   }
   __syncthreads();
-  if (my_pivot >= 0 && my_pivot < n) {
-    set_bit(sh.R, (uint32_t)my_pivot);
-    sh.owner[my_pivot] = kOwnPivot;
-  }
+  if (my_pivot >= 0 && my_pivot < n) sh.owner[my_pivot] = kOwnPivot;
 
+  // row of stage st's pivot (the re-scoring waits for the rows alone: index and norm are in LDS)
+  auto stage_pivot = [&](int st) -> const unsigned char* {
+    if (st >= g.Pin)
+      return static_cast<const unsigned char*>(g.E) + ((long)b * g.Pe + (st - g.Pin)) * g.lde * esz;
+    return Xb + (long)sh.piv[st] * rowbytes;
+  };
   int next = 0;  // first stage not yet final (block-uniform)
   while (next < P) {
     if (next >= group_hi) {
@@ -213,8 +203,9 @@ __device__ __forceinline__ void retain_body(
       sh.qn = 0;
       sh.bad_first = group_hi;
       sh.fb_first = group_hi;
+      sh.walked = next;
     }
-    if (tid >= next && tid < group_hi) sh.st_kab[tid][1] = kNoKey;
+    if (tid >= next && tid < group_hi) sh.st_start[tid] = 0;
     __syncthreads();
     const int walk_end = group_hi;
     // The global pointer carries its address space: with a generic one the compiler may fold
@@ -224,141 +215,265 @@ __device__ __forceinline__ void retain_body(
     const GlobalList glist_g = (GlobalList)glist;
     auto entry_of = [&](int i, int p) -> unsigned long long {
       const int o = sh.st_off[i] - group_base + p;  // position among the staged entries
-      if (o < staged_total) return staged_entry(o);
+      if (o < staged_total) return ((unsigned long long)sh.lkey[o] << 32) | sh.lidx[o];
       if (COH) return ld_dev<true>(&glist[sh.st_off[i] + p]);
       return glist_g[sh.st_off[i] + p];
     };
 
     // ------------------------------------------------------------------ speculative walk
-    // All 16 waves walk together, 1024 list entries per step (one per thread): one step per
-    // stage unless a list is longer.  On the critical path of a step: read R, ballot,
-    // exchange the 16 wave counts (barrier), commit, barrier.  The step is bound by the
-    // number of instructions a wave issues, so the one-step case is kept free of loops and
-    // of everything the general case needs; the next stage's entries are read ahead.
-    {
-      // entries [0, 1024) of a stage's list (threads past its end read the group's entry 0)
-      auto first_entries = [&](int st) -> unsigned long long {
-        const int len = __builtin_amdgcn_readlane(len_v, st);
-        const int off = __builtin_amdgcn_readlane(off_v, st) - group_base;
-        int idx = tid < len ? off + tid : 0;
-        idx = idx < kCap ? idx : 0;
-        return staged_entry(idx);
+    // A stage depends on every earlier one, so the walk is as long as one wave's instruction
+    // chain: wave 0 walks alone, kRun runs of 64 entries per stage straight-line and more only if
+    // those do not fill the quota.  The LDS operations of a wave complete in order, so a stage's
+    // marks are seen by the next stage's reads without a barrier; an entry costs one byte read (its
+    // token's owner) and one byte written back; the next stage's indices are read ahead.  What
+    // would make it long are the entries at the head of a list that earlier stages took
+    // (near-duplicate pivots have nearly the same list, so stage i begins with most of what the i
+    // stages before it took): the other waves keep moving st_start of the later stages past such
+    // entries.  An entry once taken stays taken during the walk, so a position read late is only
+    // less far ahead.
+    const auto lds_load = [](const int* p) {
+      return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    const auto lds_store = [](int* p, int v) {
+      __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    if constexpr (WIDE) {
+      // Large quotas: all 16 waves in step, 1024 entries at a time, two barriers per stage.  The
+      // next stage's entries travel together with the wave counts.
+      auto first_tokens = [&](int st) -> int {
+        const int o = __builtin_amdgcn_readlane(off_v, st) - group_base + tid;
+        return sh.lidx[o < kRetList ? o : kRetList - 1];
       };
-      const int wv = __builtin_amdgcn_readfirstlane(wave);
-      unsigned long long e_pre = first_entries(next);
+      int pre = first_tokens(next);
       for (int i = next; i < walk_end; ++i) {
         const int quota = __builtin_amdgcn_readlane(quota_v, i);
         const int len = __builtin_amdgcn_readlane(len_v, i);
         const int off = __builtin_amdgcn_readlane(off_v, i) - group_base;
-        const unsigned long long e0 = e_pre;
-        const int inext = i + 1 < walk_end ? i + 1 : i;
-        if (quota == 0) {
-          e_pre = first_entries(inext);
-          continue;
-        }
-        const bool staged_all = off + len <= staged_total;  // the usual case: plain LDS reads
-        if (staged_all && len <= kRetThreads) {
-          // The whole list in one step, straight-line: the prefetched entries are the
-          // list.  Waves past the list's end only write a zero count and keep the barriers.
-          const uint32_t j = (uint32_t)e0;
-          const bool busy = wv * kWave < len;  // wave-uniform
-          unsigned long long bal = 0ull;
-          bool cand = false;
-          if (busy) {
-            const uint32_t rw = sh.R[j >> 5];
-            cand = tid < len && ((rw >> (j & 31)) & 1u) == 0u;
-            bal = __ballot(cand);
-          }
-          if (lane == 0) sh.wcnt[wv] = __popcll(bal);
-          __syncthreads();
-          // the next stage's entries (they do not depend on this stage's commits) travel
-          // together with the wave counts
-          if (wv * kWave < __builtin_amdgcn_readlane(len_v, inext)) e_pre = first_entries(inext);
-          if (busy) {
-            // inclusive prefix of the 16 wave counts in lanes 0..15
-            int x = lane < kRetWaves ? sh.wcnt[lane] : 0;
-            x += dpp_move<kDppShr1>(0, x);
-            x += dpp_move<kDppShr2>(0, x);
-            x += dpp_move<kDppShr4>(0, x);
-            x += dpp_move<kDppShr8>(0, x);
-            const int before = wv > 0 ? __builtin_amdgcn_readlane(x, wv > 0 ? wv - 1 : 0) : 0;
-            const int rank = before + __popcll(bal & lt_mask);
-            if (cand) {
-              if (rank < quota) {
-                set_bit(sh.R, j);
-                sh.owner[j] = (unsigned char)i;
-              }
-              const uint32_t rel = (uint32_t)(rank - (quota - 1));  // 0: last taken, 1: first refused
-              if (rel < 2u) sh.st_kab[i][rel] = e0;
-            }
-          }
-          __syncthreads();  // the commits are visible before anyone tests R again
-          continue;
-        }
-        e_pre = first_entries(inext);
-        bool have_b = false;
+        const bool staged_all = off + len <= staged_total;
         int taken = 0;
-        for (int pos = 0; pos < len && !have_b; pos += kRetThreads) {
-          if (pos + wv * kWave >= len) {
-            // this wave's 64 entries are past the list's end: it only keeps the barriers
-            if (lane == 0) sh.wcnt[wv] = 0;
-            __syncthreads();
-            __syncthreads();
-            taken = sh.walk_taken;
-            have_b = taken > quota;
-            continue;
+        for (int pos = 0; pos < len && taken < quota; pos += kRetThreads) {
+          const int p = pos + tid;
+          const bool busy = pos + (wave << 6) < len;  // wave-uniform: this wave has entries
+          int j = kMaxN + lane;
+          unsigned long long m = 0ull;
+          if (busy) {
+            if (p < len) {
+              if (staged_all) j = pos == 0 ? pre : (int)sh.lidx[off + p];
+              else j = (int)(uint32_t)entry_of(i, p);
+            }
+            m = __builtin_amdgcn_ballot_w64(sh.owner[j] == kOwnNone);
           }
-          const int t = pos + tid;
-          const bool in = t < len;
-          unsigned long long e;
-          if (staged_all) e = staged_entry(in ? off + t : 0);
-          else e = in ? entry_of(i, t) : staged_entry(0);  // a list longer than the LDS region
-          const uint32_t j = (uint32_t)e;
-          const uint32_t rw = sh.R[j >> 5];
-          const bool cand = in && ((rw >> (j & 31)) & 1u) == 0u;
-          const unsigned long long bal = __ballot(cand);
-          if (lane == 0) sh.wcnt[wv] = __popcll(bal);
+          if (lane == 0) sh.wcnt[wave] = __popcll(m);
           __syncthreads();
-          int x = lane < kRetWaves ? sh.wcnt[lane] : 0;
+          if (pos == 0) pre = first_tokens(i + 1 < walk_end ? i + 1 : i);
+          int x = lane < kRetWaves ? sh.wcnt[lane] : 0;  // inclusive prefix in lanes 0..15
           x += dpp_move<kDppShr1>(0, x);
           x += dpp_move<kDppShr2>(0, x);
           x += dpp_move<kDppShr4>(0, x);
           x += dpp_move<kDppShr8>(0, x);
-          const int total = __builtin_amdgcn_readlane(x, kRetWaves - 1);
-          const int before = wv > 0 ? __builtin_amdgcn_readlane(x, wv > 0 ? wv - 1 : 0) : 0;
-          const int rank = taken + before + __popcll(bal & lt_mask);
-          if (cand) {
-            if (rank < quota) {
-              set_bit(sh.R, j);
+          if (busy) {
+            const int wv = __builtin_amdgcn_readfirstlane(wave);
+            const int before = taken + (wv > 0 ? __builtin_amdgcn_readlane(x, wv > 0 ? wv - 1 : 0) : 0);
+            const int r = before + __popcll(m & lt_mask);
+            if (((m >> lane) & 1ull) != 0ull && r < quota) {
               sh.owner[j] = (unsigned char)i;
+              if (r == quota - 1) sh.st_start[i] = p;  // the last one taken
             }
-            const uint32_t rel = (uint32_t)(rank - (quota - 1));
-            if (rel < 2u) sh.st_kab[i][rel] = e;
           }
-          taken += total;
-          have_b = taken > quota;
-          if (tid == 0) sh.walk_taken = taken;  // for the waves that sat this step out
-          __syncthreads();  // the commits are visible before anyone tests R again
+          taken += __builtin_amdgcn_readlane(x, kRetWaves - 1);
+          __syncthreads();  // the marks are visible before anyone tests them again
         }
+        if (len == 0) pre = first_tokens(i + 1 < walk_end ? i + 1 : i);
+      }
+    } else if (wave == 0) {
+      __builtin_amdgcn_s_setprio(3);
+      int start_v = 0;  // lane i: where stage i's walk began
+      auto walk = [&](auto runs) {
+        constexpr int kRun = decltype(runs)::value;
+        int tok[kRun];  // the stage's entries (token, or a byte past the tokens: no entry)
+        int nxt[kRun];
+        int pos = 0, ahead = 0;
+        auto read_ahead = [&](int at, int off) {
+#pragma unroll
+          for (int c = 0; c < kRun; ++c) {
+            const int o = off + at + c * kWave + lane;
+            nxt[c] = sh.lidx[o < kRetList ? o : kRetList - 1];
+          }
+        };
+        auto take_over = [&](int at, int len) {
+#pragma unroll
+          for (int c = 0; c < kRun; ++c)
+            tok[c] = at + c * kWave + lane < len ? nxt[c] : kMaxN + lane;
+        };
+        int quota = __builtin_amdgcn_readlane(quota_v, next);
+        int len = __builtin_amdgcn_readlane(len_v, next);
+        int off = __builtin_amdgcn_readlane(off_v, next) - group_base;
+        read_ahead(0, off);
+        take_over(0, off + len <= staged_total ? len : 0);
+        for (int i = next; i < walk_end; ++i) {
+          int own[kRun];
+#pragma unroll
+          for (int c = 0; c < kRun; ++c) own[c] = sh.owner[tok[c]];
+          const int in = i + 1 < walk_end ? i + 1 : i;
+          const int quota_n = __builtin_amdgcn_readlane(quota_v, in);
+          const int len_n = __builtin_amdgcn_readlane(len_v, in);
+          const int off_n = __builtin_amdgcn_readlane(off_v, in) - group_base;
+          const int pos_n = __builtin_amdgcn_readfirstlane(ahead);
+          read_ahead(pos_n, off_n);
+          ahead = lds_load(&sh.st_start[i + 2 < walk_end ? i + 2 : in]);
+          start_v = lane == i ? pos : start_v;
+          int taken = 0;  // candidates met so far
+#pragma unroll
+          for (int c = 0; c < kRun; ++c) {
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(own[c] == kOwnNone);
+            const int r = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((unsigned)m, taken));
+            sh.owner[tok[c]] = (unsigned char)(own[c] == kOwnNone && r < quota ? i : own[c]);
+            taken += __popcll(m);
+          }
+          const bool staged_all = off + len <= staged_total;  // the usual case
+          for (int p = staged_all ? pos + kRun * kWave : 0; p < len && taken < quota; p += kWave) {
+            const bool have = p + lane < len;
+            const int j = !have ? kMaxN + lane
+                                : staged_all ? (int)sh.lidx[off + p + lane] : (int)(uint32_t)entry_of(i, p + lane);
+            const bool cand = sh.owner[j] == kOwnNone;
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
+            const int r = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((unsigned)m, taken));
+            if (cand && r < quota) sh.owner[j] = (unsigned char)i;
+            taken += __popcll(m);
+          }
+          lds_store(&sh.walked, i + 1);
+          pos = pos_n;
+          quota = quota_n;
+          len = len_n;
+          off = off_n;
+          take_over(pos, off + len <= staged_total ? len : 0);
+        }
+      };
+      // runs that usually fill the quota: about a third of the entries past st_start are taken
+      if (sp.q < 40) walk(std::integral_constant<int, 2>{});
+      else walk(std::integral_constant<int, 4>{});
+      if (lane >= next && lane < walk_end) sh.st_start[lane] = start_v;
+      __builtin_amdgcn_s_setprio(0);
+    } else {
+      // (A wave leaves when its last stage is the walk's next or is walked: the walk waits for
+      // nobody.  It sleeps between looks: the LDS is the walk's.)
+      const int last = next + wave - 1 + (walk_end - next - wave) / (kRetWaves - 1) * (kRetWaves - 1);
+      bool moved = true;
+      for (int seen = -1; next + wave - 1 < walk_end;) {
+        const int walked = __builtin_amdgcn_readfirstlane(lds_load(&sh.walked));
+        if (last <= walked + 1) break;
+        if (walked == seen && !moved) {
+          __builtin_amdgcn_s_sleep(4);
+          continue;
+        }
+        seen = walked;
+        moved = false;
+        for (int i = next + wave - 1; i < walk_end; i += kRetWaves - 1) {
+          const int len = __builtin_amdgcn_readlane(len_v, i);
+          const int off = __builtin_amdgcn_readlane(off_v, i) - group_base;
+          // (the next two stages' positions have been read already)
+          if (i <= walked + 1 || off + len > staged_total) continue;
+          const int at = __builtin_amdgcn_readfirstlane(lds_load(&sh.st_start[i]));
+          const int p = at + lane;
+          const int j = p < len ? (int)sh.lidx[off + p] : 0;
+          const unsigned char own = *(volatile unsigned char*)&sh.owner[j];
+          const unsigned long long free_m = __ballot(p >= len || own == kOwnNone);
+          const int step = free_m ? __builtin_ctzll(free_m) : kWave;
+          if (step > 0) {
+            if (lane == 0) lds_store(&sh.st_start[i], at + step);
+            moved = true;
+          }
+        }
+        __builtin_amdgcn_s_sleep(1);
       }
     }
     __syncthreads();
 
     // ------------------------------------------------------------------ uncertain stages
-    // wave w looks at stages next+w, next+w+16, ...; R and owner are only read here
+    // wave w looks at stages next+w, next+w+16, ...; owner is only read here
     for (int i = next + wave; i < walk_end; i += kRetWaves) {
       bool unc = false;
       uint32_t lo_m = 0, hi_m = 0;
-      if (Xb && sp.quota(i) > 0 && sh.st_kab[i][1] != kNoKey) {
-        const float fa = mono_inv((uint32_t)(sh.st_kab[i][0] >> 32));
-        const float fb = mono_inv((uint32_t)(sh.st_kab[i][1] >> 32));
-        unc = !((fb - fa) > two_tau);
-        lo_m = mono_of((fa - two_tau) + 0.0f);
-        hi_m = mono_of((fb + two_tau) + 0.0f);
+      int pa = -1;  // list position of the last entry taken
+      if (Xb && sp.quota(i) > 0) {
+        // the last entry taken, and the first one refused: a candidate (not taken by an earlier
+        // stage) that this stage did not take
+        const int len = sh.st_len[i];
+        int pb = -1;
+        for (int p0 = sh.st_start[i]; p0 < len && pb < 0; p0 += kWave) {
+          const int p = p0 + lane;
+          const unsigned char own = p < len ? sh.owner[(uint32_t)entry_of(i, p)] : kOwnPivot;
+          const unsigned long long mt = __ballot(own == (unsigned char)i);
+          const unsigned long long mr = __ballot(own == kOwnNone || (own < kOwnPivot && (int)own > i));
+          if (mt) pa = p0 + 63 - __builtin_clzll(mt);
+          if (mr) pb = p0 + __builtin_ctzll(mr);
+        }
+        if (pa >= 0 && pb >= 0) {
+          const unsigned long long ka = entry_of(i, pa), kb = entry_of(i, pb);
+          const float fa = mono_inv((uint32_t)(ka >> 32)), fb = mono_inv((uint32_t)(kb >> 32));
+          unc = !((fb - fa) > two_tau);
+          lo_m = mono_of((fa - two_tau) + 0.0f);
+          hi_m = mono_of((fb + two_tau) + 0.0f);
+          if (lane == 0) {  // for the block-wide fallback
+            sh.st_kab[i][0] = ka;
+            sh.st_kab[i][1] = kb;
+          }
+        }
       }
       if (lane == 0) sh.st_unc[i] = unc ? 1 : 0;
       if (!unc) continue;
       const int len = sh.st_len[i];
+      // reserves cnt queue slots, only if they fit (so every reserved slot gets written)
+      auto reserve = [&](int cnt) -> int {
+        int at = kRetQ + 1;
+        if (lane == 0) {
+          int old = sh.qn;
+          while (old + cnt <= kRetQ) {
+            const int seen = atomicCAS(&sh.qn, old, old + cnt);
+            if (seen == old) {
+              at = old;
+              break;
+            }
+            old = seen;
+          }
+        }
+        return __builtin_amdgcn_readfirstlane(at);
+      };
+      // Candidates of stage i = tokens no earlier stage owned.  Usually the band is a handful of
+      // entries: one look at the 64 entries around the boundary that holds all of it, ends included.
+      {
+        const int w0 = pa - 31 > 0 ? pa - 31 : 0;
+        const int p = w0 + lane;
+        const unsigned long long e = p < len ? entry_of(i, p) : ~0ull;  // (past the end: above the band)
+        const uint32_t key = (uint32_t)(e >> 32);
+        const unsigned char own = p < len ? sh.owner[(uint32_t)e] : kOwnPivot;
+        const unsigned long long below = __ballot(key < lo_m), above = __ballot(key > hi_m);
+        const bool whole_below = w0 == 0 || (below & 1ull) != 0ull;
+        const bool whole_above = w0 + kWave <= len ? above != 0ull : len == n || __ballot(p < len && key > hi_m) != 0ull;
+        const bool band = key >= lo_m && key <= hi_m && (own == kOwnNone || (own < kOwnPivot && (int)own >= i));
+        const unsigned long long mb = __ballot(band);
+        if (whole_below && whole_above) {
+          const int cnt = __popcll(mb);
+          const int qlo = reserve(cnt);
+          if (qlo + cnt > kRetQ) {
+            if (lane == 0) atomicMin(&sh.fb_first, i);
+            continue;
+          }
+          if (band) {
+            const int slot = qlo + __popcll(mb & lt_mask);
+            sh.q_idx[slot] = (int)(uint32_t)e;
+            sh.q_stage[slot] = (unsigned char)i;
+            sh.q_taken[slot] = own == (unsigned char)i ? 1 : 0;
+          }
+          if (lane == 0) {
+            sh.st_qlo[i] = qlo;
+            sh.st_qhi[i] = qlo + cnt;
+          }
+          continue;
+        }
+      }
       // first list position whose key reaches the band (64-ary search on the sorted keys)
       int lo_pos = 0, span = len;
       while (span > kWave) {
@@ -370,7 +485,6 @@ __device__ __forceinline__ void retain_body(
         if (m > 0) lo_pos += (m - 1) * stride;
         span = stride;
       }
-      // candidates of stage i = tokens no earlier stage owned
       auto scan = [&](int qbase) -> int {
         int cnt = 0;
         bool closed = false;
@@ -396,20 +510,7 @@ __device__ __forceinline__ void retain_body(
       int cnt = scan(-1);
       const bool open = cnt < 0 && len < n;  // the band may run past the stored list
       cnt = cnt < 0 ? -1 - cnt : cnt;
-      // reserve cnt queue slots, only if they fit (so every reserved slot gets written)
-      int qlo = kRetQ + 1;
-      if (lane == 0 && !open) {
-        int old = sh.qn;
-        while (old + cnt <= kRetQ) {
-          const int seen = atomicCAS(&sh.qn, old, old + cnt);
-          if (seen == old) {
-            qlo = old;
-            break;
-          }
-          old = seen;
-        }
-      }
-      qlo = __builtin_amdgcn_readfirstlane(qlo);
+      const int qlo = open ? kRetQ + 1 : reserve(cnt);
       if (qlo + cnt > kRetQ) {
         // too many ties for the queue (or an open band): leave it to the block-wide sweep
         if (lane == 0) atomicMin(&sh.fb_first, i);
@@ -431,10 +532,10 @@ __device__ __forceinline__ void retain_body(
     for (int q = wave; q < qn; q += kRetWaves) {  // a pair per wave: 16 row pairs in flight
       const int st = sh.q_stage[q];
       if (st >= fb_first) continue;  // will be walked again anyway
-      const unsigned char* prow = pivot_row<COH>(g, X, esz, sm, b, st, piv);
+      const unsigned char* prow = stage_pivot(st);
       const unsigned char* xrow = Xb + (long)sh.q_idx[q] * rowbytes;
       const double s0 =
-          pl2 ? row_cosine_f64<DT, true, kRetInFlight>(prow, xrow, g.D, lane, ld_dev<COH>(&pl2[b * g.Ppad + st]))
+          pl2 ? row_cosine_f64<DT, true, kRetInFlight>(prow, xrow, g.D, lane, sh.pl2[st])
               : row_cosine_f64<DT, false, kRetInFlight>(prow, xrow, g.D, lane);
       if (lane == 0) sh.q_s64[q] = s0;
     }
@@ -446,6 +547,17 @@ __device__ __forceinline__ void retain_body(
     for (int i = next + wave; i < walk_end && i < fb_first; i += kRetWaves) {
       if (!sh.st_unc[i]) continue;
       const int qlo = sh.st_qlo[i], qhi = sh.st_qhi[i];
+      if (qhi - qlo <= 16) {  // few: a candidate per lane against each of the others
+        const int q = qlo + lane;
+        const bool mine = q < qhi && sh.q_taken[q] != 0;
+        const double s = q < qhi ? sh.q_s64[q] : 0.0;
+        const int j = q < qhi ? sh.q_idx[q] : 0;
+        bool wrong = false;
+        for (int o = qlo; o < qhi; ++o)
+          wrong |= mine && sh.q_taken[o] == 0 && !pair_less(s, j, sh.q_s64[o], sh.q_idx[o]);
+        if (__ballot(wrong) != 0ull && lane == 0) atomicMin(&sh.bad_first, i);
+        continue;
+      }
       double mt_s = -INFINITY, mu_s = INFINITY;
       int mt_j = -1, mu_j = 0x7fffffff;
       for (int q = qlo + lane; q < qhi; q += kWave) {
@@ -479,10 +591,7 @@ __device__ __forceinline__ void retain_body(
       // fp64 picks other tokens at stage `bad`: undo the later stages, correct this one
       for (int j = tid; j < n; j += kRetThreads) {
         const unsigned char o = sh.owner[j];
-        if (o < kOwnPivot && (int)o > bad) {
-          clear_bit(sh.R, (uint32_t)j);
-          sh.owner[j] = kOwnNone;
-        }
+        if (o < kOwnPivot && (int)o > bad) sh.owner[j] = kOwnNone;
       }
       const int qlo = sh.st_qlo[bad], qhi = sh.st_qhi[bad];
       int need = 0;
@@ -495,14 +604,8 @@ __device__ __forceinline__ void retain_body(
         for (int o = qlo; o < qhi && beaten < need; ++o)
           beaten += pair_less(sh.q_s64[o], sh.q_idx[o], s, j) ? 1 : 0;
         const bool chosen = beaten < need;
-        if (sh.q_taken[q] && !chosen) {
-          clear_bit(sh.R, (uint32_t)j);
-          sh.owner[j] = kOwnNone;
-        }
-        if (!sh.q_taken[q] && chosen) {
-          set_bit(sh.R, (uint32_t)j);
-          sh.owner[j] = (unsigned char)bad;
-        }
+        if (sh.q_taken[q] && !chosen) sh.owner[j] = kOwnNone;
+        if (!sh.q_taken[q] && chosen) sh.owner[j] = (unsigned char)bad;
       }
       next = bad + 1;
       __syncthreads();
@@ -516,10 +619,7 @@ __device__ __forceinline__ void retain_body(
       const int i = fb_first;
       for (int j = tid; j < n; j += kRetThreads) {
         const unsigned char o = sh.owner[j];
-        if (o < kOwnPivot && (int)o >= i) {
-          clear_bit(sh.R, (uint32_t)j);
-          sh.owner[j] = kOwnNone;
-        }
+        if (o < kOwnPivot && (int)o >= i) sh.owner[j] = kOwnNone;
       }
       const int quota = sp.quota(i);
       const float lo = mono_inv((uint32_t)(sh.st_kab[i][0] >> 32)) - two_tau;
@@ -529,10 +629,9 @@ __device__ __forceinline__ void retain_body(
       __syncthreads();
       int n_in = 0;
       for (int j = tid; j < n; j += kRetThreads) {
-        if (bit_of(sh.R, (uint32_t)j)) continue;
+        if (sh.owner[j] != kOwnNone) continue;
         const float s = ld_dev<COH>(&Srow[j]) + 0.0f;
         if (s < lo) {  // below the band: certainly among the quota lowest
-          set_bit(sh.R, (uint32_t)j);
           sh.owner[j] = (unsigned char)i;
           ++n_in;
         } else if (s <= hi) {
@@ -546,8 +645,8 @@ __device__ __forceinline__ void retain_body(
 #pragma unroll
       for (int w = 0; w < kRetWaves; ++w) need -= sh.wcnt[w];
       const int nU = sh.cnt;
-      const unsigned char* prow = pivot_row<COH>(g, X, esz, sm, b, i, piv);
-      const double pp_i = pl2 ? ld_dev<COH>(&pl2[b * g.Ppad + i]) : 0.0;
+      const unsigned char* prow = stage_pivot(i);
+      const double pp_i = pl2 ? sh.pl2[i] : 0.0;
       for (int u = wave; u < nU; u += kRetWaves) {
         const unsigned char* xrow = Xb + (long)sweep_idx[u] * rowbytes;
         const double s64 = pl2 ? row_cosine_f64<DT, true, kRetInFlight>(prow, xrow, g.D, lane, pp_i)
@@ -561,10 +660,7 @@ __device__ __forceinline__ void retain_body(
         int beaten = 0;
         for (int o = 0; o < nU && beaten < need; ++o)
           beaten += pair_less(sweep_s64[o], sweep_idx[o], su, ju) ? 1 : 0;
-        if (beaten < need) {
-          set_bit(sh.R, (uint32_t)ju);
-          sh.owner[ju] = (unsigned char)i;
-        }
+        if (beaten < need) sh.owner[ju] = (unsigned char)i;
       }
       next = i + 1;
       __syncthreads();
@@ -572,11 +668,19 @@ __device__ __forceinline__ void retain_body(
   }
   __syncthreads();
 
-  // emit the retained indices in ascending order
-  const int per = (words + kRetThreads - 1) / kRetThreads;
-  const int w0 = tid * per;
-  int mine = 0;
-  for (int t = w0; t < w0 + per && t < words; ++t) mine += __popc(sh.R[t]);
+  // emit the retained indices in ascending order: a thread owns 4, 8, 12 or 16 consecutive tokens
+  const int per = (n + 4 * kRetThreads - 1) / (4 * kRetThreads);  // groups of four tokens (uniform)
+  const int j0 = tid * per * 4;
+  uint32_t kept = 0u;  // bit r: token j0 + r is retained
+  for (int q = 0; q < per; ++q) {
+    if (j0 + 4 * q < n) {  // (the bytes past the last token were cleared to kOwnNone with it)
+      const uint32_t o4 = reinterpret_cast<const uint32_t*>(sh.owner)[tid * per + q];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        kept |= ((o4 >> (8 * r)) & 0xffu) != kOwnNone ? 1u << (4 * q + r) : 0u;
+    }
+  }
+  const int mine = __popc(kept);
   int off = wave_excl_scan(mine, lane);
   const int wtotal = __builtin_amdgcn_readlane(off + mine, 63);
   if (lane == 0) sh.wcnt[wave] = wtotal;
@@ -584,25 +688,21 @@ __device__ __forceinline__ void retain_body(
 #pragma unroll
   for (int w = 0; w < kRetWaves; ++w) off += w < wave ? sh.wcnt[w] : 0;
   int* out = keep + sm.keep0 + off;
-  for (int t = w0; t < w0 + per && t < words; ++t) {
-    uint32_t m = sh.R[t];
-    while (m) {
-      int bit = __ffs(m) - 1;
-      st_dev<COH>(out++, t * 32 + bit);
-      m &= m - 1;
-    }
+  while (kept) {
+    st_dev<COH>(out++, j0 + __ffs(kept) - 1);
+    kept &= kept - 1;
   }
 }
 
 // grid: B blocks of kRetThreads: block b builds the retained set of sample b.
-template <int DT, bool PACKED>
+template <int DT, bool WIDE>
 __global__ __launch_bounds__(kRetThreads) void k_retain(
     Geo g, const float* __restrict__ S, const unsigned long long* __restrict__ lists,
     const int* __restrict__ piv, const void* __restrict__ X, int* __restrict__ keep,
     int* __restrict__ cu_keep_out, double* __restrict__ scr_f64, float two_tau,
     const double* __restrict__ pl2) {
   __shared__ RetainShared sh;
-  retain_body<DT, false, PACKED>(g, blockIdx.x, S, lists, piv, X, keep, cu_keep_out, scr_f64,
+  retain_body<DT, false, WIDE>(g, blockIdx.x, S, lists, piv, X, keep, cu_keep_out, scr_f64,
                                  two_tau, sh, pl2);
 }
 
