@@ -378,30 +378,45 @@ thread_local StageEvents t_stage;
     }                                                                                           \
   } while (0)
 
-// Fills the ragged offsets (no-op for dense batches) and points g at them.
-dart_status launch_prepare(Plan& p, void* ws, hipStream_t st) {
-  if (p.g.cu == nullptr) return DART_OK;
-  int* cu_keep = at<int>(ws, p.o_cu_keep);
-  int* tile_start = at<int>(ws, p.o_tile_start);
+// Points g at the ragged offsets in the workspace (no-op for dense batches); the caller launches
+// what fills them.
+PrepareArgs prepare_args(Plan& p, void* ws) {
+  PrepareArgs a = {};
+  if (p.g.cu == nullptr) return a;
+  a.cu_keep = at<int>(ws, p.o_cu_keep);
+  a.tile_start = at<int>(ws, p.o_tile_start);
+  a.status = at<int>(ws, p.o_status);
   // (only where the ordering kernel's B*P workgroups, one per compute unit, need several rounds)
-  int* by_size = p.g.B <= kMaxBySize && (long)p.g.B * p.g.P > compute_units()
-                     ? at<int>(ws, p.o_by_size) : nullptr;
-  DART_LAUNCH(k_prepare, dim3(1), dim3(1024), 0, st, p.g, cu_keep, tile_start,
-              at<int>(ws, p.o_status), by_size);
+  a.by_size = p.g.B <= kMaxBySize && (long)p.g.B * p.g.P > compute_units()
+                  ? at<int>(ws, p.o_by_size) : nullptr;
+  p.g.cu_keep = a.cu_keep;
+  p.g.tile_start = a.tile_start;
+  p.g.by_size = a.by_size;
+  return a;
+}
+
+// Fills the ragged offsets (no-op for dense batches).  seq_cu, seq_cu_out: see PrepareArgs.
+dart_status launch_prepare(Plan& p, void* ws, hipStream_t st, const int* seq_cu = nullptr,
+                           int* seq_cu_out = nullptr) {
+  if (p.g.cu == nullptr) return DART_OK;
+  PrepareArgs a = prepare_args(p, ws);
+  a.seq_cu = seq_cu;
+  a.seq_cu_out = seq_cu_out;
+  DART_LAUNCH(k_prepare, dim3(1), dim3(1024), 0, st, p.g, a);
   DART_LAUNCH_CHECK();
-  p.g.cu_keep = cu_keep;
-  p.g.tile_start = tile_start;
-  p.g.by_size = by_size;
   return DART_OK;
 }
 
 // keep_cached: the rows will be read again soon (they are the hidden states themselves).
-dart_status launch_row_l1(const Plan& p, const void* C, int Dc, long ldc, float* l1,
-                          bool keep_cached, hipStream_t st, double* l2sq = nullptr) {
+// Ragged batches: also fills the ragged offsets (a block of the same launch).
+dart_status launch_row_l1(Plan& p, const void* C, int Dc, long ldc, float* l1, bool keep_cached,
+                          void* ws, hipStream_t st, double* l2sq = nullptr) {
   constexpr int ROWS = 1;  // one row per wave measured best (more, shorter-lived waves)
   const int rows = p.g.total_N;
-  if (rows == 0) return DART_OK;
-  const int blocks = (int)round_up8((rows + 4 * ROWS - 1) / (4 * ROWS));
+  if (rows == 0) return launch_prepare(p, ws, st);
+  const PrepareArgs prep = prepare_args(p, ws);
+  const bool ragged = p.g.cu != nullptr;
+  const int blocks = (int)round_up8((rows + 4 * ROWS - 1) / (4 * ROWS)) + (ragged ? kXcds : 0);
   // The 256 MB memory-side cache serves the score kernel's second pass if this pass leaves
   // the rows there: measured 31 instead of 38 us on that kernel for 0.7 us more on this one
   // at 189 MB; at 264 MB this pass loses 7 us and that one gains 0.7; a loss for matrices
@@ -409,30 +424,27 @@ dart_status launch_row_l1(const Plan& p, const void* C, int Dc, long ldc, float*
   // With spans the caller moves whole sequences afterwards, which sweeps that cache anyway:
   // measured slower with ordinary loads there.
   const bool keep = keep_cached && (double)rows * ldc * p.esz <= 224e6;
-  double* const no_l2sq = nullptr;
+#define DART_LAUNCH_L1_AS(DT, KEEP, SPAN, L2SQ)                                                  \
+  do {                                                                                           \
+    if (ragged)                                                                                  \
+      DART_LAUNCH((k_row_l1<DT, ROWS, KEEP, SPAN, L2SQ, true>), dim3(blocks), dim3(256), 0, st,  \
+                  C, Dc, ldc, rows, l1, p.g, l2sq, prep);                                        \
+    else                                                                                         \
+      DART_LAUNCH((k_row_l1<DT, ROWS, KEEP, SPAN, L2SQ, false>), dim3(blocks), dim3(256), 0, st, \
+                  C, Dc, ldc, rows, l1, p.g, l2sq, prep);                                        \
+  } while (0)
 #define DART_LAUNCH_L1(DT)                                                                       \
   do {                                                                                           \
-    if (l2sq && p.g.span)                                                                        \
-      DART_LAUNCH((k_row_l1<kBF16, ROWS, false, true, true>), dim3(blocks), dim3(256), 0,        \
-                  st, C, Dc, ldc, rows, l1, p.g, l2sq);                                          \
-    else if (l2sq && keep)                                                                       \
-      DART_LAUNCH((k_row_l1<kBF16, ROWS, true, false, true>), dim3(blocks), dim3(256), 0,        \
-                  st, C, Dc, ldc, rows, l1, p.g, l2sq);                                          \
-    else if (l2sq)                                                                               \
-      DART_LAUNCH((k_row_l1<kBF16, ROWS, false, false, true>), dim3(blocks), dim3(256),          \
-                  0, st, C, Dc, ldc, rows, l1, p.g, l2sq);                                       \
-    else if (p.g.span)                                                                           \
-      DART_LAUNCH((k_row_l1<DT, ROWS, false, true>), dim3(blocks), dim3(256), 0, st, C,          \
-                  Dc, ldc, rows, l1, p.g, no_l2sq);                                              \
-    else if (keep)                                                                               \
-      DART_LAUNCH((k_row_l1<DT, ROWS, true, false>), dim3(blocks), dim3(256), 0, st, C,          \
-                  Dc, ldc, rows, l1, p.g, no_l2sq);                                              \
-    else                                                                                         \
-      DART_LAUNCH((k_row_l1<DT, ROWS, false, false>), dim3(blocks), dim3(256), 0, st, C,         \
-                  Dc, ldc, rows, l1, p.g, no_l2sq);                                              \
+    if (l2sq && p.g.span) DART_LAUNCH_L1_AS(kBF16, false, true, true);                           \
+    else if (l2sq && keep) DART_LAUNCH_L1_AS(kBF16, true, false, true);                          \
+    else if (l2sq) DART_LAUNCH_L1_AS(kBF16, false, false, true);                                 \
+    else if (p.g.span) DART_LAUNCH_L1_AS(DT, false, true, false);                                \
+    else if (keep) DART_LAUNCH_L1_AS(DT, true, false, false);                                    \
+    else DART_LAUNCH_L1_AS(DT, false, false, false);                                             \
   } while (0)
   if (p.g.dtype == kBF16) DART_LAUNCH_L1(kBF16); else DART_LAUNCH_L1(kF32);
 #undef DART_LAUNCH_L1
+#undef DART_LAUNCH_L1_AS
   DART_LAUNCH_CHECK();
   return DART_OK;
 }
@@ -794,12 +806,14 @@ dart_status reduce_impl(const dart_desc* desc, const void* X, const void* crit, 
   // retained-set kernel 10 % on near-duplicate video frames)
   p.norms_given = p.g.mode != kGiven && p.g.Pin > 0 && crit == X && p.g.dtype == kBF16 &&
                   !l1_given && (double)p.g.total_N * p.g.ld * p.esz <= 1e9;
-  DART_TRY(launch_prepare(p, ws, st));
-  stage(0);
   // (the one-launch path computes its own norms: not for profiled calls or the caller's norms)
-  if (p.fusable && crit == X && events == nullptr && !l1_given && p.g.total_N > 0 &&
-      fused_enabled())
-    return launch_fused(p, X, pos, Y, pos_out, keep, cu_keep, piv, S, ws, st);
+  const bool fused = p.fusable && crit == X && events == nullptr && !l1_given && p.g.total_N > 0 &&
+                     fused_enabled();
+  // a norm pass fills the ragged offsets on the side (as part of its stage)
+  const bool norm_pass = !fused && p.g.mode != kGiven && p.g.Pin > 0 && !l1_given;
+  if (!norm_pass) DART_TRY(launch_prepare(p, ws, st));
+  stage(0);
+  if (fused) return launch_fused(p, X, pos, Y, pos_out, keep, cu_keep, piv, S, ws, st);
   if (p.g.mode == kGiven) {
     // the caller's pivots: check them, compute their norms; no pass over the criterion
     if (random) {
@@ -813,8 +827,8 @@ dart_status reduce_impl(const dart_desc* desc, const void* X, const void* crit, 
     DART_TRY(launch_pivot_norms(p, X, piv, 0, piv, ws, st));
   } else {
     // pivots chosen among the tokens (none if all of them come from outside) ...
-    if (p.g.Pin > 0 && !l1_given)
-      DART_TRY(launch_row_l1(p, crit, crit_D, crit_ld, l1, crit == X, st,
+    if (norm_pass)
+      DART_TRY(launch_row_l1(p, crit, crit_D, crit_ld, l1, crit == X, ws, st,
                              p.norms_given ? at<double>(ws, p.o_l2) : nullptr));
     stage(1);
     if (p.g.Pin > 0)
@@ -897,11 +911,12 @@ dart_status dart_select_pivots(const dart_desc* desc, const void* X, const void*
   DART_TRY(check_ws(p, ws, ws_bytes));
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* l1 = l1_out ? l1_out : at<float>(ws, p.o_l1);
-  DART_TRY(launch_prepare(p, ws, st));
+  const bool norm_pass = p.g.mode != kRandom && p.g.Pin > 0;
+  if (!norm_pass) DART_TRY(launch_prepare(p, ws, st));
   if (p.g.mode == kRandom) {  // no criterion is read and l1_out is left as it is
     DART_TRY(launch_random_pivots(p, piv, st));
-  } else if (p.g.Pin > 0) {
-    DART_TRY(launch_row_l1(p, crit, crit_D, crit_ld, l1, false, st));
+  } else if (norm_pass) {
+    DART_TRY(launch_row_l1(p, crit, crit_D, crit_ld, l1, false, ws, st));
     DART_TRY(launch_select_pivots(p, X, crit, crit_D, crit_ld, l1, piv, ws, st));
   }
   if (p.g.Pe > 0) DART_TRY(launch_pivot_norms(p, X, piv, p.g.Pin, piv, ws, st));
@@ -981,38 +996,26 @@ dart_status dart_compact_sequences(const dart_desc* desc, const int32_t* seq_cu,
     return DART_ERR_SHAPE;
   DART_TRY(check_ws(p, ws, ws_bytes));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  DART_TRY(launch_prepare(p, ws, st));
+  DART_TRY(launch_prepare(p, ws, st, seq_cu, seq_cu_out));
   DART_TRY(launch_given_status(p, nullptr, ws, st));
   // every sequence loses its pruned vision tokens; at most this many rows remain
   const long rows_bound = (long)p.g.x_rows - p.g.total_N + p.keep_rows_bound;
-  DART_LAUNCH(k_seq_offsets, dim3(1), dim3(1024), 0, st, p.g, seq_cu, seq_cu_out,
-              at<int>(ws, p.o_status));
-  DART_LAUNCH_CHECK();
   if (p.g.B == 0 || rows_bound <= 0) return DART_OK;
-  DART_LAUNCH(k_seq_row_map, dim3((unsigned)((rows_bound + 255) / 256)), dim3(256), 0, st,
-              p.g, seq_cu, seq_cu_out, keep, row_map);
-  DART_LAUNCH_CHECK();
-  const int* n_rows = seq_cu_out + p.g.B;
-  for (int i0 = 0; i0 < n_tensors; i0 += kSeqOps) {
-    SeqOps ops;
-    const int cnt = n_tensors - i0 < kSeqOps ? n_tensors - i0 : kSeqOps;
-    for (int i = 0; i < kSeqOps; ++i) {
-      const dart_row_tensor& t = tensors[i0 + (i < cnt ? i : 0)];
+  SeqPos sp = {reinterpret_cast<const long long*>(pos), reinterpret_cast<long long*>(pos_out),
+               (long)pos_plane_stride, (long)pos_out_plane_stride, pos_planes};
+  for (int i0 = 0; i0 == 0 || i0 < n_tensors; i0 += kSeqOps) {
+    SeqOps ops = {};
+    const int cnt = std::min(n_tensors - i0, kSeqOps);
+    for (int i = 0; i < cnt; ++i) {
+      const dart_row_tensor& t = tensors[i0 + i];
       ops.src[i] = static_cast<const unsigned char*>(t.src);
       ops.dst[i] = static_cast<unsigned char*>(t.dst);
       ops.row_bytes[i] = t.row_bytes;
       ops.src_ld[i] = t.src_ld_bytes;
       ops.dst_ld[i] = t.dst_ld_bytes;
     }
-    DART_LAUNCH(k_gather_rows, dim3((unsigned)round_up8((rows_bound + 3) / 4), cnt), dim3(256), 0,
-                st, ops, n_rows, row_map);
-    DART_LAUNCH_CHECK();
-  }
-  if (pos_planes > 0) {
-    DART_LAUNCH(k_gather_pos, dim3((unsigned)((rows_bound + 255) / 256), pos_planes),
-                dim3(256), 0, st, n_rows, row_map,
-                reinterpret_cast<const long long*>(pos), (long)pos_plane_stride,
-                reinterpret_cast<long long*>(pos_out), (long)pos_out_plane_stride);
+    DART_LAUNCH(k_gather_rows, dim3((unsigned)round_up8((rows_bound + 3) / 4), std::max(cnt, 1)),
+                dim3(256), 0, st, p.g, ops, cnt, i0 == 0, seq_cu, seq_cu_out, keep, row_map, sp);
     DART_LAUNCH_CHECK();
   }
   return DART_OK;

@@ -6,7 +6,7 @@
 
 namespace dart {
 
-// Ragged batches only.  One block of 1024 threads: validates the offsets and every
+// Ragged batches only.  One block of THREADS threads: validates the offsets and every
 // sample and writes the packed offsets cu_keep[B+1] (retained rows; a skipped
 // sample keeps 0) and tile_start[B+1] (score tiles of g.tile_rows rows).  status[0] becomes
 // 1 if a non-empty sample was rejected (its sizes or budget, or a span that leaves X), 2 if
@@ -16,26 +16,48 @@ namespace dart {
 // (ties in batch order).  The ordering kernel runs one workgroup per compute unit, a list's
 // time grows with its sample's length, and workgroups start in id order: with the long
 // samples first the short ones fill the gaps at the end instead of the other way round.
-__global__ __launch_bounds__(1024) void k_prepare(Geo g, int* __restrict__ cu_keep,
-                                                  int* __restrict__ tile_start,
-                                                  int* __restrict__ status,
-                                                  int* __restrict__ by_size) {
-  __shared__ int red[2][16];
-  __shared__ int carry[2];
+// seq_cu (optional, spans only): sequence b is rows [seq_cu[b], seq_cu[b+1]) of the caller's
+// per-token tensors and must contain its span [span[b], span[b] + N_b).  seq_cu_out[B+1] gets the
+// new offsets: sequence b shrinks by N_b - K_b rows (K_b = 0 for a skipped sample, whose vision
+// tokens are all dropped).  status[2] = 1 and all-zero offsets if seq_cu is not a non-decreasing
+// sequence from 0 to x_rows, a span is not inside its sequence, or cu_seqlens is broken.
+struct PrepareArgs {
+  int* cu_keep;
+  int* tile_start;
+  int* status;
+  int* by_size;
+  const int* seq_cu;
+  int* seq_cu_out;
+};
+
+template <int THREADS>
+__device__ __forceinline__ void prepare_body(const Geo& g, const PrepareArgs& a) {
+  constexpr int kWaves = THREADS / kWave;
+  __shared__ int red[3][kWaves];
+  __shared__ int carry[3];
   __shared__ int len_of[kMaxBySize];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int broken = 0;
-  for (int b = tid; b < g.B; b += 1024) broken |= g.cu[b + 1] < g.cu[b] ? 1 : 0;
-  if (tid == 0) {
-    carry[0] = 0;
-    carry[1] = 0;
-    broken |= (g.cu[0] != 0 || g.cu[g.B] != g.total_N) ? 1 : 0;
+  int broken = 0, seq_bad = 0;
+  for (int b = tid; b < g.B; b += THREADS) {
+    const int n = g.cu[b + 1] - g.cu[b];
+    broken |= n < 0 ? 1 : 0;
+    if (a.seq_cu) {
+      const int lo = a.seq_cu[b], hi = a.seq_cu[b + 1];
+      seq_bad |= (hi < lo || g.span[b] < lo || (long)g.span[b] + n > (long)hi) ? 1 : 0;
+    }
   }
-  broken = __syncthreads_or(broken);
+  if (tid == 0) {
+    carry[0] = carry[1] = carry[2] = 0;
+    broken |= (g.cu[0] != 0 || g.cu[g.B] != g.total_N) ? 1 : 0;
+    if (a.seq_cu) seq_bad |= (a.seq_cu[0] != 0 || a.seq_cu[g.B] != g.x_rows) ? 1 : 0;
+  }
+  const int flags = __syncthreads_or(broken | (seq_bad << 1));
+  broken = flags & 1;
+  seq_bad = flags != 0;  // (broken offsets: the lengths are meaningless)
   int bad = 0;
-  for (int b0 = 0; b0 < g.B; b0 += 1024) {
+  for (int b0 = 0; b0 < g.B; b0 += THREADS) {
     const int b = b0 + tid;
-    int k = 0, tiles = 0;
+    int k = 0, tiles = 0, rows = 0;
     if (b < g.B && !broken) {
       int n = g.cu[b + 1] - g.cu[b];
       int kb = budget_of(g, n);
@@ -48,50 +70,56 @@ __global__ __launch_bounds__(1024) void k_prepare(Geo g, int* __restrict__ cu_ke
       } else if (n != 0) {
         bad = 1;
       }
+      if (a.seq_cu && !seq_bad) rows = (a.seq_cu[b + 1] - a.seq_cu[b]) - n + k;
     }
-    int sk = wave_excl_scan(k, lane), st = wave_excl_scan(tiles, lane);
+    const int s[3] = {wave_excl_scan(k, lane), wave_excl_scan(tiles, lane), wave_excl_scan(rows, lane)};
     if (lane == 63) {
-      red[0][w] = sk + k;
-      red[1][w] = st + tiles;
+      red[0][w] = s[0] + k;
+      red[1][w] = s[1] + tiles;
+      red[2][w] = s[2] + rows;
     }
     __syncthreads();
-    int bk = carry[0], bt = carry[1], tk = 0, tt = 0;
+    int base[3], sum[3];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      bk += i < w ? red[0][i] : 0;
-      bt += i < w ? red[1][i] : 0;
-      tk += red[0][i];
-      tt += red[1][i];
+    for (int q = 0; q < 3; ++q) {
+      base[q] = carry[q];
+      sum[q] = 0;
+#pragma unroll
+      for (int i = 0; i < kWaves; ++i) {
+        base[q] += i < w ? red[q][i] : 0;
+        sum[q] += red[q][i];
+      }
     }
     if (b < g.B) {
-      cu_keep[b] = bk + sk;
-      tile_start[b] = bt + st;
+      a.cu_keep[b] = base[0] + s[0];
+      a.tile_start[b] = base[1] + s[1];
+      if (a.seq_cu) a.seq_cu_out[b] = base[2] + s[2];
     }
     __syncthreads();
-    if (tid == 0) {
-      carry[0] += tk;
-      carry[1] += tt;
-    }
+    if (tid < 3) carry[tid] += tid == 0 ? sum[0] : tid == 1 ? sum[1] : sum[2];
     __syncthreads();
   }
   bad = __syncthreads_or(bad);
-  if (by_size != nullptr) {  // (block-uniform; g.B <= kMaxBySize)
-    const int n = tid < g.B && !broken ? g.cu[tid + 1] - g.cu[tid] : 0;
-    if (tid < g.B) len_of[tid] = n;
+  if (a.by_size != nullptr) {  // (block-uniform; g.B <= kMaxBySize)
+    for (int b = tid; b < g.B; b += THREADS) len_of[b] = broken ? 0 : g.cu[b + 1] - g.cu[b];
     __syncthreads();
-    if (tid < g.B) {
+    for (int b = tid; b < g.B; b += THREADS) {
+      const int n = len_of[b];
       int rank = 0;
-      for (int o = 0; o < g.B; ++o) rank += (len_of[o] > n || (len_of[o] == n && o < tid)) ? 1 : 0;
-      by_size[rank] = tid;
+      for (int o = 0; o < g.B; ++o) rank += (len_of[o] > n || (len_of[o] == n && o < b)) ? 1 : 0;
+      a.by_size[rank] = b;
     }
   }
   if (tid == 0) {
-    cu_keep[g.B] = carry[0];
-    tile_start[g.B] = carry[1];
-    status[0] = broken ? 2 : bad;
-    status[2] = 0;  // set by k_seq_offsets if it runs after this
+    a.cu_keep[g.B] = carry[0];
+    a.tile_start[g.B] = carry[1];
+    if (a.seq_cu) a.seq_cu_out[g.B] = carry[2];
+    a.status[0] = broken ? 2 : bad;
+    a.status[2] = a.seq_cu ? seq_bad : 0;
   }
 }
+
+__global__ __launch_bounds__(1024) void k_prepare(Geo g, PrepareArgs a) { prepare_body<1024>(g, a); }
 
 // Caller-supplied pivots: status[1] = 1 if any processed sample's Pin indices are not
 // distinct indices inside the sample, else 0.  grid: 1 block of 1024.
@@ -278,104 +306,63 @@ __global__ __launch_bounds__(256) void k_gather(Geo g, int esz, const void* __re
 // ---- whole-sequence compaction (Appendix D: text before the vision span, the retained
 // vision tokens, text after it) ------------------------------------------------------
 
-// One block of 1024.  Sequence b is rows [seq_cu[b], seq_cu[b+1]) of the caller's per-token
-// tensors and must contain its span [span[b], span[b] + N_b).  Writes the new offsets
-// seq_cu_out[B+1]: sequence b shrinks by N_b - K_b rows (K_b = 0 for a skipped sample, whose
-// vision tokens are all dropped).  status[2] = 1 and all-zero offsets if seq_cu is not a
-// non-decreasing sequence from 0 to x_rows or a span is not inside its sequence.
-__global__ __launch_bounds__(1024) void k_seq_offsets(Geo g, const int* __restrict__ seq_cu,
-                                                      int* __restrict__ seq_cu_out,
-                                                      int* __restrict__ status) {
-  __shared__ int red[16];
-  __shared__ int carry;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int bad = 0;
-  for (int b = tid; b < g.B; b += 1024) {
-    const int lo = seq_cu[b], hi = seq_cu[b + 1];
-    const int n = g.cu[b + 1] - g.cu[b];
-    bad |= (hi < lo || g.span[b] < lo || (long)g.span[b] + n > (long)hi) ? 1 : 0;
-  }
-  if (tid == 0) {
-    carry = 0;
-    // status[0] == 2: k_prepare found cu_seqlens itself broken (lengths are meaningless)
-    bad |= (status[0] == 2 || seq_cu[0] != 0 || seq_cu[g.B] != g.x_rows) ? 1 : 0;
-  }
-  bad = __syncthreads_or(bad);
-  for (int b0 = 0; b0 < g.B; b0 += 1024) {
-    const int b = b0 + tid;
-    int len = 0;
-    if (b < g.B && !bad) {
-      const int n = g.cu[b + 1] - g.cu[b];
-      len = (seq_cu[b + 1] - seq_cu[b]) - n + (g.cu_keep[b + 1] - g.cu_keep[b]);
-    }
-    const int sc = wave_excl_scan(len, lane);
-    if (lane == 63) red[w] = sc + len;
-    __syncthreads();
-    int base = carry, tot = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      base += i < w ? red[i] : 0;
-      tot += red[i];
-    }
-    if (b < g.B) seq_cu_out[b] = base + sc;
-    __syncthreads();
-    if (tid == 0) carry += tot;
-    __syncthreads();
-  }
-  if (tid == 0) {
-    seq_cu_out[g.B] = carry;
-    status[2] = bad;
-  }
-}
-
-// row_map[r] = row of the original tensors that row r of the shortened ones comes from.
-// grid: ceil(rows_bound / 256) blocks of 256; rows beyond seq_cu_out[B] are left alone.
-__global__ __launch_bounds__(256) void k_seq_row_map(Geo g, const int* __restrict__ seq_cu,
-                                                     const int* __restrict__ seq_cu_out,
-                                                     const int* __restrict__ keep,
-                                                     int* __restrict__ row_map) {
-  const long r = (long)blockIdx.x * 256 + threadIdx.x;
-  if (r >= seq_cu_out[g.B]) return;
-  int lo = 0, hi = g.B;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (seq_cu_out[mid] <= r) lo = mid; else hi = mid;
-  }
-  const int b = lo;
-  const int t = (int)(r - seq_cu_out[b]);
-  const int n = g.cu[b + 1] - g.cu[b];
-  const int k = g.cu_keep[b + 1] - g.cu_keep[b];
-  const int before = g.span[b] - seq_cu[b];  // text rows ahead of the span
-  int src;
-  if (t < before) {
-    src = seq_cu[b] + t;
-  } else if (t < before + k) {
-    int kr = keep[g.cu_keep[b] + (t - before)];
-    kr = kr < 0 ? 0 : (kr < n ? kr : n - 1);  // a caller's bad index must not leave the span
-    src = g.span[b] + kr;
-  } else {
-    src = g.span[b] + n + (t - before - k);
-  }
-  row_map[r] = src;
-}
-
 constexpr int kSeqOps = 8;  // tensors one gather launch moves
 struct SeqOps {
   const unsigned char* src[kSeqOps];
   unsigned char* dst[kSeqOps];
   long row_bytes[kSeqOps], src_ld[kSeqOps], dst_ld[kSeqOps];  // bytes, multiples of 16
 };
+struct SeqPos {  // position ids, plane-major
+  const long long* pos;
+  long long* pos_out;
+  long in_stride, out_stride;
+  int planes;
+};
 
-// dst row r = src row row_map[r] for every tensor of ops.  One wave per (row, tensor):
-// grid (ceil(rows_bound / 4) rounded up to a multiple of 8, tensors) blocks of 256 (with a
-// multiple of 8 in x the die of a block depends on its x only: xcd_contiguous); 16 bytes per
-// lane, 1 KiB per access.
-__global__ __launch_bounds__(256) void k_gather_rows(SeqOps ops, const int* __restrict__ n_rows,
-                                                     const int* __restrict__ row_map) {
+// Row r of the shortened batch comes from row src(r) of the original tensors: the rows of its
+// sequence before the span, then span + keep, then the rows behind the span.  Every wave works out
+// its row's source by itself (one load of the offsets per 64 samples and a ballot instead of a
+// chain of loads per halving), so that the map, the position ids and the tensors need one launch:
+// five launches of which three moved a few KB took 38 us on eight sequences of 1900 rows, two take
+// 28.  dst row r = src row src(r) for every tensor of ops; the waves of tensor 0 also write row_map
+// and the position planes (first: the first launch of the call).
+// One wave per (row, tensor): grid (ceil(rows_bound / 4) rounded up to a multiple of 8, tensors or
+// 1) blocks of 256 (with a multiple of 8 in x the die of a block depends on its x only:
+// xcd_contiguous); 16 bytes per lane, 1 KiB per access.  Rows beyond seq_cu_out[B] are left alone.
+__global__ __launch_bounds__(256) void k_gather_rows(Geo g, SeqOps ops, int n_ops, bool first,
+                                                     const int* __restrict__ seq_cu,
+                                                     const int* __restrict__ seq_cu_out,
+                                                     const int* __restrict__ keep,
+                                                     int* __restrict__ row_map, SeqPos sp) {
   const int lane = threadIdx.x & 63, o = blockIdx.y;
   const long r = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
-  if (r >= *n_rows) return;
-  const long src = row_map[r];
+  if (r >= seq_cu_out[g.B]) return;
+  int b = 0;  // the last sample whose offset is at most r
+  for (int b0 = 0; b0 < g.B; b0 += kWave) {
+    const unsigned long long m = __ballot(b0 + lane < g.B && seq_cu_out[b0 + lane] <= r);
+    if (m == 0ull) break;
+    b = b0 + 63 - __builtin_clzll(m);
+    if (m != ~0ull) break;
+  }
+  const int s0 = seq_cu[b], span = g.span[b], n = g.cu[b + 1] - g.cu[b], k0 = g.cu_keep[b];
+  const int k = g.cu_keep[b + 1] - k0;
+  const int t = (int)(r - seq_cu_out[b]), before = span - s0;  // text rows ahead of the span
+  long src;
+  if (t < before) {
+    src = s0 + t;
+  } else if (t < before + k) {
+    int kr = keep[k0 + (t - before)];
+    kr = kr < 0 ? 0 : (kr < n ? kr : n - 1);  // a caller's bad index must not leave the span
+    src = span + kr;
+  } else {
+    src = span + n + (t - before - k);
+  }
+  if (o == 0 && first) {
+    if (lane == 0) row_map[r] = (int)src;
+    for (int p = lane; p < sp.planes; p += kWave)
+      sp.pos_out[p * sp.out_stride + r] = sp.pos[p * sp.in_stride + src];
+  }
+  if (o >= n_ops) return;  // no tensors: the map and the position ids only
   const u32x4* in = reinterpret_cast<const u32x4*>(ops.src[o] + src * ops.src_ld[o]);
   u32x4* out = reinterpret_cast<u32x4*>(ops.dst[o] + r * ops.dst_ld[o]);
   const int pieces = (int)(ops.row_bytes[o] / 16);
@@ -392,19 +379,6 @@ __global__ __launch_bounds__(256) void k_gather_rows(SeqOps ops, const int* __re
       if (t < pieces) out[t] = v[u];
     }
   }
-}
-
-// Position ids, plane-major: pos_out[p*out_stride + r] = pos[p*in_stride + row_map[r]].
-// grid: (ceil(rows_bound / 256), planes) blocks of 256.
-__global__ __launch_bounds__(256) void k_gather_pos(const int* __restrict__ n_rows,
-                                                    const int* __restrict__ row_map,
-                                                    const long long* __restrict__ pos,
-                                                    long in_stride, long long* __restrict__ pos_out,
-                                                    long out_stride) {
-  const long r = (long)blockIdx.x * 256 + threadIdx.x;
-  if (r >= *n_rows) return;
-  const long p = blockIdx.y;
-  pos_out[p * out_stride + r] = pos[p * in_stride + row_map[r]];
 }
 
 }  // namespace dart

@@ -3,6 +3,7 @@
 // norm).  One streaming pass over [rows, Dc]; HBM-bound.
 #pragma once
 #include "common.hpp"
+#include "k_misc.hpp"
 
 namespace dart {
 
@@ -52,19 +53,26 @@ inline double l1_rel_bound(int dtype, int Dc) {
 // kernel's second pass (worth it only if the whole matrix fits there); otherwise
 // streaming (non-temporal) loads, which read faster.
 // SPAN: the samples' rows are spans of C (Geo::span); packed row r belongs to the sample b
-// with cu[b] <= r < cu[b+1] and lives at row span[b] + (r - cu[b]) of C.  Rows of a sample
-// that keeps nothing (skipped: its span may be invalid) are not read.
+// with cu[b] <= r < cu[b+1] and lives at row span[b] + (r - cu[b]) of C.  Rows of a span that
+// leaves C, or of broken offsets, are not read.
+// PREP: the first 8 blocks are not for rows: block 0 does k_prepare's work (this kernel needs
+// none of its results), which as a launch of its own took 4-5 us before this one.
 // L2SQ (bf16 only, when the rows are the hidden states themselves): also the squared
 // Euclidean norm of every row, which the score kernel divides by: piece sums in fp32 (see
 // piece_sq_sum_bf16), added in fp64 in a fixed lane-strided order plus butterfly, so the
 // result is a function of the row's bytes with a relative error of at most 3.5 * 2^-24.
-template <int DT, int ROWS, bool KEEP, bool SPAN, bool L2SQ = false>
+template <int DT, int ROWS, bool KEEP, bool SPAN, bool L2SQ, bool PREP>
 __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int Dc, long ldc,
                                                 int rows, float* __restrict__ l1, Geo g,
-                                                double* __restrict__ l2sq = nullptr) {
+                                                double* __restrict__ l2sq, PrepareArgs prep) {
+  if (PREP && blockIdx.x < kXcds) {
+    if (blockIdx.x == 0) prepare_body<256>(g, prep);
+    return;
+  }
+  const unsigned bid = blockIdx.x - (PREP ? kXcds : 0), blocks = gridDim.x - (PREP ? kXcds : 0);
   const int lane = threadIdx.x & 63;
   // (ordinary loads: the plain order measured faster; streaming loads: a die per eighth)
-  const long blk = KEEP ? (long)blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x);
+  const long blk = KEEP ? (long)bid : xcd_contiguous(bid, blocks);
   const long wave = blk * 4 + (threadIdx.x >> 6);
   const int esz = DT == kBF16 ? 2 : 4;
   const int pieces = Dc * esz / 16;
@@ -87,8 +95,9 @@ __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int 
         const int mid = (lo + hi) >> 1;
         if (g.cu[mid] <= row) lo = mid; else hi = mid;
       }
-      live[r] = g.cu_keep[lo + 1] != g.cu_keep[lo];
-      crow = live[r] ? (long)g.span[lo] + (row - g.cu[lo]) : 0;
+      const long at = row - g.cu[lo], n = (long)g.cu[lo + 1] - g.cu[lo], s0 = g.span[lo];
+      live[r] = at >= 0 && at < n && s0 >= 0 && s0 + n <= (long)g.x_rows;
+      crow = live[r] ? s0 + at : 0;
     }
     rp[r] = base + crow * rowbytes;
     acc[r] = 0.f;
