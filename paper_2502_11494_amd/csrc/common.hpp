@@ -331,45 +331,6 @@ __device__ __forceinline__ void row_l1_l2_f64(const void* row, int D, int lane, 
   l2 = wave_sum(b);
 }
 
-// The same for R rows at once (all their loads in flight together).  Rows past
-// `live` are skipped; each row's result is identical to row_l1_l2_f64's.
-template <int DT, int R>
-__device__ __forceinline__ void rows_l1_l2_f64(const void* const (&row)[R], int live, int D,
-                                               int lane, double (&l1)[R], double (&l2)[R]) {
-  const int pieces = D * (DT == kBF16 ? 2 : 4) / 16;
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  double a[R], b[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) a[r] = b[r] = 0.0;
-  for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
-    u32x4 v[R][8];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        int t = t0 + u * kWave + lane;
-        v[r][u] = (r < live && t < pieces) ? reinterpret_cast<const u32x4*>(row[r])[t] : zero;
-      }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        double x[8];
-        piece_to_f64<DT>(v[r][u], x);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          a[r] += fabs(x[e]);
-          b[r] = fma(x[e], x[e], b[r]);
-        }
-      }
-  }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    l1[r] = wave_sum(a[r]);
-    l2[r] = wave_sum(b[r]);
-  }
-}
-
 // Cosine of Eq. (7) between rows p and x in fp64; 0 if either norm is 0.
 // PPG: the squared norm of p is given (pp_given, an fp64 sum over the same row) and its
 // products are left out (a sixth of the arithmetic).

@@ -484,10 +484,10 @@ dart_status launch_select_pivots(const Plan& p, const void* X, const void* C, in
 #define DART_LAUNCH_PIVOTS(PER)                                                                  \
   do {                                                                                           \
     if (p.g.dtype == kBF16)                                                                      \
-      DART_LAUNCH((k_select_pivots<kBF16, 1024, PER>), dim3(p.g.B), dim3(1024), 0, st,           \
+      DART_LAUNCH((k_select_pivots<kBF16, PER>), dim3(p.g.B), dim3(1024), 0, st,           \
                   p.g, X, C, Dc, ldc, l1, piv, pl2, scr, tau);                                   \
     else                                                                                         \
-      DART_LAUNCH((k_select_pivots<kF32, 1024, PER>), dim3(p.g.B), dim3(1024), 0, st,            \
+      DART_LAUNCH((k_select_pivots<kF32, PER>), dim3(p.g.B), dim3(1024), 0, st,            \
                   p.g, X, C, Dc, ldc, l1, piv, pl2, scr, tau);                                   \
   } while (0)
   DART_FOR_VALUES_PER_THREAD(values_per_thread(p.g.max_N), DART_LAUNCH_PIVOTS);

@@ -26,12 +26,15 @@ __device__ __forceinline__ void order_scores_body(const Geo& g, int b, int i, co
   const int want = sp.stage_len(n, i);
   if (want == 0) return;  // the stage takes nothing
   const float* row = S + (long)g.P * sm.row0 + (long)i * n;
+  // (all loads before the first use, from clamped places: see select_pivots_body)
   float v[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    int j = tid + e * kSelThreads;
-    v[e] = (e * kSelThreads < n && j < n) ? ld_dev<COH>(&row[j]) + 0.0f : 0.f;
+    const int j = tid + e * kSelThreads;
+    v[e] = ld_dev<COH>(&row[j < n ? j : n - 1]);
   }
+#pragma unroll
+  for (int e = 0; e < PER; ++e) v[e] += 0.0f;  // -0 and +0 compare equal
   int first = 0;  // keys of the first sorted run (all of them unless the sort was split)
   collect_sorted<THREADS, true, PER>(v, n, want, tid, sh, &first);
   // offset of this stage's list = sum of the earlier stages' lengths: lane s of every wave

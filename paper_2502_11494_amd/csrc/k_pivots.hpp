@@ -8,59 +8,120 @@
 // every pivot, which the score kernel divides by.
 #pragma once
 #include "common.hpp"
-#include "k_select.hpp"
 
 namespace dart {
 
 constexpr int kPivLdsCand = 512;  // candidates whose fp64 norms fit in LDS
 
-template <int THREADS, int PER = kSelPerThread>
+// 1024 threads; PER values per thread, PER*1024 >= the longest sample.
+constexpr int kPivThreads = 1024, kPivWaves = kPivThreads / kWave, kPivGroups = kPivThreads / 4;
+
+template <int PER>
 struct PivotShared {
-  SelectShared<THREADS, PER> sel;
+  __attribute__((aligned(16))) uint32_t group[kPivGroups];
+  int cand[kPivThreads * PER];  // token indices
   double c64[kPivLdsCand];
   double l2[kPivLdsCand];
   int nU;
+  float thr;
 };
 
-// Pivot selection of sample b by one workgroup of THREADS (1024) threads.
+// An upper bound of the want-th lowest (1 <= want <= 64) of 256 values (the images of mono_of),
+// close enough to add few values to the want lowest: bisection of their range until at most one more
+// is below the bound, or a thousandth of the range is left (six to eight steps as a rule).  By one wave, lane l holding four values; every step is four
+// compares and their ballots.
+__device__ __forceinline__ uint32_t rank_bound_of_256(const u32x4& v, int want) {
+  const uint32_t none = mono_of(INFINITY);  // groups without a token: not part of the range
+  uint32_t lo = none, hi = 0u;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    lo = v[c] < lo ? v[c] : lo;
+    hi = v[c] != none && v[c] > hi ? v[c] : hi;
+  }
+  const int lane = threadIdx.x & 63;
+#define DART_MINMAX_STEP(J)                                                        \
+  {                                                                                \
+    const uint32_t a = (uint32_t)lane_xor<J>((int)lo, lane), b = (uint32_t)lane_xor<J>((int)hi, lane); \
+    lo = lo < a ? lo : a;                                                          \
+    hi = hi > b ? hi : b;                                                          \
+  }
+  DART_MINMAX_STEP(1) DART_MINMAX_STEP(2) DART_MINMAX_STEP(4) DART_MINMAX_STEP(8)
+  DART_MINMAX_STEP(16) DART_MINMAX_STEP(32)
+#undef DART_MINMAX_STEP
+  uint32_t l = __builtin_amdgcn_readfirstlane(lo), h = __builtin_amdgcn_readfirstlane(hi);
+  h = h > l ? h : l;
+  for (int step = 0; step < 10 && l < h; ++step) {  // the bound is in [l, h]
+    const uint32_t mid = l + ((h - l) >> 1);
+    const int cnt = __popcll(__builtin_amdgcn_ballot_w64(v.x <= mid)) +
+                    __popcll(__builtin_amdgcn_ballot_w64(v.y <= mid)) +
+                    __popcll(__builtin_amdgcn_ballot_w64(v.z <= mid)) +
+                    __popcll(__builtin_amdgcn_ballot_w64(v.w <= mid));
+    if (cnt >= want) h = mid; else l = mid + 1;
+    if (cnt == want || cnt == want + 1) break;  // close enough (h = mid)
+  }
+  return h;
+}
+
+// Pivot selection of sample b by one workgroup of kPivThreads threads.
 // l1 [total_N] fp32 criterion norms; piv [B*P] (the first Pin entries of a sample are
 // written); pl2 [B*Ppad] squared L2 norms of the pivots' hidden-state rows (0 for the
 // other slots); scr [2*total_N] doubles.
 // COH: l1 was written, and piv / pl2 will be read, by other workgroups of this launch.
-template <int DT, int THREADS, bool COH, int PER = kSelPerThread>
+template <int DT, bool COH, int PER>
 __device__ __forceinline__ void select_pivots_body(
     const Geo& g, int b, const void* X, const void* C, int Dc, long ldc, const float* l1,
-    int* piv, double* pl2, double* scr, float tau, PivotShared<THREADS, PER>& sh) {
-  constexpr int kSelThreads = THREADS;
-  constexpr int kSelWaves = THREADS / kWave;
+    int* piv, double* pl2, double* scr, float tau, PivotShared<PER>& sh) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const Sample sm = sample_of(g, b);
   if (tid < g.Ppad) st_dev<COH>(&pl2[b * g.Ppad + tid], 0.0);
   if (sm.k == 0) return;
   if (COH) stores_done();
-  __syncthreads();  // the zeros are ordered before the pivots' norms below
   const int n = sm.n, P = g.Pin;  // pivots chosen among the tokens; stride of piv is g.P
   const float sign = g.mode == kMaxL1 ? -1.f : 1.f;  // "lowest" of -norm = largest norm
 
+  // Candidates: every token that may belong to the exact top P.  The tokens form 256 groups (four
+  // threads each, dealt so that a sample of at most 256 tokens has one per group); the P-th lowest
+  // of the groups' lowest values is reached by P tokens, so with vsel at least that,
+  // {v <= vsel + 2.5 tau |vsel|} holds every token within the norm pass's error of the P-th best:
+  // usually P and a handful more.  They are ranked in fp64 below, so neither their order nor the
+  // exact P-th value is needed here.  (Two barriers; the histogram over the block's value range that
+  // this replaces had six.)
+  const int tok0 = (tid >> 2) + kPivGroups * (tid & 3);
+  // (all loads before the first use, from clamped places: a load whose value is used under its
+  // condition is waited for before the next one is issued, 0.3 us each)
   float v[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    int j = tid + e * kSelThreads;
-    v[e] = (e * kSelThreads < n && j < n) ? sign * ld_dev<COH>(&l1[sm.row0 + j]) + 0.0f : 0.f;
+    const int j = tok0 + e * kPivThreads;
+    v[e] = ld_dev<COH>(&l1[sm.row0 + (j < n ? j : n - 1)]);
   }
-  // Candidates: every token that may belong to the exact top P.  With vsel >= the P-th lowest
-  // fp32 value, {v <= vsel + 2.5 tau |vsel|} holds every token within the norm pass's error of
-  // the P-th best: usually P and a handful more.  They are ranked in fp64 below, so neither
-  // their order nor the exact P-th value is needed here.
-  const float vsel = rank_upper_bound<THREADS, PER>(v, n, P, tid, sh.sel);
-  const float thr = vsel + 2.5f * tau * fabsf(vsel);
-  if (tid == 0) sh.nU = 0;
-  __syncthreads();
+  float low = INFINITY;
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    const int j = tid + e * kSelThreads;
-    if (e * kSelThreads < n && j < n && v[e] <= thr)
-      sh.sel.buf[atomicAdd(&sh.nU, 1)] = ((unsigned long long)mono_of(v[e]) << 32) | (unsigned)j;
+    v[e] = tok0 + e * kPivThreads < n ? sign * v[e] + 0.0f : INFINITY;
+    low = fminf(low, v[e]);
+  }
+  low = fminf(low, lane_xor<1>(low, lane));
+  low = fminf(low, lane_xor<2>(low, lane));
+  if ((tid & 3) == 0) sh.group[tid >> 2] = mono_of(low);
+  if (tid == 0) sh.nU = 0;
+  __syncthreads();  // (and the zeros above are ordered before the pivots' norms below)
+  if (w == 0) {  // (alone it takes half as long as with all waves beside it)
+    const u32x4 g4 = reinterpret_cast<const u32x4*>(sh.group)[lane];
+    const float vsel = mono_inv(rank_bound_of_256(g4, P));
+    if (lane == 0) sh.thr = vsel + 2.5f * tau * fabsf(vsel);
+  }
+  __syncthreads();
+  const float thr = sh.thr;
+  uint32_t hit = 0u;  // (few threads have one)
+#pragma unroll
+  for (int e = 0; e < PER; ++e) hit |= v[e] <= thr ? 1u << e : 0u;
+  while (__builtin_amdgcn_ballot_w64(hit != 0u) != 0ull) {
+    if (hit != 0u) {
+      const int j = tok0 + (__ffs(hit) - 1) * kPivThreads;
+      hit &= hit - 1u;
+      if (j < n) sh.cand[atomicAdd(&sh.nU, 1)] = j;
+    }
   }
   __syncthreads();
   const int nU = sh.nU;  // 0 only if the norms are not numbers: then no pivot is written
@@ -70,31 +131,17 @@ __device__ __forceinline__ void select_pivots_body(
   const int esz = DT == kBF16 ? 2 : 4;
   const unsigned char* Xb = static_cast<const unsigned char*>(X) + (long)sm.xrow * g.ld * esz;
   const unsigned char* Cb = static_cast<const unsigned char*>(C) + (long)sm.xrow * ldc * esz;
-  // R candidates per wave at a time: 16 rows in flight per block with 4 or 16 waves
-  constexpr int R = 16 / kSelWaves;
-  for (int u0 = w * R; u0 < nU; u0 += kSelWaves * R) {
-    const int live = nU - u0 < R ? nU - u0 : R;
-    const void* crow[R];
-    const void* xrow[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int j = (int)(uint32_t)sh.sel.buf[u0 + (r < live ? r : 0)];
-      crow[r] = Cb + (long)j * ldc * esz;
-      xrow[r] = Xb + (long)j * g.ld * esz;
-    }
-    double a[R], q[R];
-    rows_l1_l2_f64<DT, R>(crow, live, Dc, lane, a, q);
+  for (int u = w; u < nU; u += kPivWaves) {  // a candidate per wave
+    const int j = sh.cand[u];
+    double a, q;
+    row_l1_l2_f64<DT>(Cb + (long)j * ldc * esz, Dc, lane, a, q);
     if (C != X) {
-      double dummy[R];
-      rows_l1_l2_f64<DT, R>(xrow, live, g.D, lane, dummy, q);
+      double unused;
+      row_l1_l2_f64<DT>(Xb + (long)j * g.ld * esz, g.D, lane, unused, q);
     }
     if (lane == 0) {
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (r < live) {
-          c64[u0 + r] = g.mode == kMaxL1 ? -a[r] : a[r];
-          l2s[u0 + r] = q[r];
-        }
+      c64[u] = g.mode == kMaxL1 ? -a : a;
+      l2s[u] = q;
     }
   }
   __syncthreads();
@@ -103,10 +150,10 @@ __device__ __forceinline__ void select_pivots_body(
     // a wave per candidate: lane o compares candidate o with it, the ballot counts
     const bool on = lane < nU;
     const double co = on ? c64[lane] : 0.0;
-    const int jo = on ? (int)(uint32_t)sh.sel.buf[lane] : 0;
-    for (int u = w; u < nU; u += kSelWaves) {
+    const int jo = on ? sh.cand[lane] : 0;
+    for (int u = w; u < nU; u += kPivWaves) {
       const double cu = c64[u];
-      const int ju = (int)(uint32_t)sh.sel.buf[u];
+      const int ju = sh.cand[u];
       const int cnt = __popcll(__ballot(on && (co < cu || (co == cu && jo < ju))));
       if (lane == 0 && cnt < P) {
         st_dev<COH>(&piv[b * g.P + cnt], ju);
@@ -115,13 +162,13 @@ __device__ __forceinline__ void select_pivots_body(
     }
     return;
   }
-  for (int u = tid; u < nU; u += kSelThreads) {
+  for (int u = tid; u < nU; u += kPivThreads) {
     const double cu = c64[u];
-    const int ju = (int)(uint32_t)sh.sel.buf[u];
+    const int ju = sh.cand[u];
     int cnt = 0;
     for (int o = 0; o < nU && cnt < P; ++o) {
       const double co = c64[o];
-      const int jo = (int)(uint32_t)sh.sel.buf[o];
+      const int jo = sh.cand[o];
       cnt += (co < cu || (co == cu && jo < ju)) ? 1 : 0;
     }
     if (cnt < P) {
@@ -131,16 +178,14 @@ __device__ __forceinline__ void select_pivots_body(
   }
 }
 
-// grid: B blocks of THREADS (1024): block b selects the pivots of sample b.
-// PER*THREADS >= the longest sample.
-template <int DT, int THREADS, int PER>
-__global__ __launch_bounds__(THREADS) void k_select_pivots(
+// grid: B blocks of kPivThreads: block b selects the pivots of sample b.
+template <int DT, int PER>
+__global__ __launch_bounds__(kPivThreads) void k_select_pivots(
     Geo g, const void* __restrict__ X, const void* __restrict__ C, int Dc, long ldc,
     const float* __restrict__ l1, int* __restrict__ piv, double* __restrict__ pl2,
     double* __restrict__ scr, float tau) {
-  __shared__ PivotShared<THREADS, PER> sh;
-  select_pivots_body<DT, THREADS, false, PER>(g, blockIdx.x, X, C, Dc, ldc, l1, piv, pl2, scr, tau,
-                                              sh);
+  __shared__ PivotShared<PER> sh;
+  select_pivots_body<DT, false, PER>(g, blockIdx.x, X, C, Dc, ldc, l1, piv, pl2, scr, tau, sh);
 }
 
 }  // namespace dart

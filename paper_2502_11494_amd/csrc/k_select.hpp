@@ -139,28 +139,6 @@ __device__ __forceinline__ BucketSplit bucket_split(const float (&v)[PER], int n
   return bs;
 }
 
-// An upper bound of the want-th lowest of the n values that is itself one of the values: the
-// largest value of the buckets up to d*.  For callers that need a superset of the `want`
-// lowest, not their order (five barriers, no sort).
-template <int THREADS, int PER>
-__device__ __forceinline__ float rank_upper_bound(const float (&v)[PER], int n, int want,
-                                                  int tid, SelectShared<THREADS, PER>& sh) {
-  constexpr int kSelWaves = THREADS / kWave;
-  const int lane = tid & 63, w = tid >> 6;
-  const BucketSplit bs = bucket_split<THREADS, PER>(v, n, want, tid, sh);
-  float top = -INFINITY;  // largest value of the buckets <= d*
-#pragma unroll
-  for (int e = 0; e < PER; ++e)
-    if (e * THREADS < n && tid + e * THREADS < n && bs.bucket(v[e]) <= bs.dstar)
-      top = fmaxf(top, v[e]);
-  top = wave_max(top);
-  if (lane == 0) sh.redg[w] = top;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kSelWaves; ++i) top = fmaxf(top, sh.redg[i]);
-  return top;
-}
-
 // v[e] belongs to index tid + e*THREADS (n <= PER*THREADS); entries with index >= n are ignored.
 // Compacts every entry whose bucket is <= d* and sorts;
 // returns how many were compacted (>= min(want, n)); the same value on every thread.
