@@ -10,8 +10,8 @@
 // n <= PER*THREADS values (1024 threads and PER = 16 for the 16384-token limit).  PER is a
 // template parameter chosen by the host from the longest sample: the loops over a thread's
 // values are unrolled and a slot past the sample's end still issues its instructions with
-// every lane switched off (measured on 2880-token samples: PER = 4 instead of 16 takes 1.9 us
-// off pivot selection and 1.7 us off the ordering kernel).
+// every lane switched off (measured on 2880-token samples: PER = 4 instead of 16 takes 1.7 us
+// off the ordering kernel).
 #pragma once
 #include "common.hpp"
 
@@ -26,7 +26,11 @@ constexpr int kSelCountMin = 128, kSelMaxSeg = 64;
 
 template <int THREADS, int PER = kSelPerThread>
 struct SelectShared {
-  static constexpr int kBuf = pow2_at_least(THREADS * PER);  // (the sorts pad to a power of two)
+  static constexpr int kPad = pow2_at_least(THREADS * PER);  // (the sorts pad to a power of two)
+  // Ordering by counting holds its keys twice.  Samples of at most 4096 tokens have room for all of
+  // them (two workgroups still share a compute unit); with half of it a list of 1050 of 1500 tokens
+  // fell to the sorting network: 14.4 us instead of 7.0 for the lists of sixteen such samples.
+  static constexpr int kBuf = PER <= 4 ? 2 * kPad : kPad;
   unsigned long long buf[kBuf];  // compacted keys, then sorted
   int hist[kSelBuckets];
   float redf[2 * (THREADS / kWave)];
@@ -344,8 +348,8 @@ __device__ __forceinline__ int collect_sorted(const float (&v)[PER], int n, int 
       for (int t = c1 + tid; t < np1; t += kSelThreads) sh.buf[t] = ~0ull;
       for (int t = c2 + tid; t < np2; t += kSelThreads) sh.buf[kSelThreads + t] = ~0ull;
       __syncthreads();
-      block_bitonic_sort<kSelThreads, SelectShared<THREADS, PER>::kBuf / THREADS>(sh.buf, np1, tid);
-      block_bitonic_sort<kSelThreads, SelectShared<THREADS, PER>::kBuf / THREADS>(sh.buf + kSelThreads, np2, tid);
+      block_bitonic_sort<kSelThreads, SelectShared<THREADS, PER>::kPad / THREADS>(sh.buf, np1, tid);
+      block_bitonic_sort<kSelThreads, SelectShared<THREADS, PER>::kPad / THREADS>(sh.buf + kSelThreads, np2, tid);
       *part2 = c1;
       return cstar;
     }
@@ -363,7 +367,7 @@ __device__ __forceinline__ int collect_sorted(const float (&v)[PER], int n, int 
   const int np = next_pow2(c < kWave ? kWave : c);
   for (int t = c + tid; t < np; t += kSelThreads) sh.buf[t] = ~0ull;
   __syncthreads();
-  block_bitonic_sort<kSelThreads, SelectShared<THREADS, PER>::kBuf / THREADS>(sh.buf, np, tid);
+  block_bitonic_sort<kSelThreads, SelectShared<THREADS, PER>::kPad / THREADS>(sh.buf, np, tid);
   if (part2) *part2 = c;
   return c;
 }

@@ -34,7 +34,8 @@ def test_pivots_against_the_oracle(n, P, kind, mode):
 
 
 @pytest.mark.parametrize("N,P,K", [(700, 2, 699), (1024, 3, 1000), (1025, 4, 1000), (1500, 8, 1050),
-                                   (2048, 2, 2047), (2049, 2, 2000)])
+                                   (2048, 2, 2047), (2049, 2, 2000), (3500, 3, 3000), (4096, 2, 4095),
+                                   (4097, 2, 4000)])
 @pytest.mark.parametrize("ties", [False, True])
 def test_long_lists_in_order(N, P, K, ties):
     """Lists of nearly all tokens: the ordering kernel's counting sort at its capacity."""
