@@ -24,13 +24,14 @@ constexpr int kSelBuckets = 1024;
 // sort (measured cross-over), unless one fine histogram bucket holds more than kSelMaxSeg of them (massive ties).
 constexpr int kSelCountMin = 128, kSelMaxSeg = 64;
 
-template <int THREADS, int PER = kSelPerThread>
+// COUNTING: ordering by counting may be asked for (see collect_sorted).
+template <int THREADS, int PER = kSelPerThread, bool COUNTING = true>
 struct SelectShared {
   static constexpr int kPad = pow2_at_least(THREADS * PER);  // (the sorts pad to a power of two)
   // Ordering by counting holds its keys twice.  Samples of at most 4096 tokens have room for all of
   // them (two workgroups still share a compute unit); with half of it a list of 1050 of 1500 tokens
   // fell to the sorting network: 14.4 us instead of 7.0 for the lists of sixteen such samples.
-  static constexpr int kBuf = PER <= 4 ? 2 * kPad : kPad;
+  static constexpr int kBuf = COUNTING && PER <= 4 ? 2 * kPad : kPad;
   unsigned long long buf[kBuf];  // compacted keys, then sorted
   int hist[kSelBuckets];
   float redf[2 * (THREADS / kWave)];
@@ -76,7 +77,7 @@ struct BucketSplit {
 // bucket counts.)
 template <int THREADS, int PER>
 __device__ __forceinline__ BucketSplit bucket_split(const float (&v)[PER], int n, int want,
-                                                    int tid, SelectShared<THREADS, PER>& sh) {
+                                                    int tid, SelectShared<THREADS, PER, false>& sh) {
   constexpr int kSelWaves = THREADS / kWave;
   constexpr int kSelBucketsPerThread = kSelBuckets / THREADS;
   const int lane = tid & 63, w = tid >> 6;

@@ -20,7 +20,7 @@ enum { kAggMin = 1, kAggMax = 2 };
 
 template <int PER>
 struct SingleShared {
-  SelectShared<1024, PER> sel;
+  SelectShared<1024, PER, false> sel;
   uint32_t R[kMaxN / 32];
   int piv[kMaxP];
   int wcnt[16];
