@@ -77,12 +77,15 @@ int compute_units() {
 // divide the batch evenly over the 256 units therefore win: 9 waves (144 rows) for four
 // samples of 9216 tokens (47 us against 55 with 64-row tiles), 12 waves in 4 groups (48 rows)
 // for sixteen of 576 (18 us against 27 for four workgroups per tile and a finishing pass).
-// The candidates are the shapes instantiated below.
+// The candidates are the shapes instantiated below; (8, 8), 16-row tiles with a chain of an eighth of
+// the chunks, is for batches of so few rows that nothing but the chain counts (whole step against
+// the 32-row tiles of (8, 4): one frame of 256 tokens 32.8 and 35.3 us, four 576-token images 37.8
+// and 40.3, one sample of 2880 tokens 47.2 and 49.0).
 struct KsChoice { int waves, split; };
 #define DART_KS_SHAPES(X_)                                                                   \
   X_(3, 1) X_(4, 1) X_(5, 1) X_(6, 1) X_(8, 1) X_(9, 1) X_(10, 1) X_(11, 1) X_(12, 1)        \
   X_(4, 2) X_(6, 2) X_(8, 2) X_(12, 2) X_(6, 3) X_(9, 3) X_(12, 3)                          \
-  X_(8, 4) X_(12, 4) X_(16, 4)
+  X_(8, 4) X_(12, 4) X_(16, 4) X_(8, 8)
 constexpr KsChoice kKsShapes[] = {
 #define DART_KS_ENTRY(W, KS) {W, KS},
     DART_KS_SHAPES(DART_KS_ENTRY)
