@@ -53,8 +53,11 @@ struct RetainShared {
   int st_off[kMaxP];  // offset of the stage's list inside the sample's list region
   int st_len[kMaxP];
   // per stage: a list position at or before the last entry taken (where the walk began, every entry
-  // before being taken by earlier stages); then the last key taken and the first refused
+  // before being taken by earlier stages; written by the walk alone); the position up to which the
+  // helpers have found the list's entries taken (theirs alone, the walk reads it before its stage);
+  // then the last key taken and the first refused
   int st_start[kMaxP];
+  int st_ahead[kMaxP];
   unsigned long long st_kab[kMaxP][2];
   int st_qlo[kMaxP], st_qhi[kMaxP];
   unsigned char st_unc[kMaxP];
@@ -205,7 +208,7 @@ __device__ __forceinline__ void retain_body(
       sh.fb_first = group_hi;
       sh.walked = next;
     }
-    if (tid >= next && tid < group_hi) sh.st_start[tid] = 0;
+    if (tid >= next && tid < group_hi) sh.st_start[tid] = sh.st_ahead[tid] = 0;
     __syncthreads();
     const int walk_end = group_hi;
     // The global pointer carries its address space: with a generic one the compiler may fold
@@ -228,9 +231,12 @@ __device__ __forceinline__ void retain_body(
     // token's owner) and one byte written back; the next stage's indices are read ahead.  What
     // would make it long are the entries at the head of a list that earlier stages took
     // (near-duplicate pivots have nearly the same list, so stage i begins with most of what the i
-    // stages before it took): the other waves keep moving st_start of the later stages past such
+    // stages before it took): the other waves keep moving st_ahead of the later stages past such
     // entries.  An entry once taken stays taken during the walk, so a position read late is only
-    // less far ahead.
+    // less far ahead.  The walk reads a stage's position before it marks anything for that stage, so
+    // what it reads passes over earlier stages' entries only.  A helper may store as late as it
+    // likes: it may by then have passed over the stage's own entries, but nobody reads st_ahead of
+    // a stage again, and st_start, which the boundary search below starts from, is not the helpers'.
     const auto lds_load = [](const int* p) {
       return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
@@ -320,7 +326,7 @@ __device__ __forceinline__ void retain_body(
           const int off_n = __builtin_amdgcn_readlane(off_v, in) - group_base;
           const int pos_n = __builtin_amdgcn_readfirstlane(ahead);
           read_ahead(pos_n, off_n);
-          ahead = lds_load(&sh.st_start[i + 2 < walk_end ? i + 2 : in]);
+          ahead = lds_load(&sh.st_ahead[i + 2 < walk_end ? i + 2 : in]);
           start_v = lane == i ? pos : start_v;
           int taken = 0;  // candidates met so far
 #pragma unroll
@@ -351,7 +357,7 @@ __device__ __forceinline__ void retain_body(
           take_over(pos, off + len <= staged_total ? len : 0);
         }
       };
-      // runs that usually fill the quota: about a third of the entries past st_start are taken
+      // runs that usually fill the quota: about a third of the entries past st_ahead are taken
       if (sp.q < 40) walk(std::integral_constant<int, 2>{});
       else walk(std::integral_constant<int, 4>{});
       if (lane >= next && lane < walk_end) sh.st_start[lane] = start_v;
@@ -375,14 +381,14 @@ __device__ __forceinline__ void retain_body(
           const int off = __builtin_amdgcn_readlane(off_v, i) - group_base;
           // (the next two stages' positions have been read already)
           if (i <= walked + 1 || off + len > staged_total) continue;
-          const int at = __builtin_amdgcn_readfirstlane(lds_load(&sh.st_start[i]));
+          const int at = __builtin_amdgcn_readfirstlane(lds_load(&sh.st_ahead[i]));
           const int p = at + lane;
           const int j = p < len ? (int)sh.lidx[off + p] : 0;
           const unsigned char own = *(volatile unsigned char*)&sh.owner[j];
           const unsigned long long free_m = __ballot(p >= len || own == kOwnNone);
           const int step = free_m ? __builtin_ctzll(free_m) : kWave;
           if (step > 0) {
-            if (lane == 0) lds_store(&sh.st_start[i], at + step);
+            if (lane == 0) lds_store(&sh.st_ahead[i], at + step);
             moved = true;
           }
         }
