@@ -74,6 +74,11 @@ struct RetainShared {
   unsigned char q_taken[kRetQ];
 };
 
+// A score that is not a number (a row or a pivot with an infinite or undefined element) counts as
+// above every number.  With the pairs in a total order exactly `need` of a set have fewer than
+// `need` before them, whatever the input holds: the retained set never outgrows its budget.
+__device__ __forceinline__ double ordered_score(double s) { return s == s ? s : INFINITY; }
+
 // (score, index) pairs compare lexicographically
 __device__ __forceinline__ bool pair_less(double sa, int ja, double sb, int jb) {
   return sa < sb || (sa == sb && ja < jb);
@@ -543,7 +548,7 @@ __device__ __forceinline__ void retain_body(
       const double s0 =
           pl2 ? row_cosine_f64<DT, true, kRetInFlight>(prow, xrow, g.D, lane, sh.pl2[st])
               : row_cosine_f64<DT, false, kRetInFlight>(prow, xrow, g.D, lane);
-      if (lane == 0) sh.q_s64[q] = s0;
+      if (lane == 0) sh.q_s64[q] = ordered_score(s0);
     }
     __syncthreads();
 
@@ -657,7 +662,7 @@ __device__ __forceinline__ void retain_body(
         const unsigned char* xrow = Xb + (long)sweep_idx[u] * rowbytes;
         const double s64 = pl2 ? row_cosine_f64<DT, true, kRetInFlight>(prow, xrow, g.D, lane, pp_i)
                                : row_cosine_f64<DT, false, kRetInFlight>(prow, xrow, g.D, lane);
-        if (lane == 0) sweep_s64[u] = s64;
+        if (lane == 0) sweep_s64[u] = ordered_score(s64);
       }
       __syncthreads();
       for (int u = tid; u < nU; u += kRetThreads) {
@@ -693,9 +698,9 @@ __device__ __forceinline__ void retain_body(
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kRetWaves; ++w) off += w < wave ? sh.wcnt[w] : 0;
-  int* out = keep + sm.keep0 + off;
-  while (kept) {
-    st_dev<COH>(out++, j0 + __ffs(kept) - 1);
+  int* out = keep + sm.keep0;
+  for (; kept && off < k; ++off) {  // (never more than the budget: the next sample's rows follow)
+    st_dev<COH>(out + off, j0 + __ffs(kept) - 1);
     kept &= kept - 1;
   }
 }
