@@ -8,13 +8,14 @@
 // every pivot, which the score kernel divides by.
 #pragma once
 #include "common.hpp"
+#include "pivot_rank.hpp"
 
 namespace dart {
 
 constexpr int kPivLdsCand = 512;  // candidates whose fp64 norms fit in LDS
 
-// 1024 threads; PER values per thread, PER*1024 >= the longest sample.
-constexpr int kPivThreads = 1024, kPivWaves = kPivThreads / kWave, kPivGroups = kPivThreads / 4;
+// PER values per thread, PER*1024 >= the longest sample.
+constexpr int kPivWaves = kPivThreads / kWave;
 
 template <int PER>
 struct PivotShared {
@@ -26,10 +27,8 @@ struct PivotShared {
   float thr;
 };
 
-// An upper bound of the want-th lowest (1 <= want <= 64) of 256 values (the images of mono_of),
-// close enough to add few values to the want lowest: bisection of their range until at most one more
-// is below the bound, or a thousandth of the range is left (six to eight steps as a rule).  By one wave, lane l holding four values; every step is four
-// compares and their ballots.
+// rank_bound over 256 values by one wave, lane l holding four: a step is four compares and their
+// ballots.
 __device__ __forceinline__ uint32_t rank_bound_of_256(const u32x4& v, int want) {
   const uint32_t none = mono_of(INFINITY);  // groups without a token: not part of the range
   uint32_t lo = none, hi = 0u;
@@ -48,18 +47,13 @@ __device__ __forceinline__ uint32_t rank_bound_of_256(const u32x4& v, int want) 
   DART_MINMAX_STEP(1) DART_MINMAX_STEP(2) DART_MINMAX_STEP(4) DART_MINMAX_STEP(8)
   DART_MINMAX_STEP(16) DART_MINMAX_STEP(32)
 #undef DART_MINMAX_STEP
-  uint32_t l = __builtin_amdgcn_readfirstlane(lo), h = __builtin_amdgcn_readfirstlane(hi);
-  h = h > l ? h : l;
-  for (int step = 0; step < 10 && l < h; ++step) {  // the bound is in [l, h]
-    const uint32_t mid = l + ((h - l) >> 1);
-    const int cnt = __popcll(__builtin_amdgcn_ballot_w64(v.x <= mid)) +
-                    __popcll(__builtin_amdgcn_ballot_w64(v.y <= mid)) +
-                    __popcll(__builtin_amdgcn_ballot_w64(v.z <= mid)) +
-                    __popcll(__builtin_amdgcn_ballot_w64(v.w <= mid));
-    if (cnt >= want) h = mid; else l = mid + 1;
-    if (cnt == want || cnt == want + 1) break;  // close enough (h = mid)
-  }
-  return h;
+  const uint32_t l = __builtin_amdgcn_readfirstlane(lo), h = __builtin_amdgcn_readfirstlane(hi);
+  return rank_bound(l, h, none, want, [&](uint32_t m) {
+    return __popcll(__builtin_amdgcn_ballot_w64(v.x <= m)) +
+           __popcll(__builtin_amdgcn_ballot_w64(v.y <= m)) +
+           __popcll(__builtin_amdgcn_ballot_w64(v.z <= m)) +
+           __popcll(__builtin_amdgcn_ballot_w64(v.w <= m));
+  });
 }
 
 // Pivot selection of sample b by one workgroup of kPivThreads threads.
@@ -79,26 +73,24 @@ __device__ __forceinline__ void select_pivots_body(
   const int n = sm.n, P = g.Pin;  // pivots chosen among the tokens; stride of piv is g.P
   const float sign = g.mode == kMaxL1 ? -1.f : 1.f;  // "lowest" of -norm = largest norm
 
-  // Candidates: every token that may belong to the exact top P.  The tokens form 256 groups (four
-  // threads each, dealt so that a sample of at most 256 tokens has one per group); the P-th lowest
-  // of the groups' lowest values is reached by P tokens, so with vsel at least that,
-  // {v <= vsel + 2.5 tau |vsel|} holds every token within the norm pass's error of the P-th best:
-  // usually P and a handful more.  They are ranked in fp64 below, so neither their order nor the
-  // exact P-th value is needed here.  (Two barriers; the histogram over the block's value range that
-  // this replaces had six.)
-  const int tok0 = (tid >> 2) + kPivGroups * (tid & 3);
+  // Candidates: every token that may belong to the exact top P.  The tokens form 256 groups of four
+  // threads each (pivot_token); the P-th lowest of the groups' lowest values is reached by P tokens,
+  // so with vsel at least that, {v <= vsel + 2.5 tau |vsel|} holds every token within the norm
+  // pass's error of the P-th best: usually P and a handful more.  They are ranked in fp64 below, so
+  // neither their order nor the exact P-th value is needed here.  (Two barriers; the histogram over
+  // the block's value range that this replaces had six.)
   // (all loads before the first use, from clamped places: a load whose value is used under its
   // condition is waited for before the next one is issued, 0.3 us each)
   float v[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    const int j = tok0 + e * kPivThreads;
+    const int j = pivot_token(tid, e);
     v[e] = ld_dev<COH>(&l1[sm.row0 + (j < n ? j : n - 1)]);
   }
   float low = INFINITY;
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    v[e] = tok0 + e * kPivThreads < n ? sign * v[e] + 0.0f : INFINITY;
+    v[e] = pivot_token(tid, e) < n ? sign * v[e] + 0.0f : INFINITY;
     low = fminf(low, v[e]);
   }
   low = fminf(low, lane_xor<1>(low, lane));
@@ -109,7 +101,7 @@ __device__ __forceinline__ void select_pivots_body(
   if (w == 0) {  // (alone it takes half as long as with all waves beside it)
     const u32x4 g4 = reinterpret_cast<const u32x4*>(sh.group)[lane];
     const float vsel = mono_inv(rank_bound_of_256(g4, P));
-    if (lane == 0) sh.thr = vsel + 2.5f * tau * fabsf(vsel);
+    if (lane == 0) sh.thr = candidate_limit(vsel, tau);
   }
   __syncthreads();
   const float thr = sh.thr;
@@ -118,7 +110,7 @@ __device__ __forceinline__ void select_pivots_body(
   for (int e = 0; e < PER; ++e) hit |= v[e] <= thr ? 1u << e : 0u;
   while (__builtin_amdgcn_ballot_w64(hit != 0u) != 0ull) {
     if (hit != 0u) {
-      const int j = tok0 + (__ffs(hit) - 1) * kPivThreads;
+      const int j = pivot_token(tid, __ffs(hit) - 1);
       hit &= hit - 1u;
       if (j < n) sh.cand[atomicAdd(&sh.nU, 1)] = j;
     }

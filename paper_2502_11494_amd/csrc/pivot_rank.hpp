@@ -1,0 +1,48 @@
+// How pivot selection finds a bound of the P-th best norm: the plain integer part of it, which
+// compiles for the host too, so that the number of candidates it leaves can be checked without a GPU.
+#pragma once
+#include <stdint.h>
+
+#ifdef __HIPCC__
+#define DART_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define DART_HOST_DEVICE inline
+#endif
+
+namespace dart {
+
+// 1024 threads; four of them share a group of tokens.
+constexpr int kPivThreads = 1024, kPivGroups = kPivThreads / 4;
+
+// Token that thread tid holds in slot e: a group is every 256th token, one per group up to 256 tokens.
+DART_HOST_DEVICE int pivot_token(int tid, int e) {
+  return (4 * e + (tid & 3)) * kPivGroups + (tid >> 2);
+}
+
+// A bound of the want-th lowest of a set of values (order-preserving images of floats), at least
+// that value: bisection between the lowest value and the highest, lo and hi, where count(m) says how
+// many values are at most m.  It ends when at most one value too many is below the bound (six to ten
+// steps as a rule) or at a range of kRankClose images, about the margin that the caller adds to
+// the bound anyway, however far apart lo and hi are: an image is a floating-point number, and one zero
+// among norms of thousands makes it 18 steps. 
+constexpr uint32_t kRankClose = 32;
+template <typename Count>
+DART_HOST_DEVICE uint32_t rank_bound(uint32_t lo, uint32_t hi, uint32_t none, int want,
+                                     const Count& count) {
+  uint32_t l = lo, h = hi > lo ? hi : lo;  // (lo = none, hi = 0: no value is a number)
+  while (l < h && h - l >= kRankClose) {  // the bound is in [l, h]
+    const uint32_t mid = l + ((h - l) >> 1);
+    const int c = count(mid);
+    if (c >= want) h = mid; else l = mid + 1;
+    if (c == want || c == want + 1) break;  // close enough (h = mid)
+  }
+  return h;
+}
+
+// Values up to this belong to the candidates: the bound and the norm pass's error tau on either
+// side of it.
+DART_HOST_DEVICE float candidate_limit(float bound, float tau) {
+  return bound + 2.5f * tau * (bound < 0.f ? -bound : bound);
+}
+
+}  // namespace dart
