@@ -40,13 +40,18 @@ def norms(kind, n, rng):
         x *= np.where(rng.random(n) < 0.02, 1.5 + 2.5 * rng.random(n), 1)
     elif kind == "tiny":
         x *= 1e-30
+    elif kind.startswith("frames"):         # the norm follows the place inside the frame
+        per = int(kind.split()[1])
+        place = 3268 + 30 * rng.standard_normal(per)
+        x = np.tile(place, -(-n // per))[:n] + rng.standard_normal(n)
     return x
 
 
 SIZES = [(5, 5), (256, 8), (576, 8), (1500, 64), (2880, 16), (9216, 32), (16384, 16)]
 
 
-@pytest.mark.parametrize("kind", ["plain", "a zero row", "zero padding", "a huge row", "heavy", "tiny"])
+@pytest.mark.parametrize("kind", ["plain", "a zero row", "zero padding", "a huge row", "heavy", "tiny"]
+                         + [f"frames {p}" for p in (16, 64, 144, 219, 256, 510, 576, 1024)])
 def test_candidates_are_the_best_and_few(search, kind):
     for n, P in SIZES:
         x = norms(kind, n, np.random.default_rng(n + P))
