@@ -32,25 +32,27 @@ DART_HOST_DEVICE int pivot_token(int tid, int e) {
 // many values are at most m.  It ends when at most one value too many is below the bound (six to ten
 // steps as a rule) or at a range of kRankClose images, about the margin that the caller adds to
 // the bound anyway, however far apart lo and hi are: an image is a floating-point number, and one zero
-// among norms of thousands makes it 18 steps. 
+// among norms of thousands makes it 18 steps.  none if hi itself does not reach want values.
 constexpr uint32_t kRankClose = 32;
 template <typename Count>
 DART_HOST_DEVICE uint32_t rank_bound(uint32_t lo, uint32_t hi, uint32_t none, int want,
                                      const Count& count) {
-  uint32_t l = lo, h = hi > lo ? hi : lo;  // (lo = none, hi = 0: no value is a number)
+  uint32_t l = lo, h = hi;
   while (l < h && h - l >= kRankClose) {  // the bound is in [l, h]
     const uint32_t mid = l + ((h - l) >> 1);
     const int c = count(mid);
     if (c >= want) h = mid; else l = mid + 1;
     if (c == want || c == want + 1) break;  // close enough (h = mid)
   }
-  return h;
+  return h == hi && count(h) < want ? none : h;
 }
 
 // Values up to this belong to the candidates: the bound and the norm pass's error tau on either
-// side of it.
+// side of it.  Everything if the bound is not a finite number (norms beyond the range of fp32, or
+// fewer groups than pivots hold a number): the fp64 ranking decides.
 DART_HOST_DEVICE float candidate_limit(float bound, float tau) {
-  return bound + 2.5f * tau * (bound < 0.f ? -bound : bound);
+  const float mag = bound < 0.f ? -bound : bound;
+  return mag < __builtin_inff() ? bound + 2.5f * tau * mag : __builtin_inff();
 }
 
 }  // namespace dart

@@ -1,5 +1,6 @@
 """Pivot selection at the edges of its candidate search: samples smaller and larger than the number of
-groups, as many pivots as tokens, equal norms, a few norms far above the others, both orders."""
+groups, as many pivots as tokens, equal norms, a few norms far above the others, norms that overflow
+fp32, both orders."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,P", [(1, 1), (3, 3), (64, 64), (65, 64), (255, 16), (256, 64), (257, 1),
                                  (1023, 8), (1024, 64), (1025, 33), (4096, 16), (9217, 32),
                                  (16384, 64)])
-@pytest.mark.parametrize("kind", ["spread", "equal", "heavy", "zero"])
+@pytest.mark.parametrize("kind", ["spread", "equal", "heavy", "zero", "overflow"])
 @pytest.mark.parametrize("mode", [D.DART_PIVOT_MAX_L1, D.DART_PIVOT_MIN_L1])
 def test_pivots_against_the_oracle(n, P, kind, mode):
     rng = np.random.default_rng(n + P)
@@ -24,6 +25,9 @@ def test_pivots_against_the_oracle(n, P, kind, mode):
         X *= np.where(rng.random((n, 1)) < 0.05, 1e6, 1.0) * np.where(rng.random((n, 1)) < 0.05, 1e-6, 1.0)
     elif kind == "zero":
         X[rng.random(n) < 0.9] = 0.0
+    elif kind == "overflow":  # norms beyond fp32's range: ranked in fp64 alone
+        X *= np.where(rng.random((n, 1)) < 0.5, 3e37, 1.0)
+        X = np.clip(X, -1e38, 1e38) * np.where(X > 0, 1.0, 3.0)
     X = X.astype(np.float32)
     desc = D.make_desc(1, 8, P, D.DART_F32, N=n, K=n, pivot_mode=mode)
     piv = torch.full((P,), -1, dtype=torch.int32, device="cuda")

@@ -63,6 +63,17 @@ def test_candidates_are_the_best_and_few(search, kind):
             assert cand.sum() <= max(2 * P + 8, must.sum()), (n, P)
 
 
+@pytest.mark.parametrize("beyond", [1, 7, 100, 100000])  # norms that overflow fp32
+def test_norms_beyond_fp32_are_candidates(search, beyond):
+    for n, P in SIZES:
+        rng = np.random.default_rng(n + beyond)
+        x = 3268 + 30 * rng.standard_normal(n)
+        x[rng.permutation(n)[:beyond]] = np.inf
+        for v in (-x, x):
+            cand = search(v, P)
+            assert cand.sum() >= P and np.all(cand[v <= np.sort(v)[P - 1]]), (n, P)
+
+
 def test_undefined_norms_are_passed_over(search):
     v = -(3268 + 30 * np.random.default_rng(1).standard_normal(2880))
     v[::3] = np.nan
