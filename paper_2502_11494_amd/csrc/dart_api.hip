@@ -1006,9 +1006,15 @@ dart_status dart_compact_sequences(const dart_desc* desc, const int32_t* seq_cu,
   if (p.g.B == 0 || rows_bound <= 0) return DART_OK;
   SeqPos sp = {reinterpret_cast<const long long*>(pos), reinterpret_cast<long long*>(pos_out),
                (long)pos_plane_stride, (long)pos_out_plane_stride, pos_planes};
-  for (int i0 = 0; i0 == 0 || i0 < n_tensors; i0 += kSeqOps) {
+  if (n_tensors == 0) {
+    DART_LAUNCH(k_seq_row_map, dim3((unsigned)((rows_bound + 255) / 256)), dim3(256), 0, st, p.g,
+                seq_cu, seq_cu_out, keep, row_map, sp);
+    DART_LAUNCH_CHECK();
+  }
+  for (int i0 = 0; i0 < n_tensors; i0 += kSeqOps) {
     SeqOps ops = {};
     const int cnt = std::min(n_tensors - i0, kSeqOps);
+    long longest = 0;
     for (int i = 0; i < cnt; ++i) {
       const dart_row_tensor& t = tensors[i0 + i];
       ops.src[i] = static_cast<const unsigned char*>(t.src);
@@ -1016,9 +1022,18 @@ dart_status dart_compact_sequences(const dart_desc* desc, const int32_t* seq_cu,
       ops.row_bytes[i] = t.row_bytes;
       ops.src_ld[i] = t.src_ld_bytes;
       ops.dst_ld[i] = t.dst_ld_bytes;
+      longest = std::max(longest, (long)t.row_bytes);
     }
-    DART_LAUNCH(k_gather_rows, dim3((unsigned)round_up8((rows_bound + 3) / 4), std::max(cnt, 1)),
-                dim3(256), 0, st, p.g, ops, cnt, i0 == 0, seq_cu, seq_cu_out, keep, row_map, sp);
+    // rows per wave (measured: see the kernel)
+    const int R = longest <= 1024 ? 4 : longest <= 2048 ? 2 : 1;
+    const dim3 grid((unsigned)round_up8((rows_bound + 4 * R - 1) / (4 * R)), cnt);
+#define DART_LAUNCH_SEQ(ROWS)                                                                    \
+  DART_LAUNCH(k_gather_rows<ROWS>, grid, dim3(256), 0, st, p.g, ops, i0 == 0, seq_cu, seq_cu_out, \
+              keep, row_map, sp)
+    if (R == 4) DART_LAUNCH_SEQ(4);
+    else if (R == 2) DART_LAUNCH_SEQ(2);
+    else DART_LAUNCH_SEQ(1);
+#undef DART_LAUNCH_SEQ
     DART_LAUNCH_CHECK();
   }
   return DART_OK;

@@ -320,58 +320,141 @@ struct SeqPos {  // position ids, plane-major
 };
 
 // Row r of the shortened batch comes from row src(r) of the original tensors: the rows of its
-// sequence before the span, then span + keep, then the rows behind the span.  Every wave works out
-// its row's source by itself (one load of the offsets per 64 samples and a ballot instead of a
-// chain of loads per halving), so that the map, the position ids and the tensors need one launch:
-// five launches of which three moved a few KB took 38 us on eight sequences of 1900 rows, two take
-// 28.  dst row r = src row src(r) for every tensor of ops; the waves of tensor 0 also write row_map
-// and the position planes (first: the first launch of the call).
-// One wave per (row, tensor): grid (ceil(rows_bound / 4) rounded up to a multiple of 8, tensors or
-// 1) blocks of 256 (with a multiple of 8 in x the die of a block depends on its x only:
-// xcd_contiguous); 16 bytes per lane, 1 KiB per access.  Rows beyond seq_cu_out[B] are left alone.
-__global__ __launch_bounds__(256) void k_gather_rows(Geo g, SeqOps ops, int n_ops, bool first,
+// sequence before the span, then span + keep, then the rows behind the span.
+struct SeqRow {  // the sample of a row: the last one whose new offset is at most r
+  int off, end;  // its rows are [off, end) of the shortened batch
+  int s0, span, n, k0, k;
+  __device__ __forceinline__ void load(const Geo& g, const int* seq_cu, const int* seq_cu_out, int b) {
+    off = seq_cu_out[b];
+    end = seq_cu_out[b + 1];
+    s0 = seq_cu[b];
+    span = g.span[b];
+    n = g.cu[b + 1] - g.cu[b];
+    k0 = g.cu_keep[b];
+    k = g.cu_keep[b + 1] - k0;
+  }
+  __device__ __forceinline__ long source(int r, const int* keep) const {
+    const int t = r - off, before = span - s0;  // text rows ahead of the span
+    if (t < before) return s0 + t;
+    if (t >= before + k) return span + n + (t - before - k);
+    int kr = keep[k0 + (t - before)];
+    kr = kr < 0 ? 0 : (kr < n ? kr : n - 1);  // a caller's bad index must not leave the span
+    return span + kr;
+  }
+};
+
+// No tensors to move: the map and the position planes, a row per thread.  grid: ceil(rows_bound / 256)
+// blocks of 256.  (590 000 rows of 16384 sequences, the offsets' launch included: 62 us; 85 at best
+// with the rows dealt as in k_gather_rows.)
+__global__ __launch_bounds__(256) void k_seq_row_map(Geo g, const int* __restrict__ seq_cu,
+                                                     const int* __restrict__ seq_cu_out,
+                                                     const int* __restrict__ keep,
+                                                     int* __restrict__ row_map, SeqPos sp) {
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  if (r >= seq_cu_out[g.B]) return;
+  int lo = 0, hi = g.B;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (seq_cu_out[mid] <= r) lo = mid; else hi = mid;
+  }
+  SeqRow q;
+  q.load(g, seq_cu, seq_cu_out, lo);
+  const long src = q.source(r, keep);
+  row_map[r] = (int)src;
+  for (int p = 0; p < sp.planes; ++p)
+    sp.pos_out[p * sp.out_stride + r] = sp.pos[p * sp.in_stride + src];
+}
+
+// dst row r = src row src(r) for every tensor of ops.  Every wave works out its rows' sources by
+// itself, so that the map, the position ids and the tensors need one launch (five launches of which
+// three moved a few KB took 38 us on eight sequences of 1900 rows, two take 28); the waves of
+// tensor 0 also write row_map and the position planes (first: the first launch of the call).
+// A row's sample is found by 64 offsets in the lanes and a ballot; of more samples every look leaves
+// a 64th (one after the other, 64 at a time, 4096 sequences of 20 tokens and nine tensors of 512
+// bytes took 2875 us; 281 now, 351 with a launch for the map before it).
+// A wave per R rows of a tensor: grid (ceil(rows_bound / (4 R)) rounded up to a multiple of 8, tensors)
+// blocks of 256 (with a multiple of 8 in x the die of a block depends on its x only: xcd_contiguous);
+// 16 bytes per lane, 1 KiB per access.  R > 1 (rows of at most 2 KiB): what a wave has to find out
+// takes longer than a short row takes to move, and several rows are in flight together.  R rows
+// per wave: 1, 2, 4, 8, 16, by 64 sequences of 937 tokens and nine tensors of 512 bytes: 58, 41, 36,
+// 39, 44 us; rows of 1 KiB, 4096 sequences of 20 tokens: 97, 69, 64, 67, 71; of 2 KiB: 131, 126, 124,
+// 127, 125, but eight tensors of 2 KiB in 64 sequences 74, 75, 76, 84, 88; of 8 KiB, five tensors: 236,
+// -, 255, 269, -.  Rows beyond seq_cu_out[B] are left alone.
+template <int R>
+__global__ __launch_bounds__(256) void k_gather_rows(Geo g, SeqOps ops, bool first,
                                                      const int* __restrict__ seq_cu,
                                                      const int* __restrict__ seq_cu_out,
                                                      const int* __restrict__ keep,
                                                      int* __restrict__ row_map, SeqPos sp) {
   const int lane = threadIdx.x & 63, o = blockIdx.y;
-  const long r = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
-  if (r >= seq_cu_out[g.B]) return;
-  int b = 0;  // the last sample whose offset is at most r
-  for (int b0 = 0; b0 < g.B; b0 += kWave) {
-    const unsigned long long m = __ballot(b0 + lane < g.B && seq_cu_out[b0 + lane] <= r);
-    if (m == 0ull) break;
-    b = b0 + 63 - __builtin_clzll(m);
-    if (m != ~0ull) break;
-  }
-  const int s0 = seq_cu[b], span = g.span[b], n = g.cu[b + 1] - g.cu[b], k0 = g.cu_keep[b];
-  const int k = g.cu_keep[b + 1] - k0;
-  const int t = (int)(r - seq_cu_out[b]), before = span - s0;  // text rows ahead of the span
-  long src;
-  if (t < before) {
-    src = s0 + t;
-  } else if (t < before + k) {
-    int kr = keep[k0 + (t - before)];
-    kr = kr < 0 ? 0 : (kr < n ? kr : n - 1);  // a caller's bad index must not leave the span
-    src = span + kr;
-  } else {
-    src = span + n + (t - before - k);
+  const int r0 = __builtin_amdgcn_readfirstlane(
+      (int)(xcd_contiguous(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6)) * R);
+  const int rows = seq_cu_out[g.B];
+  if (r0 >= rows) return;
+  SeqRow q;
+  q.end = 0;
+  auto find = [&](int r) {
+    int from = 0, left = g.B;
+    auto last_at_most = [&](int stride) {
+      const int d = lane * stride;
+      return 63 - __builtin_clzll(__ballot(d < left && seq_cu_out[from + (d < left ? d : 0)] <= r));
+    };
+    while (left > kWave) {
+      const int stride = (left + kWave - 1) / kWave, skip = last_at_most(stride) * stride;
+      from += skip;
+      left = left - skip < stride ? left - skip : stride;
+    }
+    q.load(g, seq_cu, seq_cu_out, __builtin_amdgcn_readfirstlane(from + last_at_most(1)));
+  };
+  long src[R];
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    src[u] = 0;
+    if (r0 + u >= rows) continue;
+    if (r0 + u >= q.end) find(r0 + u);
+    src[u] = q.source(r0 + u, keep);
   }
   if (o == 0 && first) {
-    if (lane == 0) row_map[r] = (int)src;
-    for (int p = lane; p < sp.planes; p += kWave)
-      sp.pos_out[p * sp.out_stride + r] = sp.pos[p * sp.in_stride + src];
+    const int u = lane % R;
+    long mine = src[0];
+#pragma unroll
+    for (int v = 1; v < R; ++v) mine = u == v ? src[v] : mine;
+    if (r0 + u < rows) {
+      if (lane < R) row_map[r0 + u] = (int)mine;
+      for (int p = lane / R; p < sp.planes; p += kWave / R)
+        sp.pos_out[p * sp.out_stride + r0 + u] = sp.pos[p * sp.in_stride + mine];
+    }
   }
-  if (o >= n_ops) return;  // no tensors: the map and the position ids only
-  const u32x4* in = reinterpret_cast<const u32x4*>(ops.src[o] + src * ops.src_ld[o]);
-  u32x4* out = reinterpret_cast<u32x4*>(ops.dst[o] + r * ops.dst_ld[o]);
+  const u32x4 zero = {0u, 0u, 0u, 0u};
   const int pieces = (int)(ops.row_bytes[o] / 16);
+  auto row_in = [&](int u) { return reinterpret_cast<const u32x4*>(ops.src[o] + src[u] * ops.src_ld[o]); };
+  auto row_out = [&](int u) { return reinterpret_cast<u32x4*>(ops.dst[o] + (long)(r0 + u) * ops.dst_ld[o]); };
+  if (R > 1) {  // (pieces <= 2 * kWave: see the launch) all rows in flight
+    u32x4 v[R][2];
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int t = h * kWave + lane;
+        v[u][h] = r0 + u < rows && t < pieces ? __builtin_nontemporal_load(row_in(u) + t) : zero;
+      }
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int t = h * kWave + lane;
+        if (r0 + u < rows && t < pieces) row_out(u)[t] = v[u][h];
+      }
+    return;
+  }
+  const u32x4* in = row_in(0);
+  u32x4* out = row_out(0);
   for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
     u32x4 v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int t = t0 + u * kWave + lane;
-      v[u] = t < pieces ? __builtin_nontemporal_load(in + t) : u32x4{0u, 0u, 0u, 0u};
+      v[u] = t < pieces ? __builtin_nontemporal_load(in + t) : zero;
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
