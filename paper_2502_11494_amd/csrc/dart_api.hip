@@ -381,6 +381,12 @@ thread_local StageEvents t_stage;
     }                                                                                           \
   } while (0)
 
+#define DART_TRY(expr)                    \
+  do {                                    \
+    dart_status _s = (expr);              \
+    if (_s != DART_OK) return _s;         \
+  } while (0)
+
 // Points g at the ragged offsets in the workspace (no-op for dense batches); the caller launches
 // what fills them.
 PrepareArgs prepare_args(Plan& p, void* ws) {
@@ -411,15 +417,21 @@ dart_status launch_prepare(Plan& p, void* ws, hipStream_t st, const int* seq_cu 
 }
 
 // keep_cached: the rows will be read again soon (they are the hidden states themselves).
-// Ragged batches: also fills the ragged offsets (a block of the same launch).
+// Ragged batches: also fills the ragged offsets, by a block of the same launch for up to
+// kPrepareInPass samples: as a launch of its own that takes 4-5 us first, however few they are, but a
+// block of the pass is 256 threads and takes about 0.5 us per 256 samples, which with many short
+// samples is longer than the rest of the pass (samples of at most 8 tokens of 64: 2048 samples 20.2 us
+// for norms and selection against 22.9 with the launch, 8192 60.6 and 61.9, 65536 485 and 420).
+constexpr int kPrepareInPass = 2048;
 dart_status launch_row_l1(Plan& p, const void* C, int Dc, long ldc, float* l1, bool keep_cached,
                           void* ws, hipStream_t st, double* l2sq = nullptr) {
   constexpr int ROWS = 1;  // one row per wave measured best (more, shorter-lived waves)
   const int rows = p.g.total_N;
   if (rows == 0) return launch_prepare(p, ws, st);
+  const bool fill = p.g.cu != nullptr && p.g.B <= kPrepareInPass;
+  if (!fill) DART_TRY(launch_prepare(p, ws, st));
   const PrepareArgs prep = prepare_args(p, ws);
-  const bool ragged = p.g.cu != nullptr;
-  const int blocks = (int)round_up8((rows + 4 * ROWS - 1) / (4 * ROWS)) + (ragged ? kXcds : 0);
+  const int blocks = (int)round_up8((rows + 4 * ROWS - 1) / (4 * ROWS)) + (fill ? kXcds : 0);
   // The 256 MB memory-side cache serves the score kernel's second pass if this pass leaves
   // the rows there: measured 31 instead of 38 us on that kernel for 0.7 us more on this one
   // at 189 MB; at 264 MB this pass loses 7 us and that one gains 0.7; a loss for matrices
@@ -429,7 +441,7 @@ dart_status launch_row_l1(Plan& p, const void* C, int Dc, long ldc, float* l1, b
   const bool keep = keep_cached && (double)rows * ldc * p.esz <= 224e6;
 #define DART_LAUNCH_L1_AS(DT, KEEP, SPAN, L2SQ)                                                  \
   do {                                                                                           \
-    if (ragged)                                                                                  \
+    if (fill)                                                                                    \
       DART_LAUNCH((k_row_l1<DT, ROWS, KEEP, SPAN, L2SQ, true>), dim3(blocks), dim3(256), 0, st,  \
                   C, Dc, ldc, rows, l1, p.g, l2sq, prep);                                        \
     else                                                                                         \
@@ -746,12 +758,6 @@ bool fused_enabled() {
   const char* v = std::getenv("DART_FUSED");
   return v && v[0] == '1';
 }
-
-#define DART_TRY(expr)                    \
-  do {                                    \
-    dart_status _s = (expr);              \
-    if (_s != DART_OK) return _s;         \
-  } while (0)
 
 dart_status check_crit(const Plan& p, const void* X, const void*& crit, int32_t& crit_D,
                        int64_t& crit_ld) {

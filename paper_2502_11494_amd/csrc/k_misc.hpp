@@ -51,9 +51,8 @@ __device__ __forceinline__ void prepare_body(const Geo& g, const PrepareArgs& a)
     broken |= (g.cu[0] != 0 || g.cu[g.B] != g.total_N) ? 1 : 0;
     if (a.seq_cu) seq_bad |= (a.seq_cu[0] != 0 || a.seq_cu[g.B] != g.x_rows) ? 1 : 0;
   }
-  const int flags = __syncthreads_or(broken | (seq_bad << 1));
-  broken = flags & 1;
-  seq_bad = flags != 0;  // (broken offsets: the lengths are meaningless)
+  broken = __syncthreads_or(broken);
+  if (a.seq_cu) seq_bad = __syncthreads_or(seq_bad) | broken;  // (broken: the lengths are meaningless)
   int bad = 0;
   for (int b0 = 0; b0 < g.B; b0 += THREADS) {
     const int b = b0 + tid;

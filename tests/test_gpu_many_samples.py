@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("B,n_tensors,spans", [(1, 1, True), (64, 0, True), (65, 9, True),
                                                (255, 2, False), (257, 1, True), (1030, 1, True),
-                                               (1025, 0, False)])
+                                               (1025, 0, False), (2048, 0, False),
+                                               (2049, 0, False)])
 def test_many_small_samples(B, n_tensors, spans):
     rng = np.random.default_rng(B)
     w = W.ragged_batch(seed=B, B=B, n_lo=5, n_hi=40, D=64, P=3, keep_num=400)
