@@ -420,8 +420,9 @@ dart_status launch_prepare(Plan& p, void* ws, hipStream_t st, const int* seq_cu 
 // Ragged batches: also fills the ragged offsets, by a block of the same launch for up to
 // kPrepareInPass samples: as a launch of its own that takes 4-5 us first, however few they are, but a
 // block of the pass is 256 threads and takes about 0.5 us per 256 samples, which with many short
-// samples is longer than the rest of the pass (samples of at most 8 tokens of 64: 2048 samples 20.2 us
-// for norms and selection against 22.9 with the launch, 8192 60.6 and 61.9, 65536 485 and 420).
+// samples is longer than the rest of the pass (norms and selection of samples of at most 8 tokens of
+// 64 elements, in the pass and with the launch: 1000 samples 13.4 and 16.3 us, 4096 34.3 and 34.5, 8192
+// 60.6 and 58.2, 65536 485 and 400).
 constexpr int kPrepareInPass = 2048;
 dart_status launch_row_l1(Plan& p, const void* C, int Dc, long ldc, float* l1, bool keep_cached,
                           void* ws, hipStream_t st, double* l2sq = nullptr) {
