@@ -103,6 +103,14 @@ __device__ __forceinline__ bool sample_ok(const Geo& g, int n, int k) {
   return n > 0 && n <= g.max_N && g.Pin <= n && k >= g.Pin && k <= n;
 }
 
+// sample_ok of a sample with its own budget, for kernels that run beside prepare_body.  (Without
+// the division: floor(n * num / den) >= Pin exactly if n * num >= Pin * den; num <= den.)
+__device__ __forceinline__ bool sample_processed(const Geo& g, int n) {
+  if (n <= 0 || n > g.max_N || g.Pin > n) return false;
+  if (g.K > 0) return g.K >= g.Pin && g.K <= n;
+  return (long)n * g.keep_num >= (long)g.Pin * g.keep_den;
+}
+
 // Dense: arithmetic.  Ragged: k_prepare has validated the offsets and stored the
 // per-sample budgets as differences of cu_keep (0 for a skipped sample).
 __device__ __forceinline__ Sample sample_of(const Geo& g, int b) {

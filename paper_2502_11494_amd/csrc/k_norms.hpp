@@ -53,8 +53,8 @@ inline double l1_rel_bound(int dtype, int Dc) {
 // kernel's second pass (worth it only if the whole matrix fits there); otherwise
 // streaming (non-temporal) loads, which read faster.
 // SPAN: the samples' rows are spans of C (Geo::span); packed row r belongs to the sample b
-// with cu[b] <= r < cu[b+1] and lives at row span[b] + (r - cu[b]) of C.  Rows of a span that
-// leaves C, or of broken offsets, are not read.
+// with cu[b] <= r < cu[b+1] and lives at row span[b] + (r - cu[b]) of C.  Rows of a sample that
+// is skipped are not read and their norms are left alone.
 // PREP: the first 8 blocks are not for rows: block 0 does k_prepare's work (this kernel needs
 // none of its results), which as a launch of its own took 4-5 us before this one.
 // L2SQ (bf16 only, when the rows are the hidden states themselves): also the squared
@@ -95,8 +95,10 @@ __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int 
         const int mid = (lo + hi) >> 1;
         if (g.cu[mid] <= row) lo = mid; else hi = mid;
       }
+      // (the offsets may be anything here: prepare_body checks them while this runs)
       const long at = row - g.cu[lo], n = (long)g.cu[lo + 1] - g.cu[lo], s0 = g.span[lo];
-      live[r] = at >= 0 && at < n && s0 >= 0 && s0 + n <= (long)g.x_rows;
+      live[r] = at >= 0 && at < n && n <= g.max_N && sample_processed(g, (int)n) && s0 >= 0 &&
+                s0 + n <= (long)g.x_rows;
       crow = live[r] ? s0 + at : 0;
     }
     rp[r] = base + crow * rowbytes;

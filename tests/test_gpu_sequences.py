@@ -155,6 +155,34 @@ def test_invalid_spans_and_sequences_are_reported():
     assert not g["seq_out"].any()
 
 
+@pytest.mark.parametrize("budget", [dict(keep_num=1, keep_den=10), dict(K=60)])
+def test_skipped_samples_leave_their_norms_alone(budget):
+    """A span that leaves X, a budget below the pivots or above the sample, a sample above max_N."""
+    P, n_max = 8, 300
+    lens = np.array([200, 79, 250, 80, 301, 59, 300, 61])
+    kept = [n <= n_max and P <= (budget.get("K") or n // 10) <= n for n in lens]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    span = cu[:-1] + 5
+    rows = int(cu[-1]) + 20
+    span[2], kept[2] = rows - 249, False
+    X = torch.randn((rows, 64), generator=torch.Generator().manual_seed(3)).cuda()
+    desc = D.make_desc(len(lens), 64, P, D.DART_F32, cu_seqlens=torch.from_numpy(cu).cuda(),
+                       total_N=int(cu[-1]), max_N=n_max, X_rows=rows,
+                       span_start=torch.from_numpy(span.astype(np.int32)).cuda(), **budget)
+    ws = D.alloc_workspace(desc)
+    l1 = torch.full((int(cu[-1]),), -3.0, device="cuda")
+    piv = torch.full((len(lens) * P,), -5, dtype=torch.int32, device="cuda")
+    D.dart_select_pivots(desc, X, piv, ws, l1_out=l1)
+    assert D.dart_device_status(desc, ws) == D.DART_ERR_DEVICE
+    for b, n in enumerate(lens):
+        got = l1[cu[b]:cu[b + 1]]
+        if kept[b]:
+            want = X[span[b]:span[b] + n].double().abs().sum(1)
+            assert torch.allclose(got.double(), want, rtol=1e-6, atol=0.0)
+        else:
+            assert torch.all(got == -3.0) and torch.all(piv[b * P:(b + 1) * P] == -5)
+
+
 def test_random_combinations_of_the_variants():
     """Sixteen seeded random batches mixing everything the descriptor offers: spans inside
     whole sequences, pivots from outside, either retained-set rule, largest / smallest /
