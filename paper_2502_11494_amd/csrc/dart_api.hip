@@ -48,6 +48,7 @@ struct Plan {
   bool fusable;  // the shape and modes the one-launch path covers (see reduce_impl)
   bool norms_given;  // this call's norm pass also leaves the squared token norms
   int ks_waves, ks_split;  // bf16 score kernel: waves per workgroup and groups of them (fp32: 0)
+  int f32_groups;  // fp32 score tiles of 4 rows: groups of four pivots per workgroup
   unsigned long long seed; // DART_PIVOT_RANDOM: the seed of the draw
 };
 
@@ -165,25 +166,38 @@ KsChoice choose_score_tiles(const Geo& g, int units, bool first_read) {
   return best;
 }
 
-// Tile height of the fp32 score kernels.  Up to 4 rows per compute unit: tiles of 4 rows.  Beyond,
-// the height for which the busiest unit takes in the least: its tiles' rows plus the pivots, which
-// every tile reads again (ragged batches: half a tile is lost per sample).  Measured on 5776 rows
-// of 2048 with 16 pivots: 16, 20, 24, 28, 32 rows per tile take 20.0, 28.0, 17.4, 17.7, 18.8 us.
-// Above 48 pivots a second block of rows does not fit the registers: 16 rows.
-int f32_tile_rows(const Geo& g, int units) {
-  if (g.total_N <= 4L * units) return 4;
-  if (g.P > 48) return 16;
-  int best = 16;
-  long best_cost = -1;
-  for (int rows = 16; rows <= 32; rows += 4) {
-    const long tiles = g.cu == nullptr ? (long)g.B * ((g.N + rows - 1) / rows)
-                                       : (long)g.total_N / rows + (g.B + 1) / 2;
-    const long cost = (tiles + units - 1) / units * (rows + g.P);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best = rows;
-    }
+// Tiles of the fp32 score kernels: rows 2 (k_scores_f32_rows), 4 (k_scores_f32_t4, 4 * groups pivots
+// each) or 16 to 32 (k_scores_f32_t16).  All run at the speed of the compute unit that takes in the
+// most, token rows and the pivots that every tile reads again (ragged batches: half a tile is lost per
+// sample): the cheapest in rounds of the chip times rows per workgroup, weighted by how fast a kernel
+// takes rows in (its score pass on 40 to 9216 rows of 512 to 8192, 1 to 64 pivots: the choice is within
+// 1 % of the best on average; k_scores_f32_rows pays from rows of 12 KiB on).  Heights on 5776 rows of
+// 2048 with 16 pivots: 16, 20, 24, 28, 32 rows per tile take 20.0, 28.0, 17.4, 17.7, 18.8 us; above 48
+// pivots a second block of rows does not fit the registers: 16 rows.
+struct F32Tile { int rows, groups; };
+F32Tile f32_tile(const Geo& g, int units) {
+  auto tiles = [&](int rows) {
+    return g.cu == nullptr ? (long)g.B * ((g.N + rows - 1) / rows)
+                           : (long)g.total_N / rows + (g.B + 1) / 2;
+  };
+  auto rounds = [&](long blocks) { return (double)((blocks + units - 1) / units); };
+  F32Tile best = {16, 0};
+  double best_cost = 1e300;
+  auto consider = [&](int rows, int groups, double cost) {
+    if (cost >= best_cost) return;
+    best = {rows, groups};
+    best_cost = cost;
+  };
+  for (int rows = 16; rows <= (g.P > 48 ? 16 : 32); rows += 4)
+    consider(rows, 0, rounds(tiles(rows)) * (rows + g.P) * (g.P <= 16 ? 1.0 : 1.1));
+  for (int groups = 1; groups <= 4; groups *= 2) {
+    const int per = 4 * groups;
+    consider(4, groups, rounds(tiles(4) * ((g.P + per - 1) / per)) * (4 + std::min(per, g.P)) *
+                            (groups == 1 ? 1.0 : groups == 2 ? 1.3 : 1.5));
   }
+  if (g.D > 3072 && g.P <= 24 && g.total_N <= 8L * units)
+    consider(2, 0, rounds(tiles(2)) * ((g.P + kF32Piv - 1) / kF32Piv) * (kF32Rows + kF32Piv) *
+                       (g.D > 4096 ? 0.65 : g.P <= 8 ? 0.6 : 0.9));
   return best;
 }
 
@@ -295,7 +309,9 @@ dart_status make_plan(const dart_desc* d, Plan& p) {
   g.span = d->span_start;
   g.x_rows = d->span_start ? d->X_rows : (int)total;
   // score tiles: the height (fp32) or the shape (bf16) chosen for this batch
-  g.tile_rows = f32_tile_rows(g, compute_units());
+  const F32Tile ft = f32_tile(g, compute_units());
+  g.tile_rows = ft.rows;
+  p.f32_groups = ft.groups;
   p.ks_waves = p.ks_split = 0;
   if (d->dtype == DART_BF16) {
     // (pivots given, drawn or all from outside: no norm pass reads X before the score pass)
@@ -595,21 +611,29 @@ dart_status launch_scores(const Plan& p, const void* X, const int* piv, float* S
   const double* pl2 = at<double>(ws, p.o_pl2);
   const double* l2sq = p.norms_given ? at<double>(ws, p.o_l2) : nullptr;
   if (p.g.dtype == kF32) {
-#define DART_LAUNCH_F32(KERNEL)                                                                  \
-  DART_LAUNCH((KERNEL), dim3(p.tiles_bound), dim3(kF32Waves * 64), 0, st, p.g, X, piv, pl2, S)
-    if (p.g.tile_rows == 4) {
-      if (p.g.P <= 8) DART_LAUNCH_F32(k_scores_f32_t4<2>); else DART_LAUNCH_F32(k_scores_f32_t4<4>);
+#define DART_LAUNCH_F32(KERNEL, PIVOTS, THREADS)                                                 \
+  DART_LAUNCH((KERNEL), dim3(p.tiles_bound, (p.g.P + (PIVOTS) - 1) / (PIVOTS)), dim3(THREADS), 0, \
+              st, p.g, X, piv, pl2, S)
+    constexpr int threads = kF32Waves * 64;
+    if (p.g.tile_rows == kF32Rows) {
+      DART_LAUNCH_F32(k_scores_f32_rows, kMaxP, 256);
+    } else if (p.g.tile_rows == 4) {
+      switch (p.f32_groups) {
+        case 1: DART_LAUNCH_F32(k_scores_f32_t4<1>, 4, threads); break;
+        case 2: DART_LAUNCH_F32(k_scores_f32_t4<2>, 8, threads); break;
+        default: DART_LAUNCH_F32(k_scores_f32_t4<4>, 16, threads); break;
+      }
     } else {
 #define DART_LAUNCH_F32_NB(NB)                                                                   \
   do {                                                                                           \
-    if (p.g.tile_rows == 16) DART_LAUNCH_F32((k_scores_f32_t16<NB, 1>));                         \
-    else DART_LAUNCH_F32((k_scores_f32_t16<NB, 2>));                                             \
+    if (p.g.tile_rows == 16) DART_LAUNCH_F32((k_scores_f32_t16<NB, 1>), kMaxP, threads);         \
+    else DART_LAUNCH_F32((k_scores_f32_t16<NB, 2>), kMaxP, threads);                             \
   } while (0)
       switch (p.g.Ppad / 16) {
         case 1: DART_LAUNCH_F32_NB(1); break;
         case 2: DART_LAUNCH_F32_NB(2); break;
         case 3: DART_LAUNCH_F32_NB(3); break;
-        default: DART_LAUNCH_F32((k_scores_f32_t16<4, 1>)); break;  // (f32_tile_rows)
+        default: DART_LAUNCH_F32((k_scores_f32_t16<4, 1>), kMaxP, threads); break;  // (f32_tile)
       }
 #undef DART_LAUNCH_F32_NB
     }

@@ -499,11 +499,14 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_scores_f32_t16(
   }
 }
 
-// Few rows (k_scores_f32_t4): tiles of 4 rows, so that one 576-token image gives more than a
-// hundred workgroups; v_mfma_f64_4x4x4 (four independent 4x4x4 blocks, 16 cycles).  PG = 4: the
-// blocks are four groups of four pivots; PG = 2 (at most 8 pivots): two groups of pivots times
-// two halves of a step's pieces.  Latency-bound (a chain of launch, pivot indices, rows, sums): eight
-// steps in flight per wave.  One 576-token image of 4096: 13.4 us on the vector ALU, 13.1 us here.
+// Few rows (k_scores_f32_t4): tiles of 4 rows by 4 PG pivots, so that one 576-token image gives
+// hundreds of workgroups; v_mfma_f64_4x4x4 (four independent 4x4x4 blocks, 16 cycles).  Of the blocks
+// PG are groups of four pivots, times 4 / PG parts of a step's pieces: with PG = 1 a workgroup takes in
+// the fewest pivot rows and a load's neighbouring lanes are neighbours in memory, with PG = 4 the
+// fewest workgroups read a token row (f32_tile chooses).  Latency-bound (a chain of launch, pivot
+// indices, rows, sums): eight steps in flight per wave.  Scores of 300 rows of 4096, stage entry point,
+// with 8, 24, 64 pivots: 11.6, 16.9, 37 us; on the vector ALU 12.3, 26.9, 64 us, and 14.5, 37, 78 us
+// with a workgroup per 4 rows going through all pivots.
 // Operand layout: lane l holds row l & 3 of block (l >> 2) & 3, k = l >> 4; result: lane l holds
 // column l & 3 of block (l >> 2) & 3, row l >> 4.
 struct F32SmallShared {
@@ -511,7 +514,7 @@ struct F32SmallShared {
   double xx[kF32Waves][kWave];
 };
 
-// grid: tiles of 4 rows; 512 threads.
+// grid: (tiles of 4 rows, groups of 4 PG pivots); 512 threads.
 template <int PG>
 __global__ __launch_bounds__(kF32Waves * 64) void k_scores_f32_t4(
     Geo g, const void* __restrict__ X, const int* __restrict__ piv,
@@ -525,7 +528,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_scores_f32_t4(
   if (sm.k == 0 || tl * 4 >= sm.n) return;
   const int n = sm.n, P = g.P, j0 = tl * 4;
   const int r4 = lane & 3, blk = (lane >> 2) & 3, pg = blk % PG;
-  const int col = (blk / PG) * 4 + (lane >> 4);  // the lane's piece inside a step
+  const int col = (lane >> 4) * kHalves + blk / PG;  // the lane's piece inside a step
   const int pieces = g.D / 4;
   const int steps = pieces / kStep;  // whole steps
   const int s0 = wave * steps / kF32Waves, cnt = (wave + 1) * steps / kF32Waves - s0;
@@ -538,72 +541,184 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_scores_f32_t4(
   const bool rest_in = steps * kStep + col < pieces;
   const int t_rest = rest_in ? steps * kStep + col : 0;
   float* Sb = S + (long)P * sm.row0;
-  for (int i0 = 0; i0 < P; i0 += 4 * PG) {
-    const int i = i0 + pg * 4 + r4 < P ? i0 + pg * 4 + r4 : P - 1;  // columns past P: never stored
-    const f32x4v* pr = reinterpret_cast<const f32x4v*>(pivot_row(g, X, 4, sm, b, i, piv));
-    const f32x4v* ps = pr + s0 * kStep + col;
-    f32x4v ra[kRing], rp[kRing];
-    auto load = [&](int slot, int s) {
-      ra[slot] = xs[s * kStep];
-      rp[slot] = ps[s * kStep];
+  const int i0 = blockIdx.y * 4 * PG;
+  const int i = i0 + pg * 4 + r4 < P ? i0 + pg * 4 + r4 : P - 1;  // columns past P: never stored
+  const f32x4v* pr = reinterpret_cast<const f32x4v*>(pivot_row(g, X, 4, sm, b, i, piv));
+  const f32x4v* ps = pr + s0 * kStep + col;
+  f32x4v ra[kRing], rp[kRing];
+  auto load = [&](int slot, int s) {
+    ra[slot] = xs[s * kStep];
+    rp[slot] = ps[s * kStep];
+  };
+  double acc4[4] = {0.0, 0.0, 0.0, 0.0}, xx4[4] = {0.0, 0.0, 0.0, 0.0};  // independent chains
+  auto use = [&](const f32x4v& x, const f32x4v& p) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double a = (double)x[e];
+      acc4[e] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, (double)p[e], acc4[e], 0, 0, 0);
+      xx4[e] = fma(a, a, xx4[e]);
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < kRing; ++u)
+    if (u < cnt) load(u, u);
+  int s = 0;
+  for (; s + 2 * kRing <= cnt; s += kRing) {
+#pragma unroll
+    for (int u = 0; u < kRing; ++u) {
+      use(ra[u], rp[u]);
+      load(u, s + kRing + u);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kRing; ++u)
+    if (s + u < cnt) {
+      use(ra[u], rp[u]);
+      if (s + kRing + u < cnt) load(u, s + kRing + u);
+    }
+#pragma unroll
+  for (int u = 0; u < kRing - 1; ++u)
+    if (s + kRing + u < cnt) use(ra[u], rp[u]);
+  if (rest) {
+    const f32x4v fz = {0.f, 0.f, 0.f, 0.f};
+    const f32x4v x = xr[t_rest], p = pr[t_rest];
+    use(rest_in ? x : fz, rest_in ? p : fz);
+  }
+  const double acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
+  const double xx = (xx4[0] + xx4[1]) + (xx4[2] + xx4[3]);
+  sh.part[wave][lane] = acc;
+  sh.xx[wave][lane] = xx;
+  __syncthreads();
+  if (tid < 16 * PG) {
+    const int m = tid & 3, pi = tid >> 2;  // token row of the tile, pivot of this group
+    double d = 0.0, x2 = 0.0;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {
+#pragma unroll
+      for (int h = 0; h < kHalves; ++h) {
+        d += sh.part[w][(pi & 3) + 4 * ((pi >> 2) + PG * h) + 16 * m];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x2 += sh.xx[w][m + 4 * (PG * h) + 16 * k];
+      }
+    }
+    if (i0 + pi < P && j0 + m < n) {
+      const double den = sqrt(pl2[b * g.Ppad + i0 + pi]) * sqrt(x2);
+      Sb[(long)(i0 + pi) * n + j0 + m] = (float)(den > 0.0 ? d / den : 0.0) + 0.0f;
+    }
+  }
+}
+
+// Long rows, few of them (k_scores_f32_rows): two rows by 8 pivots at a time on the vector ALU.  A wave's
+// load is 1 KiB of one row, where the matrix instructions want 4 or 16 rows side by side: from rows
+// of 16 KiB on a compute unit takes in half again as much that way (about 50 against 31 GB/s), and with
+// few pivots that counts for more than the arithmetic.  Scores of 1500 rows of 8192 by 8 pivots: 24.8 us,
+// 31 on tiles of 16 rows or of 4; 576 rows by 8: 20, 23.  With more than 24 pivots it is always slower.
+// Its 4 waves split D (piece t of a row goes to wave (t / 64) % 4); the next pieces are requested before
+// the current ones are used; the 4 partial sums of a dot product are added in wave order, each wave's
+// own sum is a fixed lane-strided order plus butterfly: a score depends only on the two rows' bytes.
+constexpr int kF32Piv = 8, kF32Rows = 2;
+
+// grid: tiles of 2 rows; 256 threads.
+__global__ __launch_bounds__(256) void k_scores_f32_rows(Geo g, const void* __restrict__ X,
+                                                         const int* __restrict__ piv,
+                                                         const double* __restrict__ pl2,
+                                                         float* __restrict__ S) {
+  __shared__ double red[4][kF32Rows * kF32Piv + kF32Rows];  // per wave: dot[2][8], xx[2]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int b, tl;
+  if (!locate_tile(g, blockIdx.x, b, tl)) return;
+  const Sample sm = sample_of(g, b);
+  const int n = sm.n, P = g.P, j0 = tl * kF32Rows;
+  if (sm.k == 0 || j0 >= n) return;
+  const float* Xb = static_cast<const float*>(X) + (long)sm.xrow * g.ld;
+  const int pieces = g.D / 4;
+  const f32x4v* xr[kF32Rows];
+#pragma unroll
+  for (int r = 0; r < kF32Rows; ++r) {
+    const int j = j0 + r < n ? j0 + r : n - 1;  // rows past the end re-read the last; never stored
+    xr[r] = reinterpret_cast<const f32x4v*>(Xb + (long)j * g.ld);
+  }
+  float* Sb = S + (long)P * sm.row0;
+  const f32x4v fz = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0; i0 < P; i0 += kF32Piv) {
+    const f32x4v* pr[kF32Piv];
+#pragma unroll
+    for (int q = 0; q < kF32Piv; ++q) {
+      const int i = i0 + q < P ? i0 + q : P - 1;
+      pr[q] = reinterpret_cast<const f32x4v*>(pivot_row(g, X, 4, sm, b, i, piv));
+    }
+    double dot[kF32Rows][kF32Piv], xx[kF32Rows];
+#pragma unroll
+    for (int r = 0; r < kF32Rows; ++r) {
+      xx[r] = 0.0;
+#pragma unroll
+      for (int q = 0; q < kF32Piv; ++q) dot[r][q] = 0.0;
+    }
+    f32x4v xv[kF32Rows], pv[kF32Piv], xn[kF32Rows], pn[kF32Piv];
+    int t = tid;  // piece index: 256 apart per step
+    auto fetch = [&](int tt, f32x4v (&xo)[kF32Rows], f32x4v (&po)[kF32Piv]) {
+      const bool in = tt < pieces;
+      const int ts = in ? tt : 0;  // a piece past the end re-reads piece 0 and counts as zero
+#pragma unroll
+      for (int r = 0; r < kF32Rows; ++r) {
+        const f32x4v v = xr[r][ts];
+        xo[r] = in ? v : fz;
+      }
+#pragma unroll
+      for (int q = 0; q < kF32Piv; ++q) {
+        const f32x4v v = pr[q][ts];
+        po[q] = in ? v : fz;
+      }
     };
-    double acc4[4] = {0.0, 0.0, 0.0, 0.0}, xx4[4] = {0.0, 0.0, 0.0, 0.0};  // independent chains
-    auto use = [&](const f32x4v& x, const f32x4v& p) {
+    fetch(t, xv, pv);
+    for (; t < pieces; t += 256) {
+      fetch(t + 256, xn, pn);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const double a = (double)x[e];
-        acc4[e] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, (double)p[e], acc4[e], 0, 0, 0);
-        xx4[e] = fma(a, a, xx4[e]);
-      }
-    };
+        double x[kF32Rows];
 #pragma unroll
-    for (int u = 0; u < kRing; ++u)
-      if (u < cnt) load(u, u);
-    int s = 0;
-    for (; s + 2 * kRing <= cnt; s += kRing) {
+        for (int r = 0; r < kF32Rows; ++r) {
+          x[r] = (double)xv[r][e];
+          xx[r] = fma(x[r], x[r], xx[r]);
+        }
 #pragma unroll
-      for (int u = 0; u < kRing; ++u) {
-        use(ra[u], rp[u]);
-        load(u, s + kRing + u);
-      }
-    }
+        for (int q = 0; q < kF32Piv; ++q) {
+          const double p = (double)pv[q][e];
 #pragma unroll
-    for (int u = 0; u < kRing; ++u)
-      if (s + u < cnt) {
-        use(ra[u], rp[u]);
-        if (s + kRing + u < cnt) load(u, s + kRing + u);
-      }
-#pragma unroll
-    for (int u = 0; u < kRing - 1; ++u)
-      if (s + kRing + u < cnt) use(ra[u], rp[u]);
-    if (rest) {
-      const f32x4v fz = {0.f, 0.f, 0.f, 0.f};
-      const f32x4v x = xr[t_rest], p = pr[t_rest];
-      use(rest_in ? x : fz, rest_in ? p : fz);
-    }
-    const double acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
-    const double xx = (xx4[0] + xx4[1]) + (xx4[2] + xx4[3]);
-    sh.part[wave][lane] = acc;
-    sh.xx[wave][lane] = xx;
-    __syncthreads();
-    if (tid < 16 * PG) {
-      const int m = tid & 3, pi = tid >> 2;  // token row of the tile, pivot of this group
-      double d = 0.0, x2 = 0.0;
-#pragma unroll
-      for (int w = 0; w < kF32Waves; ++w) {
-#pragma unroll
-        for (int h = 0; h < kHalves; ++h) {
-          d += sh.part[w][(pi & 3) + 4 * ((pi >> 2) + PG * h) + 16 * m];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) x2 += sh.xx[w][m + 4 * (PG * h) + 16 * k];
+          for (int r = 0; r < kF32Rows; ++r) dot[r][q] = fma(p, x[r], dot[r][q]);
         }
       }
-      if (i0 + pi < P && j0 + m < n) {
-        const double den = sqrt(pl2[b * g.Ppad + i0 + pi]) * sqrt(x2);
-        Sb[(long)(i0 + pi) * n + j0 + m] = (float)(den > 0.0 ? d / den : 0.0) + 0.0f;
+#pragma unroll
+      for (int r = 0; r < kF32Rows; ++r) xv[r] = xn[r];
+#pragma unroll
+      for (int q = 0; q < kF32Piv; ++q) pv[q] = pn[q];
+    }
+    // the wave's sums, then the four waves' partials in wave order
+#pragma unroll
+    for (int r = 0; r < kF32Rows; ++r) {
+#pragma unroll
+      for (int q = 0; q < kF32Piv; ++q) {
+        const double d = wave_sum(dot[r][q]);
+        if (lane == 0) red[wave][r * kF32Piv + q] = d;
+      }
+      const double x2 = wave_sum(xx[r]);
+      if (lane == 0) red[wave][kF32Rows * kF32Piv + r] = x2;
+    }
+    __syncthreads();
+    if (tid < kF32Rows * kF32Piv) {
+      const int r = tid / kF32Piv, q = tid - r * kF32Piv;
+      if (i0 + q < P && j0 + r < n) {
+        double d = 0.0, x2 = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          d += red[w][r * kF32Piv + q];
+          x2 += red[w][kF32Rows * kF32Piv + r];
+        }
+        const double den = sqrt(pl2[b * g.Ppad + i0 + q]) * sqrt(x2);
+        Sb[(long)(i0 + q) * n + j0 + r] = (float)(den > 0.0 ? d / den : 0.0) + 0.0f;
       }
     }
-    __syncthreads();  // part and xx are reused by the next group of pivots
+    __syncthreads();  // red is reused by the next group of pivots
   }
 }
 

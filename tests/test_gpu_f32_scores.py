@@ -1,5 +1,6 @@
-"""The fp32 score kernels at the edges of their tiles: every tile height the host can choose, every
-number of pivot blocks, rows whose pieces end inside a step, samples that end inside a tile."""
+"""The fp32 score kernels at the edges of their tiles: every kernel and tile height the host can
+choose, every number of pivot blocks, rows whose pieces end inside a step, samples that end inside a
+tile."""
 import numpy as np
 import pytest
 import torch
@@ -9,13 +10,16 @@ import paper_2502_11494_amd as D
 
 pytestmark = pytest.mark.gpu
 
-# (lengths, D, P): up to 4 rows per compute unit -> tiles of 4 rows; more -> 16 to 32 rows
+# (lengths, D, P)
 CASES = [
-    ([1], 4, 1), ([5], 36, 5), ([70], 128, 8), ([67, 3, 258], 1028, 3),        # 4 rows, <= 8 pivots
-    ([40], 64, 9), ([200, 201], 100, 16), ([130], 260, 17), ([90], 2052, 64),  # 4 rows, > 8 pivots
-    ([1100], 36, 8), ([513, 800], 132, 16), ([1029], 4, 1),                    # 16 rows
+    ([1], 4, 1), ([5], 36, 5), ([70], 128, 8), ([67, 3, 258], 1028, 3),        # tiles of 4 rows, 4 pivots
+    ([40], 64, 9), ([130], 260, 17), ([1029], 4, 1),
+    ([200, 201], 100, 16), ([603], 2052, 8), ([333], 68, 23), ([90], 2052, 64),  # 4 rows, 8 pivots
+    ([900], 100, 14), ([901, 2], 1028, 16),                                    # 4 rows, 16 pivots
+    ([1100], 36, 8), ([513, 800], 132, 16),                                    # 16 rows
     ([5776], 68, 16), ([700, 2050, 1999, 700], 96, 32), ([5001], 36, 33),      # taller tiles
     ([4500, 33], 40, 48), ([1500], 160, 64),
+    ([515, 2, 704], 4100, 5), ([1301], 3076, 8), ([700], 6148, 23), ([33], 8196, 3),  # vector ALU
 ]
 
 
