@@ -36,6 +36,7 @@ constexpr int kRetWaves = kRetThreads / kWave;
 // 32 lists of a 9216-token video sample (17424 entries) or the 16 lists of a 16384-token sample at
 // one ninth (15.6 K) are staged in one go, and the walk reads the indices alone.
 constexpr int kRetList = 18432;
+static_assert(kRetList >= kMaxN, "a list has at most an entry per token: every stage is staged whole");
 constexpr int kRetQ = 1024;      // band candidates awaiting an fp64 score
 constexpr int kRetInFlight = 4;  // 16-byte pieces per row and lane in flight in the fp64 re-scoring
 // Quotas from which the host takes the walk of all waves together (k_retain's WIDE): wave 0 alone
@@ -132,16 +133,12 @@ __device__ __forceinline__ void retain_body(
     // not always compile here)
     const int first = __builtin_amdgcn_readfirstlane(first_any);  // block-uniform: keep it scalar
     group_base = __builtin_amdgcn_readfirstlane(__shfl(off_v, first, kWave));
-    const int l0 = __builtin_amdgcn_readfirstlane(__shfl(len_v, first, kWave));
-    const int l0c = l0 < kRetList ? l0 : kRetList;
-    // a later stage s joins the group while everything up to the end of its list fits; the
-    // list ends grow with s, so the stages that fit are the lanes first+1 .. group_hi-1
-    const int rel_end = off_v + len_v - group_base - l0 + l0c;  // staged entries through stage `lane`
-    const bool fits = lane > first && lane < P && rel_end <= kRetList;
-    const int extra = __builtin_amdgcn_readfirstlane(__popcll(__ballot(fits)));
-    group_hi = first + 1 + extra;
-    const int through = __builtin_amdgcn_readfirstlane(__shfl(rel_end, first + extra, kWave));
-    staged_total = extra > 0 ? through : l0c;
+    // a later stage joins the group while everything up to the end of its list fits; the list ends
+    // grow with the stage, so the stages that fit are the lanes first .. group_hi-1
+    const int rel_end = off_v + len_v - group_base;  // entries through stage `lane`
+    const bool fits = lane >= first && lane < P && rel_end <= kRetList;
+    group_hi = first + __builtin_amdgcn_readfirstlane(__popcll(__ballot(fits)));
+    staged_total = __builtin_amdgcn_readfirstlane(__shfl(rel_end, group_hi - 1, kWave));
   };
   // a group moves in two halves of kStageLoads loads per thread (72 KiB in flight each)
   constexpr int kStageLoads = kRetList / kRetThreads / 2;
@@ -219,16 +216,9 @@ __device__ __forceinline__ void retain_body(
     if (tid >= next && tid < group_hi) sh.st_start[tid] = sh.st_ahead[tid] = 0;
     __syncthreads();
     const int walk_end = group_hi < stages ? group_hi : stages;
-    // The global pointer carries its address space: with a generic one the compiler may fold
-    // the two returns into one flat load from a selected pointer (and its LDS-to-flat cast
-    // did not compile in every context).
-    typedef const unsigned long long __attribute__((address_space(1)))* GlobalList;
-    const GlobalList glist_g = (GlobalList)glist;
-    auto entry_of = [&](int i, int p) -> unsigned long long {
-      const int o = sh.st_off[i] - group_base + p;  // position among the staged entries
-      if (o < staged_total) return ((unsigned long long)sh.lkey[o] << 32) | sh.lidx[o];
-      if (COH) return ld_dev<true>(&glist[sh.st_off[i] + p]);
-      return glist_g[sh.st_off[i] + p];
+    auto entry_of = [&](int i, int p) -> unsigned long long {  // entry p of stage i's list
+      const int o = sh.st_off[i] - group_base + p;
+      return ((unsigned long long)sh.lkey[o] << 32) | sh.lidx[o];
     };
 
     // ------------------------------------------------------------------ speculative walk
@@ -263,7 +253,6 @@ __device__ __forceinline__ void retain_body(
         const int quota = __builtin_amdgcn_readlane(quota_v, i);
         const int len = __builtin_amdgcn_readlane(len_v, i);
         const int off = __builtin_amdgcn_readlane(off_v, i) - group_base;
-        const bool staged_all = off + len <= staged_total;
         int taken = 0;
         for (int pos = 0; pos < len && taken < quota; pos += kRetThreads) {
           const int p = pos + tid;
@@ -271,10 +260,7 @@ __device__ __forceinline__ void retain_body(
           int j = kMaxN + lane;
           unsigned long long m = 0ull;
           if (busy) {
-            if (p < len) {
-              if (staged_all) j = pos == 0 ? pre : (int)sh.lidx[off + p];
-              else j = (int)(uint32_t)entry_of(i, p);
-            }
+            if (p < len) j = pos == 0 ? pre : (int)sh.lidx[off + p];
             m = __builtin_amdgcn_ballot_w64(sh.owner[j] == kOwnNone);
           }
           if (lane == 0) sh.wcnt[wave] = __popcll(m);
@@ -323,7 +309,7 @@ __device__ __forceinline__ void retain_body(
         int len = __builtin_amdgcn_readlane(len_v, next);
         int off = __builtin_amdgcn_readlane(off_v, next) - group_base;
         read_ahead(0, off);
-        take_over(0, off + len <= staged_total ? len : 0);
+        take_over(0, len);
         for (int i = next; i < walk_end; ++i) {
           int own[kRun];
 #pragma unroll
@@ -345,11 +331,8 @@ __device__ __forceinline__ void retain_body(
             sh.owner[tok[c]] = (unsigned char)(own[c] == kOwnNone && r < quota ? i : own[c]);
             taken += __popcll(m);
           }
-          const bool staged_all = off + len <= staged_total;  // the usual case
-          for (int p = staged_all ? pos + kRun * kWave : 0; p < len && taken < quota; p += kWave) {
-            const bool have = p + lane < len;
-            const int j = !have ? kMaxN + lane
-                                : staged_all ? (int)sh.lidx[off + p + lane] : (int)(uint32_t)entry_of(i, p + lane);
+          for (int p = pos + kRun * kWave; p < len && taken < quota; p += kWave) {
+            const int j = p + lane < len ? (int)sh.lidx[off + p + lane] : kMaxN + lane;
             const bool cand = sh.owner[j] == kOwnNone;
             const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
             const int r = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
@@ -362,7 +345,7 @@ __device__ __forceinline__ void retain_body(
           quota = quota_n;
           len = len_n;
           off = off_n;
-          take_over(pos, off + len <= staged_total ? len : 0);
+          take_over(pos, len);
         }
       };
       // runs that usually fill the quota: about a third of the entries past st_ahead are taken
@@ -387,8 +370,7 @@ __device__ __forceinline__ void retain_body(
         for (int i = next + wave - 1; i < walk_end; i += kRetWaves - 1) {
           const int len = __builtin_amdgcn_readlane(len_v, i);
           const int off = __builtin_amdgcn_readlane(off_v, i) - group_base;
-          // (the next two stages' positions have been read already)
-          if (i <= walked + 1 || off + len > staged_total) continue;
+          if (i <= walked + 1) continue;  // (the next two stages' positions have been read already)
           const int at = __builtin_amdgcn_readfirstlane(lds_load(&sh.st_ahead[i]));
           const int p = at + lane;
           const int j = p < len ? (int)sh.lidx[off + p] : 0;
