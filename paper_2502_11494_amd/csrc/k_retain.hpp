@@ -143,17 +143,17 @@ __device__ __forceinline__ void retain_body(
   // a group moves in two halves of kStageLoads loads per thread (72 KiB in flight each)
   constexpr int kStageLoads = kRetList / kRetThreads / 2;
   unsigned long long staged[kStageLoads];
-  auto load_half = [&](int h) {
+  auto load_half = [&](int h, int from) {
 #pragma unroll
     for (int u = 0; u < kStageLoads; ++u) {
-      const int t = (h * kStageLoads + u) * kRetThreads + tid;
+      const int t = (h * kStageLoads + u) * kRetThreads + from;
       staged[u] = t < staged_total ? ld_dev<COH>(&glist[group_base + t]) : 0ull;
     }
   };
-  auto store_half = [&](int h) {
+  auto store_half = [&](int h, int from) {
 #pragma unroll
     for (int u = 0; u < kStageLoads; ++u) {
-      const int t = (h * kStageLoads + u) * kRetThreads + tid;
+      const int t = (h * kStageLoads + u) * kRetThreads + from;
       if (t < staged_total) {
         sh.lkey[t] = (uint32_t)(staged[u] >> 32);
         sh.lidx[t] = (unsigned short)staged[u];
@@ -164,7 +164,7 @@ __device__ __forceinline__ void retain_body(
   // the first group's lists and the pivots are requested before LDS is cleared, so
   // the kernel waits for global memory once
   plan_group(0);
-  load_half(0);
+  load_half(0, tid);
   int my_pivot = -1;
   if (tid < g.Pin) my_pivot = ld_dev<COH>(&piv[b * P + tid]);  // pivots from outside hold no slot
   double my_pl2 = 0.0;
@@ -178,10 +178,10 @@ __device__ __forceinline__ void retain_body(
     sh.st_len[tid] = len_v;
     sh.st_off[tid] = off_v;
   }
-  store_half(0);
+  store_half(0, tid);
   if (staged_total > kStageLoads * kRetThreads) {
-    load_half(1);
-    store_half(1);
+    load_half(1, tid);
+    store_half(1, tid);
   }
   __syncthreads();
   if (my_pivot >= 0 && my_pivot < n) sh.owner[my_pivot] = kOwnPivot;
@@ -198,13 +198,17 @@ __device__ __forceinline__ void retain_body(
   int next = 0;  // first stage not yet final (block-uniform)
   while (next < stages) {
     if (next >= group_hi) {
+      // (opaque, or the places of all loads are worked out ahead of the loop, where they cost every
+      // call the registers of a second group: 21 spilled, 1 to 2 us)
+      int from = tid;
+      asm volatile("" : "+v"(from));
       plan_group(next);
-      load_half(0);
+      load_half(0, from);
       __syncthreads();  // nobody reads the old group any more
-      store_half(0);
+      store_half(0, from);
       if (staged_total > kStageLoads * kRetThreads) {
-        load_half(1);
-        store_half(1);
+        load_half(1, from);
+        store_half(1, from);
       }
     }
     if (tid == 0) {
