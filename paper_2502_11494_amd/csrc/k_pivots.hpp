@@ -138,15 +138,18 @@ __device__ __forceinline__ void select_pivots_body(
   }
   __syncthreads();
   // rank by (fp64 value, index); only ranks < P matter
-  if (nU <= kWave) {
-    // a wave per candidate: lane o compares candidate o with it, the ballot counts
-    const bool on = lane < nU;
-    const double co = on ? c64[lane] : 0.0;
-    const int jo = on ? sh.cand[lane] : 0;
+  if (nU <= 2 * kWave) {
+    // a wave per candidate: lane o compares candidates o and o + 64 with it, the ballots count (64
+    // pivots leave about 74 candidates)
+    const int o2 = lane + kWave;
+    const bool on = lane < nU, on2 = o2 < nU;
+    const double co = on ? c64[lane] : 0.0, co2 = on2 ? c64[o2] : 0.0;
+    const int jo = on ? sh.cand[lane] : 0, jo2 = on2 ? sh.cand[o2] : 0;
     for (int u = w; u < nU; u += kPivWaves) {
       const double cu = c64[u];
       const int ju = sh.cand[u];
-      const int cnt = __popcll(__ballot(on && (co < cu || (co == cu && jo < ju))));
+      int cnt = __popcll(__ballot(on && (co < cu || (co == cu && jo < ju))));
+      if (nU > kWave) cnt += __popcll(__ballot(on2 && (co2 < cu || (co2 == cu && jo2 < ju))));
       if (lane == 0 && cnt < P) {
         st_dev<COH>(&piv[b * g.P + cnt], ju);
         st_dev<COH>(&pl2[b * g.Ppad + cnt], l2s[u]);
