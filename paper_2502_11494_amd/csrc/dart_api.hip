@@ -308,16 +308,17 @@ dart_status make_plan(const dart_desc* d, Plan& p) {
   g.E = d->P_ext > 0 ? d->ext_pivots : nullptr;
   g.span = d->span_start;
   g.x_rows = d->span_start ? d->X_rows : (int)total;
-  // score tiles: the height (fp32) or the shape (bf16) chosen for this batch
-  const F32Tile ft = f32_tile(g, compute_units());
-  g.tile_rows = ft.rows;
-  p.f32_groups = ft.groups;
-  p.ks_waves = p.ks_split = 0;
+  // score tiles: the kernel and height (fp32) or the shape (bf16) chosen for this batch
+  p.ks_waves = p.ks_split = p.f32_groups = 0;
   if (d->dtype == DART_BF16) {
     // (pivots given, drawn or all from outside: no norm pass reads X before the score pass)
     const dart_status ts = plan_score_tiles(p, d->pivot_mode == DART_PIVOT_GIVEN ||
                                                    d->pivot_mode == DART_PIVOT_RANDOM || Pin == 0);
     if (ts != DART_OK) return ts;
+  } else {
+    const F32Tile t = f32_tile(g, compute_units());
+    g.tile_rows = t.rows;
+    p.f32_groups = t.groups;
   }
   p.esz = esz;
   if (!ragged) {
