@@ -697,9 +697,10 @@ dart_status launch_retain(const Plan& p, const float* S, const int* piv, const v
     DART_LAUNCH_CHECK();
     return DART_OK;
   }
-  // (the quota of the batch's longest sample)
+  // (of the batch's longest sample)
   const int k_big = p.g.K > 0 ? p.g.K : (int)(((long)p.g.max_N * p.g.keep_num) / p.g.keep_den);
-  const bool wide = (k_big - p.g.Pin) / p.g.P >= kWideQuota;
+  const int quota = (k_big - p.g.Pin) / p.g.P;
+  const bool wide = quota >= kWideQuota || (long)quota * p.g.P > kWideSlots;
 #define DART_LAUNCH_RETAIN(DT, WIDE)                                                             \
   DART_LAUNCH((k_retain<DT, WIDE>), dim3(p.g.B), dim3(kRetThreads), 0, st, p.g, S, lists, piv, X, \
               keep, cu_keep, scr_f64, two_tau, pl2)

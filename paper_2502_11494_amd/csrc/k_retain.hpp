@@ -42,8 +42,12 @@ constexpr int kRetInFlight = 4;  // 16-byte pieces per row and lane in flight in
 // Quotas from which the host takes the walk of all waves together (k_retain's WIDE): wave 0 alone
 // takes about 0.25 us per stage and 0.1 us more for every 64 entries beyond 128, all waves 0.5 us
 // whatever the length (8 stages of quota 130 on 1500 tokens: 8.4 against 5.5 us; 16 of quota 19 on
-// 2880 tokens: 5.1 against 8.5).
-constexpr int kWideQuota = 64;
+// 2880 tokens: 5.1 against 8.5).  The helpers pass over some 64 taken entries per look, so with many
+// stages and lists that are nearly the same wave 0 meets longer and longer heads: beyond kWideSlots
+// slots in all the walk of all waves again (order and retained set of four samples of 9216 tokens, wave
+// 0 alone and all waves, equal lists: 32 pivots of quota 32 30.3 and 33.6 us, 64 of 32 89 and 78, 64 of
+// 63 215 and 127; independent lists 25.6 and 33.0, 45.8 and 62, 73 and 81).
+constexpr int kWideQuota = 64, kWideSlots = 2048;
 constexpr unsigned char kOwnNone = 0xff, kOwnPivot = 0xfe;
 
 struct RetainShared {
