@@ -67,10 +67,10 @@ struct Geo {
   int tile_rows;    // token rows per score tile: 16 per wave of the score kernel's workgroup
   long ld;          // X row stride, elements
   const int* cu;    // device cu_seqlens, nullptr = dense
-  // ragged only, filled by k_prepare: packed offsets of keep and of score tiles
+  // ragged only, filled by prepare_body: packed offsets of keep and of score tiles
   const int* cu_keep;
   const int* tile_start;
-  // ragged batches of at most kMaxBySize samples, filled by k_prepare: the samples from the
+  // ragged batches of at most kMaxBySize samples, filled by prepare_body: the samples from the
   // longest to the shortest (nullptr: batch order)
   const int* by_size;
   // Pivots from outside the scored tokens (text-token pivots): the last Pe of the P pivots
@@ -111,7 +111,7 @@ __device__ __forceinline__ bool sample_processed(const Geo& g, int n) {
   return (long)n * g.keep_num >= (long)g.Pin * g.keep_den;
 }
 
-// Dense: arithmetic.  Ragged: k_prepare has validated the offsets and stored the
+// Dense: arithmetic.  Ragged: prepare_body has validated the offsets and stored the
 // per-sample budgets as differences of cu_keep (0 for a skipped sample).
 __device__ __forceinline__ Sample sample_of(const Geo& g, int b) {
   Sample s;

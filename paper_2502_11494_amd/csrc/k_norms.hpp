@@ -55,8 +55,8 @@ inline double l1_rel_bound(int dtype, int Dc) {
 // SPAN: the samples' rows are spans of C (Geo::span); packed row r belongs to the sample b
 // with cu[b] <= r < cu[b+1] and lives at row span[b] + (r - cu[b]) of C.  Rows of a sample that
 // is skipped are not read and their norms are left alone.
-// PREP: the first 8 blocks are not for rows: block 0 does k_prepare's work (this kernel needs
-// none of its results), which as a launch of its own took 4-5 us before this one.
+// PREP: the first 8 blocks are not for rows: block 0 fills the ragged offsets (prepare_body; this
+// kernel needs none of them), which as a launch of its own takes 4-5 us before this one.
 // L2SQ (bf16 only, when the rows are the hidden states themselves): also the squared
 // Euclidean norm of every row, which the score kernel divides by: piece sums in fp32 (see
 // piece_sq_sum_bf16), added in fp64 in a fixed lane-strided order plus butterfly, so the

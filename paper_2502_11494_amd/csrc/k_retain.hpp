@@ -10,9 +10,10 @@
 // rows, on (fp64 score, index).  The stages depend on each other, so the walk is
 // a serial chain of LDS round trips; to keep it short the kernel speculates:
 //   1. the stage lists are staged in LDS (in groups that fit);
-//   2. one wave walks the stages in fp32 order, 128 list entries at a time (ranks by
+//   2. one wave walks the stages in fp32 order, 128 or 256 list entries at a time (ranks by
 //      ballots), committing what that order says, while the other waves move ahead of
-//      it along the later stages' lists, past entries that are taken already;
+//      it along the later stages' lists, past entries that are taken already (long quotas or
+//      many stages: all waves together, kWideQuota);
 //   3. the waves then look at the stages in parallel: a stage whose last key taken and
 //      first key refused are
 //      within 2*tau is uncertain, and its candidates within 2*tau of the boundary
@@ -41,12 +42,13 @@ constexpr int kRetQ = 1024;      // band candidates awaiting an fp64 score
 constexpr int kRetInFlight = 4;  // 16-byte pieces per row and lane in flight in the fp64 re-scoring
 // Quotas from which the host takes the walk of all waves together (k_retain's WIDE): wave 0 alone
 // takes about 0.25 us per stage and 0.1 us more for every 64 entries beyond 128, all waves 0.5 us
-// whatever the length (8 stages of quota 130 on 1500 tokens: 8.4 against 5.5 us; 16 of quota 19 on
-// 2880 tokens: 5.1 against 8.5).  The helpers pass over some 64 taken entries per look, so with many
-// stages and lists that are nearly the same wave 0 meets longer and longer heads: beyond kWideSlots
-// slots in all the walk of all waves again (order and retained set of four samples of 9216 tokens, wave
-// 0 alone and all waves, equal lists: 32 pivots of quota 32 30.3 and 33.6 us, 64 of 32 89 and 78, 64 of
-// 63 215 and 127; independent lists 25.6 and 33.0, 45.8 and 62, 73 and 81).
+// whatever the length.  Order and retained set, wave 0 alone and all waves: 16 stages of quota 19 on
+// 2880 tokens 16.6 and 19.3 us, 8 of quota 63 15.7 and 15.9, independent lists and equal ones alike; 8 of
+// quota 70 15.7 and 16.0 (equal lists 16.3 and 16.1), of quota 100 15.9 and 16.4 (17.9 and 16.4).
+// The helpers pass over some 64 taken entries per look, so with many stages and lists that are nearly
+// the same wave 0 meets longer and longer heads: beyond kWideSlots slots in all the walk of all waves
+// again (four samples of 9216 tokens, equal lists: 32 pivots of quota 32 30.3 and 33.6 us, 64 of 32 89
+// and 78, 64 of 63 215 and 127; independent lists 25.6 and 33.0, 45.8 and 62, 73 and 81).
 constexpr int kWideQuota = 64, kWideSlots = 2048;
 constexpr unsigned char kOwnNone = 0xff, kOwnPivot = 0xfe;
 
