@@ -1039,7 +1039,10 @@ dart_status dart_compact_sequences(const dart_desc* desc, const int32_t* seq_cu,
   if (p.g.B == 0 || rows_bound <= 0) return DART_OK;
   SeqPos sp = {reinterpret_cast<const long long*>(pos), reinterpret_cast<long long*>(pos_out),
                (long)pos_plane_stride, (long)pos_out_plane_stride, pos_planes};
-  if (n_tensors == 0) {
+  long widest = 0;
+  for (int i = 0; i < n_tensors; ++i) widest = std::max(widest, (long)tensors[i].row_bytes);
+  const bool mapped = n_tensors == 0 || (p.g.B > kSeqMapped && widest > 1024);
+  if (mapped) {
     DART_LAUNCH(k_seq_row_map, dim3((unsigned)((rows_bound + 255) / 256)), dim3(256), 0, st, p.g,
                 seq_cu, seq_cu_out, keep, row_map, sp);
     DART_LAUNCH_CHECK();
@@ -1058,14 +1061,15 @@ dart_status dart_compact_sequences(const dart_desc* desc, const int32_t* seq_cu,
       longest = std::max(longest, (long)t.row_bytes);
     }
     // rows per wave (measured: see the kernel)
-    const int R = longest <= 1024 ? 4 : longest <= 2048 ? 2 : 1;
+    const int R = mapped ? 1 : longest <= 1024 ? 4 : longest <= 2048 ? 2 : 1;
     const dim3 grid((unsigned)round_up8((rows_bound + 4 * R - 1) / (4 * R)), cnt);
-#define DART_LAUNCH_SEQ(ROWS)                                                                    \
-  DART_LAUNCH(k_gather_rows<ROWS>, grid, dim3(256), 0, st, p.g, ops, i0 == 0, seq_cu, seq_cu_out, \
-              keep, row_map, sp)
-    if (R == 4) DART_LAUNCH_SEQ(4);
-    else if (R == 2) DART_LAUNCH_SEQ(2);
-    else DART_LAUNCH_SEQ(1);
+#define DART_LAUNCH_SEQ(ROWS, MAPPED)                                                            \
+  DART_LAUNCH((k_gather_rows<ROWS, MAPPED>), grid, dim3(256), 0, st, p.g, ops, i0 == 0, seq_cu,  \
+              seq_cu_out, keep, row_map, sp)
+    if (mapped) DART_LAUNCH_SEQ(1, true);
+    else if (R == 4) DART_LAUNCH_SEQ(4, false);
+    else if (R == 2) DART_LAUNCH_SEQ(2, false);
+    else DART_LAUNCH_SEQ(1, false);
 #undef DART_LAUNCH_SEQ
     DART_LAUNCH_CHECK();
   }

@@ -342,9 +342,9 @@ struct SeqRow {  // the sample of a row: the last one whose new offset is at mos
   }
 };
 
-// No tensors to move: the map and the position planes, a row per thread.  grid: ceil(rows_bound / 256)
-// blocks of 256.  (590 000 rows of 16384 sequences, the offsets' launch included: 62 us; 85 at best
-// with the rows dealt as in k_gather_rows.)
+// The map and the position planes, a row per thread, where there are no tensors to move or many
+// sequences (see k_gather_rows).  grid: ceil(rows_bound / 256) blocks of 256.  (590 000 rows of 16384
+// sequences, the offsets' launch included: 62 us; 85 at best with the rows dealt as in k_gather_rows.)
 __global__ __launch_bounds__(256) void k_seq_row_map(Geo g, const int* __restrict__ seq_cu,
                                                      const int* __restrict__ seq_cu_out,
                                                      const int* __restrict__ keep,
@@ -379,7 +379,12 @@ __global__ __launch_bounds__(256) void k_seq_row_map(Geo g, const int* __restric
 // 39, 44 us; rows of 1 KiB, 4096 sequences of 20 tokens: 97, 69, 64, 67, 71; of 2 KiB: 131, 126, 124,
 // 127, 125, but eight tensors of 2 KiB in 64 sequences 74, 75, 76, 84, 88; of 8 KiB, five tensors: 236,
 // -, 255, 269, -.  Rows beyond seq_cu_out[B] are left alone.
-template <int R>
+// MAPPED: k_seq_row_map has written the map and the positions.  Of more than kSeqMapped sequences with
+// rows of over 1 KiB: looking the sample up costs such batches more than that launch (four tensors of
+// 2080 bytes, 1000 sequences of 60 tokens 149 us, 155 without; 500 of 120 tokens 87 without, 83 before
+// the map and the gather were one launch; 300 of 200 tokens 66 without, 70 then).
+constexpr int kSeqMapped = 384;
+template <int R, bool MAPPED>
 __global__ __launch_bounds__(256) void k_gather_rows(Geo g, SeqOps ops, bool first,
                                                      const int* __restrict__ seq_cu,
                                                      const int* __restrict__ seq_cu_out,
@@ -410,10 +415,14 @@ __global__ __launch_bounds__(256) void k_gather_rows(Geo g, SeqOps ops, bool fir
   for (int u = 0; u < R; ++u) {
     src[u] = 0;
     if (r0 + u >= rows) continue;
+    if (MAPPED) {
+      src[u] = row_map[r0 + u];
+      continue;
+    }
     if (r0 + u >= q.end) find(r0 + u);
     src[u] = q.source(r0 + u, keep);
   }
-  if (o == 0 && first) {
+  if (!MAPPED && o == 0 && first) {
     const int u = lane % R;
     long mine = src[0];
 #pragma unroll

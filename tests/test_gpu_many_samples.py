@@ -63,8 +63,9 @@ def test_many_small_samples(B, n_tensors, spans):
 
 @pytest.mark.parametrize("B,elements,n_hi", [
     (70, 8, 30), (130, 512, 12), (4097, 512, 3), (70000, 8, 2),    # several rows per wave
-    (65, 1024, 9), (300, 1024, 3), (64, 520, 40), (4096, 520, 2),  # rows of up to 2 KiB
+    (65, 1024, 9), (300, 1024, 3), (64, 520, 40),                  # rows of up to 2 KiB
     (257, 1032, 5), (1, 3000, 50), (64, 2048, 1),                  # a row per wave
+    (384, 520, 4), (385, 520, 4), (9000, 1032, 2),                 # the map from a launch of its own
 ])
 def test_sequences_of_few_rows(B, elements, n_hi):
     """Rows of a wave in several sequences, empty sequences (more than 64 in a row), samples that keep
