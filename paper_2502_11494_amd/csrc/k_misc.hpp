@@ -263,23 +263,20 @@ __global__ __launch_bounds__(256) void k_gather(Geo g, int esz, const void* __re
                                                 void* __restrict__ Y,
                                                 long long* __restrict__ pos_out) {
   const int lane = threadIdx.x & 63;
-  const long r = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+  const long r = xcd_contiguous(blockIdx.x, gridDim.x) * 4 +
+                 __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int b;
   if (g.cu == nullptr) {
     if (r >= (long)g.B * g.K) return;
     b = (int)(r / g.K);
   } else {
     if (r >= g.cu_keep[g.B]) return;
-    int lo = 0, hi = g.B;
-    while (hi - lo > 1) {
-      int mid = (lo + hi) >> 1;
-      if (g.cu_keep[mid] <= r) lo = mid; else hi = mid;
-    }
-    b = lo;
+    b = -1;
   }
+  int kr = keep[r];  // (requested ahead of the search)
+  if (b < 0) b = last_at_most(g.cu_keep, g.B, (int)r);
   const int row0 = g.cu ? g.cu[b] : b * g.N;
   const int n = g.cu ? g.cu[b + 1] - row0 : g.N;
-  int kr = keep[r];
   kr = kr < 0 ? 0 : (kr < n ? kr : n - 1);  // a caller's bad index must not leave X
   const long src = (long)(g.span ? g.span[b] : row0) + kr;
   const u32x4* in = reinterpret_cast<const u32x4*>(static_cast<const unsigned char*>(X) +
@@ -397,19 +394,7 @@ __global__ __launch_bounds__(256) void k_gather_rows(Geo g, SeqOps ops, bool fir
   if (r0 >= rows) return;
   SeqRow q;
   q.end = 0;
-  auto find = [&](int r) {
-    int from = 0, left = g.B;
-    auto last_at_most = [&](int stride) {
-      const int d = lane * stride;
-      return 63 - __builtin_clzll(__ballot(d < left && seq_cu_out[from + (d < left ? d : 0)] <= r));
-    };
-    while (left > kWave) {
-      const int stride = (left + kWave - 1) / kWave, skip = last_at_most(stride) * stride;
-      from += skip;
-      left = left - skip < stride ? left - skip : stride;
-    }
-    q.load(g, seq_cu, seq_cu_out, __builtin_amdgcn_readfirstlane(from + last_at_most(1)));
-  };
+  auto find = [&](int r) { q.load(g, seq_cu, seq_cu_out, last_at_most(seq_cu_out, g.B, r)); };
   long src[R];
 #pragma unroll
   for (int u = 0; u < R; ++u) {

@@ -55,13 +55,8 @@ __device__ __forceinline__ bool locate_tile(const Geo& g, int tile, int& b, int&
     return b < g.B;
   }
   if (tile >= g.tile_start[g.B]) return false;
-  int lo = 0, hi = g.B;  // largest b with tile_start[b] <= tile
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (g.tile_start[mid] <= tile) lo = mid; else hi = mid;
-  }
-  b = lo;
-  tl = tile - g.tile_start[lo];
+  b = last_at_most(g.tile_start, g.B, tile);
+  tl = tile - g.tile_start[b];
   return true;
 }
 
@@ -69,41 +64,27 @@ __device__ __forceinline__ bool locate_tile(const Geo& g, int tile, int& b, int&
 // Output tile: lane holds column (lane&15) and rows 4*(lane>>4)..+3 of each 16x16 block.
 // With tokens as the A operand, rows are tokens and columns are pivots (Gram: columns are
 // tokens too, so |x_m|^2 sits in lane (m/4)*16+m, slot m%4).
-// COH: pl2 and l2sq were written, and S will be read, by other workgroups of this launch.
-template <int NB, bool COH = false>
-__device__ __forceinline__ void store_scores(const Geo& g, const Sample& sm, int b, int j0,
-                                             int lane, const double (&acc64)[NB][4],
-                                             const double (&gram64)[4], const double* pl2,
-                                             float* S, const double* l2sq) {
-  const int n = sm.n, P = g.P;
+// xnorm (the wave's 16 rows; nullptr: from the Gram diagonal) and pnorm [NB*16]: norms, in LDS.
+// put(nb, s): receives the lane's four scores against pivot 16 nb + (lane & 15).
+template <int NB, typename Put>
+__device__ __forceinline__ void finish_scores(int lane, const double (&acc64)[NB][4],
+                                              const double (&gram64)[4], const double* xnorm,
+                                              const double* pnorm, const Put& put) {
   const int g4 = lane >> 4;
   double xn[4];
-  if (l2sq != nullptr) {  // squared token norms from the norm pass (packed rows)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = j0 + g4 * 4 + r;
-      xn[r] = sqrt(ld_dev<COH>(&l2sq[sm.row0 + (j < n ? j : n - 1)]));
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) xn[r] = sqrt(__shfl(gram64[r], g4 * 16 + g4 * 4 + r, kWave));
-  }
-  float* Sb = S + (long)P * sm.row0;
+  for (int r = 0; r < 4; ++r)
+    xn[r] = xnorm ? xnorm[g4 * 4 + r] : sqrt(__shfl(gram64[r], g4 * 16 + g4 * 4 + r, kWave));
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    const int i = nb * 16 + (lane & 15);
-    if (i < P) {
-      const double pn = sqrt(ld_dev<COH>(&pl2[b * g.Ppad + i]));
+    const double pn = pnorm[nb * 16 + (lane & 15)];
+    f32x4v s;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int j = j0 + g4 * 4 + r;
-        if (j < n) {
-          const double den = pn * xn[r];
-          const double s = den > 0.0 ? acc64[nb][r] / den : 0.0;
-          st_dev<COH>(&Sb[(long)i * n + j], (float)s + 0.0f);
-        }
-      }
+    for (int r = 0; r < 4; ++r) {
+      const double den = pn * xn[r];
+      s[r] = (float)(den > 0.0 ? acc64[nb][r] / den : 0.0) + 0.0f;
     }
+    put(nb, s);
   }
 }
 
@@ -116,8 +97,8 @@ __device__ __forceinline__ void store_scores(const Geo& g, const Sample& sm, int
 // rows.
 constexpr int kKsCH = 128;  // elements of D per chunk
 
-// LDS: token chunks of the waves, pivot chunks of the KS groups (double buffered), the
-// pivots' row addresses.  Rows are padded by 16 bytes so that the 16-row x 64-byte fragment
+// LDS: token chunks of the waves, pivot chunks of the KS groups (double buffered), the norms of
+// the tile's rows and of the pivots.  Rows are padded by 16 bytes so that the 16-row x 64-byte fragment
 // reads hit distinct banks.  After the last chunk the groups' partial sums (kPartB bytes per
 // wave of the groups 1..KS-1) overlay a and, for the widest shapes, the start of p.
 template <int NB, int KS, int WAVES>
@@ -126,14 +107,15 @@ struct KSplitShared {
   static constexpr int kPartB = kWave * (NB * 4 + 4) * 8;
   unsigned char a[WAVES * 16 * kRowB];
   unsigned char p[KS * 2 * NB * 16 * kRowB];
-  const unsigned char* pivptr[NB * 16];
+  double pnorm[NB * 16], xnorm[16 * WAVES / KS];
   static_assert((WAVES - WAVES / KS) * kPartB <= WAVES * 16 * kRowB + KS * 2 * NB * 16 * kRowB,
                 "the groups' partial sums must fit in the token and pivot chunks they overlay");
 };
 
 // LDS bytes of a shape (host side: which shapes fit a compute unit).
 constexpr size_t ksplit_lds_bytes(int NB, int KS, int WAVES) {
-  return (size_t)(WAVES * 16 + KS * 2 * NB * 16) * (kKsCH * 2 + 16) + (size_t)NB * 16 * 8;
+  return (size_t)(WAVES * 16 + KS * 2 * NB * 16) * (kKsCH * 2 + 16) +
+         (size_t)(NB * 16 + 16 * WAVES / KS) * 8;
 }
 
 // Tile tl (16*WAVES/KS rows) of sample b.
@@ -160,8 +142,25 @@ __device__ __forceinline__ void score_tile_ksplit(const Geo& g, const Sample& sm
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int gk = wave / WG, wi = wave - gk * WG, tg = tid - gk * TG;
   const int n = sm.n, P = g.P;
-  if (tid < NB * 16) sh.pivptr[tid] = tid < P ? pivot_row<COH>(g, X, 2, sm, b, tid, piv) : nullptr;
-  __syncthreads();
+  // What the tile waits for is requested in the order of its need: the pivots' indices, the
+  // norms, the first rows, and, once the indices are there, the first pivot pieces.
+  // pivot pieces: piece id = tg + TG*k -> pivot row id/PC, piece id%PC (== lane%PC); padding
+  // slots read the sample's first row and are zeroed when the registers go to LDS
+  int pidx[LP];
+#pragma unroll
+  for (int k = 0; k < LP; ++k) {
+    const int i = (tg + TG * k) / PC;
+    pidx[k] = i < g.Pin ? ld_dev<COH>(&piv[b * P + i]) : 0;
+  }
+  constexpr int XR = XN ? ROWS : 0;  // the norms: a thread each, the rows' first
+  static_assert(ROWS + NB * 16 <= WAVES * kWave, "a norm per thread");
+  double l2 = 0.0;
+  if (tid < XR) {
+    const int j = tl * ROWS + tid;
+    l2 = ld_dev<COH>(&l2sq[sm.row0 + (j < n ? j : n - 1)]);
+  } else if (tid < XR + NB * 16) {
+    l2 = ld_dev<COH>(&pl2[b * g.Ppad + (tid - XR)]);
+  }
 
   const long rowbytes = g.ld * 2;
   const unsigned char* Xb = static_cast<const unsigned char*>(X) + (long)sm.xrow * rowbytes;
@@ -184,18 +183,46 @@ __device__ __forceinline__ void score_tile_ksplit(const Geo& g, const Sample& sm
   // With TAIL the lane's column offset is added per chunk instead: a piece past the end of
   // the row must re-read the row's first 16 bytes, not bytes behind a row shorter than a chunk
   const int tail_col = TAIL ? col16 * 16 : 0;
-  // pivot pieces: piece id = tg + TG*k -> pivot row id/PC, piece id%PC (== col16); padding
-  // slots read the sample's first row and are zeroed when the registers go to LDS
-  const unsigned char* pptr[LP];
+  u32x4 ra[LA], rp[LP];
+  auto chunk_offset = [&](int c) -> long {
+    const bool in = !TAIL || c * PC + col16 < pieces;
+    return in ? (long)c * (kKsCH * 2) + tail_col : 0;
+  };
+  auto load_rows = [&](long off) {
+#pragma unroll
+    for (int t = 0; t < LA; ++t)
+      ra[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aptr[t] + off));
+  };
+  const int c0 = my_cnt > 0 ? c_first : 0;
+  load_rows(chunk_offset(c0));
+  // (global pointers by type: through a generic one the loads are flat ones, which also count as
+  // LDS operations, so that the barrier and the LDS store of a chunk wait for every load in
+  // flight: 16 images of 576 tokens in tiles of 96 rows 23.4 us, 21.7 this way)
+  typedef const __attribute__((address_space(1))) unsigned char global_bytes;
+  typedef const __attribute__((address_space(1))) u32x4 global_piece;
+  global_bytes* pptr[LP];
   bool preal[LP], pmine[LP];
 #pragma unroll
   for (int k = 0; k < LP; ++k) {
-    const int pid = tg + TG * k;
+    const int pid = tg + TG * k, i = pid / PC;
     pmine[k] = pid < PP;
-    const unsigned char* pr = pmine[k] ? sh.pivptr[pid / PC] : nullptr;
-    preal[k] = pr != nullptr;
-    pptr[k] = (pr != nullptr ? pr : Xb) + (TAIL ? 0 : col16 * 16);
+    preal[k] = i < P;
+    const unsigned char* pr = Xb;
+    if (i < g.Pin) {
+      const int q = pidx[k] < 0 ? 0 : (pidx[k] < n ? pidx[k] : n - 1);
+      pr = Xb + (long)q * rowbytes;
+    } else if (i < P) {
+      pr = static_cast<const unsigned char*>(g.E) + ((long)b * g.Pe + (i - g.Pin)) * g.lde * 2;
+    }
+    pptr[k] = (global_bytes*)(pr + (TAIL ? 0 : col16 * 16));
   }
+  auto load_pivots = [&](long off) {
+#pragma unroll
+    for (int k = 0; k < LP; ++k) rp[k] = *(global_piece*)(pptr[k] + off);
+  };
+  load_pivots(chunk_offset(c0));
+  if (tid < XR) sh.xnorm[tid] = sqrt(l2);
+  else if (tid < XR + NB * 16) sh.pnorm[tid - XR] = sqrt(l2);
   unsigned char* la = sh.a + wave * (16 * kRowB);
   unsigned char* lpg = sh.p + gk * (2 * NB * 16 * kRowB);
   const int frag_off = (lane & 15) * kRowB + (lane >> 4) * 16;
@@ -209,19 +236,13 @@ __device__ __forceinline__ void score_tile_ksplit(const Geo& g, const Sample& sm
     for (int nb = 0; nb < NB; ++nb) acc64[nb][r] = 0.0;
   }
 
-  u32x4 ra[LA], rp[LP];
   // chunk c of this group (clamped to a chunk it owns, so that every load is unconditional
   // and in bounds; the surplus rounds of a group with fewer chunks compute nothing).  The
   // chunk's pivot pieces are requested just before its token pieces (vector loads return in
   // order), and nothing touches a load's result while it is in flight.
   auto load_chunk = [&](int c) {
-    const bool in = !TAIL || c * PC + col16 < pieces;
-    const long off = in ? (long)c * (kKsCH * 2) + tail_col : 0;
-#pragma unroll
-    for (int k = 0; k < LP; ++k) rp[k] = *reinterpret_cast<const u32x4*>(pptr[k] + off);
-#pragma unroll
-    for (int t = 0; t < LA; ++t)
-      ra[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aptr[t] + off));
+    load_pivots(chunk_offset(c));
+    load_rows(chunk_offset(c));
   };
   auto store_p = [&](int c, int buf) {
     const bool in = !TAIL || c * PC + col16 < pieces;
@@ -232,7 +253,6 @@ __device__ __forceinline__ void score_tile_ksplit(const Geo& g, const Sample& sm
                                   col16 * 16) = (in && preal[k]) ? rp[k] : zero;
   };
   const int c_last = my_cnt > 0 ? c_end - 1 : 0;
-  load_chunk(my_cnt > 0 ? c_first : 0);
   store_p(c_first, 0);
   for (int it = 0; it < max_cnt; ++it) {
     const int c = c_first + it;
@@ -305,8 +325,25 @@ __device__ __forceinline__ void score_tile_ksplit(const Geo& g, const Sample& sm
       }
     }
   }
-  if (gk == 0 && j0 < n)
-    store_scores<NB, COH>(g, sm, b, j0, lane, acc64, gram64, pl2, S, XN ? l2sq : nullptr);
+  if (gk != 0 || j0 >= n) return;
+  const double* xn = XN ? sh.xnorm + wi * 16 : nullptr;
+  const int r0 = (lane >> 4) * 4;
+  float* Sb = S + (long)P * sm.row0;
+  const int j = j0 + r0;
+  // four neighbouring scores in one store where that is aligned
+  const bool by4 = !COH && (n & 3) == 0 && (reinterpret_cast<uintptr_t>(Sb) & 15u) == 0;
+  finish_scores<NB>(lane, acc64, gram64, xn, sh.pnorm, [&](int nb, const f32x4v& s) {
+    const int i = nb * 16 + (lane & 15);
+    float* out = Sb + (long)i * n + j;
+    if (i >= P || j >= n) return;
+    if (by4) {
+      *reinterpret_cast<f32x4v*>(out) = s;
+      return;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (j + r < n) st_dev<COH>(out + r, s[r]);
+  });
 }
 
 // grid: the tiles of g.tile_rows = 16*WAVES/KS rows (dense: B*ceil(N/rows); ragged: an upper
