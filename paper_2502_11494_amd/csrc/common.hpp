@@ -329,6 +329,18 @@ __device__ __forceinline__ void piece_to_f64(const u32x4& v, double (&x)[8]) {
   }
 }
 
+// Adds a piece's |x| to a and, with L2, its squares to b, one element after the other.
+template <int DT, bool L2>
+__device__ __forceinline__ void add_piece_l1_l2(const u32x4& v, double& a, double& b) {
+  double x[8];
+  piece_to_f64<DT>(v, x);
+#pragma unroll
+  for (int e = 0; e < (DT == kBF16 ? 8 : 4); ++e) {
+    a += fabs(x[e]);
+    if (L2) b = fma(x[e], x[e], b);
+  }
+}
+
 template <int DT>
 __device__ __forceinline__ void row_l1_l2_f64(const void* row, int D, int lane, double& l1,
                                               double& l2) {
@@ -344,15 +356,7 @@ __device__ __forceinline__ void row_l1_l2_f64(const void* row, int D, int lane, 
       v[u] = t < pieces ? p[t] : zero;
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      double x[8];
-      piece_to_f64<DT>(v[u], x);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        a += fabs(x[e]);
-        b = fma(x[e], x[e], b);
-      }
-    }
+    for (int u = 0; u < 8; ++u) add_piece_l1_l2<DT, true>(v[u], a, b);
   }
   l1 = wave_sum(a);
   l2 = wave_sum(b);

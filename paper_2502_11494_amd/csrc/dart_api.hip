@@ -443,13 +443,13 @@ dart_status launch_prepare(Plan& p, void* ws, hipStream_t st, const int* seq_cu 
 constexpr int kPrepareInPass = 2048;
 dart_status launch_row_l1(Plan& p, const void* C, int Dc, long ldc, float* l1, bool keep_cached,
                           void* ws, hipStream_t st, double* l2sq = nullptr) {
-  constexpr int ROWS = 1;  // one row per wave measured best (more, shorter-lived waves)
+  double* l1d = at<double>(ws, p.o_scr_f64);
   const int rows = p.g.total_N;
   if (rows == 0) return launch_prepare(p, ws, st);
   const bool fill = p.g.cu != nullptr && p.g.B <= kPrepareInPass;
   if (!fill) DART_TRY(launch_prepare(p, ws, st));
   const PrepareArgs prep = prepare_args(p, ws);
-  const int blocks = (int)round_up8((rows + 4 * ROWS - 1) / (4 * ROWS)) + (fill ? kXcds : 0);
+  const int blocks = (int)round_up8((rows + 3) / 4) + (fill ? kXcds : 0);
   // The 256 MB memory-side cache serves the score kernel's second pass if this pass leaves
   // the rows there: measured 31 instead of 38 us on that kernel for 0.7 us more on this one
   // at 189 MB; at 264 MB this pass loses 7 us and that one gains 0.7; a loss for matrices
@@ -460,17 +460,17 @@ dart_status launch_row_l1(Plan& p, const void* C, int Dc, long ldc, float* l1, b
 #define DART_LAUNCH_L1_AS(DT, KEEP, SPAN, L2SQ)                                                  \
   do {                                                                                           \
     if (fill)                                                                                    \
-      DART_LAUNCH((k_row_l1<DT, ROWS, KEEP, SPAN, L2SQ, true>), dim3(blocks), dim3(256), 0, st,  \
-                  C, Dc, ldc, rows, l1, p.g, l2sq, prep);                                        \
+      DART_LAUNCH((k_row_l1<DT, KEEP, SPAN, L2SQ, true>), dim3(blocks), dim3(256), 0, st,        \
+                  C, Dc, ldc, rows, l1, l1d, p.g, l2sq, prep);                                   \
     else                                                                                         \
-      DART_LAUNCH((k_row_l1<DT, ROWS, KEEP, SPAN, L2SQ, false>), dim3(blocks), dim3(256), 0, st, \
-                  C, Dc, ldc, rows, l1, p.g, l2sq, prep);                                        \
+      DART_LAUNCH((k_row_l1<DT, KEEP, SPAN, L2SQ, false>), dim3(blocks), dim3(256), 0, st,       \
+                  C, Dc, ldc, rows, l1, l1d, p.g, l2sq, prep);                                   \
   } while (0)
 #define DART_LAUNCH_L1(DT)                                                                       \
   do {                                                                                           \
-    if (l2sq && p.g.span) DART_LAUNCH_L1_AS(kBF16, false, true, true);                           \
-    else if (l2sq && keep) DART_LAUNCH_L1_AS(kBF16, true, false, true);                          \
-    else if (l2sq) DART_LAUNCH_L1_AS(kBF16, false, false, true);                                 \
+    if (l2sq && p.g.span) DART_LAUNCH_L1_AS(DT, false, true, true);                              \
+    else if (l2sq && keep) DART_LAUNCH_L1_AS(DT, true, false, true);                             \
+    else if (l2sq) DART_LAUNCH_L1_AS(DT, false, false, true);                                    \
     else if (p.g.span) DART_LAUNCH_L1_AS(DT, false, true, false);                                \
     else if (keep) DART_LAUNCH_L1_AS(DT, true, false, false);                                    \
     else DART_LAUNCH_L1_AS(DT, false, false, false);                                             \
@@ -503,43 +503,42 @@ int values_per_thread(int max_n) {
     default: LAUNCH(16); break;                                                                  \
   }
 
-// l1_rel_err < 0: the norms are the norm pass's own (its rounding bound applies); otherwise the
-// caller's, good to that relative error.
+// l1_rel_err < 0: the norms are the norm pass's own (rounded fp64 norms, which lie in the scratch
+// area); otherwise the caller's, good to that relative error.  l2sq: the squared norms of the hidden
+// states' rows if the norm pass left them.  pl2: receives those of the pivots, or nullptr.
 dart_status launch_select_pivots(const Plan& p, const void* X, const void* C, int Dc, long ldc,
-                                 const float* l1, int* piv, void* ws, hipStream_t st,
-                                 double l1_rel_err = -1.0) {
-  // (the caller's bound plus the rounding of the threshold arithmetic itself, so that a bound
-  // of zero -- exact norms rounded to fp32 -- still holds every exact pivot)
-  const float tau = (float)(l1_rel_err < 0 ? l1_rel_bound(p.g.dtype, Dc) : l1_rel_err + 1.2e-7);
-  double* pl2 = at<double>(ws, p.o_pl2);
-  double* scr = at<double>(ws, p.o_scr_f64);
+                                 const float* l1, const double* l2sq, int* piv, double* pl2, void* ws,
+                                 hipStream_t st, double l1_rel_err = -1.0) {
+  // (the bound plus the rounding of the threshold arithmetic itself, so that exact norms rounded
+  // to fp32 still hold every exact pivot)
+  const float tau = (float)(std::max(l1_rel_err, 0.0) + 1.2e-7);
+  double* l1d = at<double>(ws, p.o_scr_f64);
   // 1024 threads: a 256-thread variant measured slower even for short samples
+#define DART_LAUNCH_PIVOTS_AS(DT, PER, EXACT)                                                    \
+  DART_LAUNCH((k_select_pivots<DT, PER, EXACT>), dim3(p.g.B), dim3(1024), 0, st, p.g, X, C, Dc,  \
+              ldc, l1, piv, pl2, l1d, l2sq, tau)
 #define DART_LAUNCH_PIVOTS(PER)                                                                  \
   do {                                                                                           \
-    if (p.g.dtype == kBF16)                                                                      \
-      DART_LAUNCH((k_select_pivots<kBF16, PER>), dim3(p.g.B), dim3(1024), 0, st,           \
-                  p.g, X, C, Dc, ldc, l1, piv, pl2, scr, tau);                                   \
-    else                                                                                         \
-      DART_LAUNCH((k_select_pivots<kF32, PER>), dim3(p.g.B), dim3(1024), 0, st,            \
-                  p.g, X, C, Dc, ldc, l1, piv, pl2, scr, tau);                                   \
+    if (p.g.dtype == kBF16 && l1_rel_err < 0) DART_LAUNCH_PIVOTS_AS(kBF16, PER, true);           \
+    else if (p.g.dtype == kBF16) DART_LAUNCH_PIVOTS_AS(kBF16, PER, false);                       \
+    else if (l1_rel_err < 0) DART_LAUNCH_PIVOTS_AS(kF32, PER, true);                             \
+    else DART_LAUNCH_PIVOTS_AS(kF32, PER, false);                                                \
   } while (0)
   DART_FOR_VALUES_PER_THREAD(values_per_thread(p.g.max_N), DART_LAUNCH_PIVOTS);
 #undef DART_LAUNCH_PIVOTS
+#undef DART_LAUNCH_PIVOTS_AS
   DART_LAUNCH_CHECK();
   return DART_OK;
 }
 
-// Norms of the pivots first..P-1; piv_mark (optional) receives the marks of the pivots from
-// outside the samples.
-dart_status launch_pivot_norms(const Plan& p, const void* X, const int* piv, int first,
-                               int* piv_mark, void* ws, hipStream_t st) {
+// Norms of all pivots; piv_mark (optional) receives the marks of the pivots from outside the samples.
+dart_status launch_pivot_norms(const Plan& p, const void* X, const int* piv, int* piv_mark, void* ws,
+                               hipStream_t st) {
   double* pl2 = at<double>(ws, p.o_pl2);
   if (p.g.dtype == kBF16)
-    DART_LAUNCH((k_pivot_norms<kBF16>), dim3(p.g.B), dim3(1024), 0, st, p.g, X, piv, first,
-                pl2, piv_mark);
+    DART_LAUNCH((k_pivot_norms<kBF16>), dim3(p.g.B), dim3(1024), 0, st, p.g, X, piv, pl2, piv_mark);
   else
-    DART_LAUNCH((k_pivot_norms<kF32>), dim3(p.g.B), dim3(1024), 0, st, p.g, X, piv, first,
-                pl2, piv_mark);
+    DART_LAUNCH((k_pivot_norms<kF32>), dim3(p.g.B), dim3(1024), 0, st, p.g, X, piv, pl2, piv_mark);
   DART_LAUNCH_CHECK();
   return DART_OK;
 }
@@ -673,7 +672,7 @@ dart_status launch_order(const Plan& p, const float* S, void* ws, hipStream_t st
 dart_status launch_retain(const Plan& p, const float* S, const int* piv, const void* X, int* keep,
                           int* cu_keep, void* ws, hipStream_t st, bool pivot_norms_ready) {
   const double* pl2 = pivot_norms_ready ? at<double>(ws, p.o_pl2) : nullptr;
-  const float two_tau = (float)(2.0 * 1.01 * score_abs_bound(p.g.dtype, p.norms_given));
+  const float two_tau = (float)(2.0 * 1.01 * score_abs_bound(p.g.dtype, p.norms_given ? kNormsF64 : kNormsGram));
   const unsigned long long* lists = at<unsigned long long>(ws, p.o_lists);
   double* scr_f64 = at<double>(ws, p.o_scr_f64);
   if (p.g.score_mode != 0) {  // one threshold for all pivots: no stage lists
@@ -757,7 +756,7 @@ dart_status launch_fused(Plan& p, const void* X, const int64_t* pos, void* Y, in
   a.gather_start = gstart;
   a.status = at<int>(ws, p.o_status);
   a.tau_l1 = (float)l1_rel_bound(p.g.dtype, p.g.D);
-  a.two_tau = (float)(2.0 * 1.01 * score_abs_bound(p.g.dtype, true));
+  a.two_tau = (float)(2.0 * 1.01 * score_abs_bound(p.g.dtype, kNormsF32Squares));
   a.keep_cached = (double)p.g.total_N * p.g.ld * p.esz <= 224e6 ? 1 : 0;
   a.spin_limit = 1 << 20;
   const dim3 grid(compute_units()), block(kFuThreads);
@@ -840,7 +839,7 @@ dart_status reduce_impl(const dart_desc* desc, const void* X, const void* crit, 
   // norm pass 1-3 % up to 264 MB and 5 % at 1.7 GB, where it runs at the memory's speed and
   // the gain of the score pass does not pay for it; the tighter error bound also saves the
   // retained-set kernel 10 % on near-duplicate video frames)
-  p.norms_given = p.g.mode != kGiven && p.g.Pin > 0 && crit == X && p.g.dtype == kBF16 &&
+  p.norms_given = p.g.mode != kGiven && p.g.Pin > 0 && crit == X &&
                   !l1_given && (double)p.g.total_N * p.g.ld * p.esz <= 1e9;
   // (the one-launch path computes its own norms: not for profiled calls or the caller's norms)
   const bool fused = p.fusable && crit == X && events == nullptr && !l1_given && p.g.total_N > 0 &&
@@ -860,18 +859,20 @@ dart_status reduce_impl(const dart_desc* desc, const void* X, const void* crit, 
       DART_LAUNCH_CHECK();
     }
     stage(1);
-    DART_TRY(launch_pivot_norms(p, X, piv, 0, piv, ws, st));
+    DART_TRY(launch_pivot_norms(p, X, piv, piv, ws, st));
   } else {
     // pivots chosen among the tokens (none if all of them come from outside) ...
     if (norm_pass)
       DART_TRY(launch_row_l1(p, crit, crit_D, crit_ld, l1, crit == X, ws, st,
                              p.norms_given ? at<double>(ws, p.o_l2) : nullptr));
     stage(1);
+    // ... with the norms and marks of those from outside
     if (p.g.Pin > 0)
-      DART_TRY(launch_select_pivots(p, X, crit, crit_D, crit_ld, l1_given ? l1_given : l1, piv, ws,
-                                    st, l1_given ? l1_rel_err : -1.0));
-    // ... then the norms and marks of those from outside
-    if (p.g.Pe > 0) DART_TRY(launch_pivot_norms(p, X, piv, p.g.Pin, piv, ws, st));
+      DART_TRY(launch_select_pivots(p, X, crit, crit_D, crit_ld, l1_given ? l1_given : l1,
+                                    p.norms_given ? at<double>(ws, p.o_l2) : nullptr, piv,
+                                    at<double>(ws, p.o_pl2), ws, st, l1_given ? l1_rel_err : -1.0));
+    else
+      DART_TRY(launch_pivot_norms(p, X, piv, piv, ws, st));
   }
   stage(2);
   DART_TRY(launch_scores(p, X, piv, S, ws, st));
@@ -953,9 +954,9 @@ dart_status dart_select_pivots(const dart_desc* desc, const void* X, const void*
     DART_TRY(launch_random_pivots(p, piv, st));
   } else if (norm_pass) {
     DART_TRY(launch_row_l1(p, crit, crit_D, crit_ld, l1, false, ws, st));
-    DART_TRY(launch_select_pivots(p, X, crit, crit_D, crit_ld, l1, piv, ws, st));
+    DART_TRY(launch_select_pivots(p, X, crit, crit_D, crit_ld, l1, nullptr, piv, nullptr, ws, st));
   }
-  if (p.g.Pe > 0) DART_TRY(launch_pivot_norms(p, X, piv, p.g.Pin, piv, ws, st));
+  if (p.g.Pe > 0 && !norm_pass) DART_TRY(launch_pivot_norms(p, X, piv, piv, ws, st));  // (their marks)
   return DART_OK;
 }
 
@@ -971,7 +972,7 @@ dart_status dart_duplication_scores(const dart_desc* desc, const void* X, const 
   hipStream_t st = static_cast<hipStream_t>(stream);
   DART_TRY(launch_prepare(p, ws, st));
   DART_TRY(launch_given_status(p, piv, ws, st));
-  DART_TRY(launch_pivot_norms(p, X, piv, 0, nullptr, ws, st));
+  DART_TRY(launch_pivot_norms(p, X, piv, nullptr, ws, st));
   return launch_scores(p, X, piv, S, ws, st);
 }
 

@@ -344,8 +344,8 @@ __device__ __attribute__((noinline)) void fused_do_norm(int b_in, int i_in) {
 __device__ __attribute__((noinline)) void fused_do_select(int b_in, int i_in) {
   DART_FUSED_PARAMS(b_in, i_in);
   DART_FUSED_PREFETCH_BEGIN();
-  select_pivots_body<kBF16, true, kSelPerThread>(g, b, a.X, a.X, g.D, g.ld, a.l1, a.piv, a.pl2,
-                                                 a.scr, a.tau_l1, fu_sh.piv);
+  select_pivots_body<kBF16, true, kSelPerThread, false>(g, b, a.X, a.X, g.D, g.ld, a.l1, a.piv,
+                                                        a.pl2, a.scr, nullptr, a.tau_l1, fu_sh.piv);
   stores_done();
   DART_FUSED_PREFETCH_END();
 }

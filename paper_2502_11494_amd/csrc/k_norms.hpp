@@ -7,6 +7,7 @@
 
 namespace dart {
 
+// (fp32 sums of a piece: the one-launch kernel's)
 // Sum of |x| over one 16-byte piece, as a fixed pairwise tree (3 roundings for
 // 8 bf16 values, 2 for 4 floats).  |x| of a bf16 widened to fp32 is exact.
 template <int DT>
@@ -34,8 +35,8 @@ __device__ __forceinline__ float piece_sq_sum_bf16(const u32x4& v) {
   return (a0 + a1) + (a2 + a3);
 }
 
-// Relative bound on |fp32 norm - exact norm| for k_row_l1: piece tree, then one
-// add per piece a lane owns, then the 6-step butterfly, each rounding at most
+// Relative bound on |fp32 norm - exact norm| for norms summed in fp32 (the one-launch kernel):
+// piece tree, then one add per piece a lane owns, then the 6-step butterfly, each rounding at most
 // 2^-24 relative on a sum of non-negative terms.
 inline double l1_rel_bound(int dtype, int Dc) {
   int per_piece = dtype == kBF16 ? 8 : 4;
@@ -45,10 +46,14 @@ inline double l1_rel_bound(int dtype, int Dc) {
   return (double)(tree + chain + 6 + 1) * 5.9604644775390625e-08;
 }
 
-// grid: ceil(rows / (4 * ROWS)) blocks of 256 threads, rounded up to a multiple of 8; wave w
-// of the grid (after xcd_contiguous) owns
-// rows [w*ROWS, (w+1)*ROWS).  Per row, lane l reads the pieces l, l+64, ... so a
-// wave's loads are 1 KiB contiguous; 8*ROWS loads are in flight per lane.
+// grid: ceil(rows / 4) blocks of 256 threads, rounded up to a multiple of 8; wave w of the grid
+// (after xcd_contiguous) owns row w.  Lane l reads the pieces l, l+64, ... so a
+// wave's loads are 1 KiB contiguous; 8 loads are in flight per lane.
+// The sums run in fp64, in the order of row_l1_l2_f64 (a function of the row's bytes): pivot selection
+// ranks by them without reading a row again, which was half of its time (selection of multi-crop 8.4
+// us, 5.5 now, of video 13.5 and 6.9), and the pass has the vector ALU to spare: a row of 4096 takes some
+// 1900 of the 2900 cycles in which the memory delivers one to every SIMD (the pass on multi-crop 32.6 us
+// with fp32 sums, 33.9).  l1 gets the norms rounded to fp32.
 // KEEP: ordinary loads, which leave the rows in the memory-side cache for the score
 // kernel's second pass (worth it only if the whole matrix fits there); otherwise
 // streaming (non-temporal) loads, which read faster.
@@ -57,13 +62,12 @@ inline double l1_rel_bound(int dtype, int Dc) {
 // is skipped are not read and their norms are left alone.
 // PREP: the first 8 blocks are not for rows: block 0 fills the ragged offsets (prepare_body; this
 // kernel needs none of them), which as a launch of its own takes 4-5 us before this one.
-// L2SQ (bf16 only, when the rows are the hidden states themselves): also the squared
-// Euclidean norm of every row, which the score kernel divides by: piece sums in fp32 (see
-// piece_sq_sum_bf16), added in fp64 in a fixed lane-strided order plus butterfly, so the
-// result is a function of the row's bytes with a relative error of at most 3.5 * 2^-24.
-template <int DT, int ROWS, bool KEEP, bool SPAN, bool L2SQ, bool PREP>
+// L2SQ (when the rows are the hidden states themselves): also the squared Euclidean norm of every
+// row, which the score kernel divides by and the pivots' norms are taken from.
+template <int DT, bool KEEP, bool SPAN, bool L2SQ, bool PREP>
 __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int Dc, long ldc,
-                                                int rows, float* __restrict__ l1, Geo g,
+                                                int rows, float* __restrict__ l1,
+                                                double* __restrict__ l1d, Geo g,
                                                 double* __restrict__ l2sq, PrepareArgs prep) {
   if (PREP && blockIdx.x < kXcds) {
     if (blockIdx.x == 0) prepare_body<256>(g, prep);
@@ -73,65 +77,44 @@ __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int 
   const int lane = threadIdx.x & 63;
   // (ordinary loads: the plain order measured faster; streaming loads: a die per eighth)
   const long blk = KEEP ? (long)bid : xcd_contiguous(bid, blocks);
-  const long wave = blk * 4 + (threadIdx.x >> 6);
+  const long row = blk * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
   const int esz = DT == kBF16 ? 2 : 4;
   const int pieces = Dc * esz / 16;
-  const long rowbytes = ldc * esz;
-  const unsigned char* base = static_cast<const unsigned char*>(C);
   const u32x4 zero = {0u, 0u, 0u, 0u};
-
-  float acc[ROWS];
-  double sq[ROWS];
-  const unsigned char* rp[ROWS];
-  bool live[ROWS];
-#pragma unroll
-  for (int r = 0; r < ROWS; ++r) {
-    long row = wave * ROWS + r;
-    live[r] = row < rows;
-    long crow = live[r] ? row : 0;
-    if (SPAN && live[r]) {
-      int lo = 0, hi = g.B;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (g.cu[mid] <= row) lo = mid; else hi = mid;
-      }
-      // (the offsets may be anything here: prepare_body checks them while this runs)
-      const long at = row - g.cu[lo], n = (long)g.cu[lo + 1] - g.cu[lo], s0 = g.span[lo];
-      live[r] = at >= 0 && at < n && n <= g.max_N && sample_processed(g, (int)n) && s0 >= 0 &&
-                s0 + n <= (long)g.x_rows;
-      crow = live[r] ? s0 + at : 0;
+  long crow = row;
+  if (SPAN) {
+    int lo = 0, hi = g.B;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (g.cu[mid] <= row) lo = mid; else hi = mid;
     }
-    rp[r] = base + crow * rowbytes;
-    acc[r] = 0.f;
-    sq[r] = 0.0;
+    // (the offsets may be anything here: prepare_body checks them while this runs)
+    const long at = row - g.cu[lo], n = (long)g.cu[lo + 1] - g.cu[lo], s0 = g.span[lo];
+    if (at < 0 || at >= n || n > g.max_N || !sample_processed(g, (int)n) || s0 < 0 ||
+        s0 + n > (long)g.x_rows)
+      return;
+    crow = s0 + at;
   }
+  const u32x4* rp = reinterpret_cast<const u32x4*>(static_cast<const unsigned char*>(C) + crow * ldc * esz);
+  double a = 0.0, b = 0.0;
   for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
-    u32x4 v[ROWS][8];
+    u32x4 v[8];
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        int t = t0 + u * kWave + lane;
-        const u32x4* src = reinterpret_cast<const u32x4*>(rp[r]) + t;
-        if (live[r] && t < pieces) v[r][u] = KEEP ? *src : __builtin_nontemporal_load(src);
-        else v[r][u] = zero;
-      }
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        acc[r] += piece_abs_sum<DT>(v[r][u]);
-        if (L2SQ) sq[r] += (double)piece_sq_sum_bf16(v[r][u]);
-      }
-  }
-#pragma unroll
-  for (int r = 0; r < ROWS; ++r) {
-    float s = wave_sum(acc[r]);
-    if (lane == 0 && live[r]) l1[wave * ROWS + r] = s;
-    if (L2SQ) {
-      const double q = wave_sum(sq[r]);
-      if (lane == 0 && live[r]) l2sq[wave * ROWS + r] = q;
+    for (int u = 0; u < 8; ++u) {
+      const int t = t0 + u * kWave + lane;
+      if (t < pieces) v[u] = KEEP ? rp[t] : __builtin_nontemporal_load(rp + t);
+      else v[u] = zero;
     }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) add_piece_l1_l2<DT, L2SQ>(v[u], a, b);
+  }
+  a = wave_sum(a);
+  if (L2SQ) b = wave_sum(b);
+  if (lane == 0) {
+    l1[row] = (float)a;
+    l1d[row] = a;
+    if (L2SQ) l2sq[row] = b;
   }
 }
 

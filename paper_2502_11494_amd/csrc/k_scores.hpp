@@ -37,13 +37,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // same kind of sum and enters through a square root (half the relative error).
 // Two more units for rounding the quotient to fp32 and the fp64 steps.
 // fp32 inputs: all fp64, only the final rounding to fp32 counts.
-// norms_given: the token norms come from k_row_l1 (relative error 3.5 * 2^-24 on the square,
-// half of it on the norm; 2 units are counted) instead of the Gram diagonal.
+// The token norms may also come from elsewhere: from the norm pass, in fp64, or from the one-launch
+// kernel's fp32 squares (relative error 3.5 * 2^-24 on the square, half of it on the norm; 2 units).
 constexpr double kMfmaUlps = 16.0;
-inline double score_abs_bound(int dtype, bool norms_given = false) {
+enum TokenNorms { kNormsGram, kNormsF64, kNormsF32Squares };
+inline double score_abs_bound(int dtype, TokenNorms norms = kNormsGram) {
   const double u = 5.9604644775390625e-08;  // 2^-24
   if (dtype != kBF16) return 4.0 * u;
-  return (norms_given ? kMfmaUlps + 2.0 + 2.0 : kMfmaUlps * 1.5 + 2.0) * u;
+  return (norms == kNormsGram ? kMfmaUlps * 1.5 + 2.0
+                              : kMfmaUlps + 2.0 + (norms == kNormsF64 ? 0.0 : 2.0)) * u;
 }
 
 // Tile -> (sample, tile inside the sample).  Returns false for surplus blocks.
