@@ -252,6 +252,24 @@ __global__ __launch_bounds__(1024) void k_pivot_norms(Geo g, const void* __restr
   }
 }
 
+// A row by one wave: 16 bytes per lane, 1 KiB per access, eight accesses in flight.
+__device__ __forceinline__ void copy_row(const u32x4* in, u32x4* out, int pieces, int lane) {
+  for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
+    u32x4 v[8];
+    load_pieces<8, true>(v, in, t0, pieces, lane);
+    if (t0 + 8 * kWave <= pieces) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) out[t0 + u * kWave + lane] = v[u];
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int t = t0 + u * kWave + lane;
+        if (t < pieces) out[t] = v[u];
+      }
+    }
+  }
+}
+
 // Compaction: one wave per retained row.  grid: ceil(rows_bound / 4) blocks of 256, rounded up
 // to a multiple of 8 (xcd_contiguous).
 // Y rows are packed (stride D); copies are 16 bytes per lane, 1 KiB per wave access.
@@ -283,19 +301,7 @@ __global__ __launch_bounds__(256) void k_gather(Geo g, int esz, const void* __re
                                                    src * g.ld * esz);
   u32x4* out = reinterpret_cast<u32x4*>(static_cast<unsigned char*>(Y) + r * (long)g.D * esz);
   const int pieces = g.D * esz / 16;
-  for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
-    u32x4 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      int t = t0 + u * kWave + lane;
-      v[u] = t < pieces ? __builtin_nontemporal_load(in + t) : u32x4{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      int t = t0 + u * kWave + lane;
-      if (t < pieces) out[t] = v[u];
-    }
-  }
+  copy_row(in, out, pieces, lane);
   if (pos && lane == 0) pos_out[r] = pos[src];
 }
 
@@ -440,21 +446,7 @@ __global__ __launch_bounds__(256) void k_gather_rows(Geo g, SeqOps ops, bool fir
       }
     return;
   }
-  const u32x4* in = row_in(0);
-  u32x4* out = row_out(0);
-  for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
-    u32x4 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = t0 + u * kWave + lane;
-      v[u] = t < pieces ? __builtin_nontemporal_load(in + t) : zero;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = t0 + u * kWave + lane;
-      if (t < pieces) out[t] = v[u];
-    }
-  }
+  copy_row(row_in(0), row_out(0), pieces, lane);
 }
 
 }  // namespace dart

@@ -81,7 +81,6 @@ __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int 
   if (row >= rows) return;
   const int esz = DT == kBF16 ? 2 : 4;
   const int pieces = Dc * esz / 16;
-  const u32x4 zero = {0u, 0u, 0u, 0u};
   long crow = row;
   if (SPAN) {
     int lo = 0, hi = g.B;
@@ -100,12 +99,7 @@ __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int 
   double a = 0.0, b = 0.0;
   for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
     u32x4 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = t0 + u * kWave + lane;
-      if (t < pieces) v[u] = KEEP ? rp[t] : __builtin_nontemporal_load(rp + t);
-      else v[u] = zero;
-    }
+    load_pieces<8, !KEEP>(v, rp, t0, pieces, lane);
 #pragma unroll
     for (int u = 0; u < 8; ++u) add_piece_l1_l2<DT, L2SQ>(v[u], a, b);
   }
