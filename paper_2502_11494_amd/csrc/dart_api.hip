@@ -99,6 +99,10 @@ constexpr size_t kKsLdsLimit = 150 * 1024;  // of the 160 KB of a compute unit
 // memory-side cache.
 KsChoice choose_score_tiles(const Geo& g, int units, bool first_read) {
   const int NB = g.Ppad / 16;
+  // Thousands of tiles spread evenly by themselves, and short ones end together (whole call on 292 000
+  // packed rows of 3584: 808 us with 64-row tiles, 827 with the model's 144; 131 000 rows, score pass: 154
+  // and 162).
+  if (NB == 1 && g.total_N >= 512L * units) return {4, 1};
   const double rowbytes = (double)g.D * 2;
   const int chunks = (g.D + kKsCH - 1) / kKsCH;
   struct Cost {
@@ -136,19 +140,27 @@ KsChoice choose_score_tiles(const Geo& g, int units, bool first_read) {
   // launch's own events): where a wave's chain of chunks matters, four groups of waves per
   // tile beat two or three of the same tile height (32 rows: 8 waves in 4 groups 15.9 us
   // against 17.4 for 6 in 3 on 32 samples of 256 tokens; 48 rows: 12 in 4 groups 15.2 against
-  // 17.2 for 6 in 2 on sixteen 576-token images, 22.1 against 25.2 at a hidden size of 5120) ...
+  // 17.2 for 6 in 2 on sixteen 576-token images, 22.1 against 25.2 at a hidden size of 5120; whole call
+  // with the present score pass 55.8 and 57.4, 67.8 and 69.8) ...
   const int R_best = 16 * best.waves / best.split;
   if (best.split >= 2 && best.split < 4 && (R_best == 32 || R_best == 48)) {
     const KsChoice four = {R_best / 4, 4};
     if (cost(four).fits) return four;
   }
+  // ... a unit that gets one tile of at most 5 waves has too few loads in flight: two groups on a tile
+  // of about the same height (score pass of eight samples of 2100 tokens 20.8 -> 19.5 us, first read 28.0
+  // -> 24.2; whole call on eight spans, 15249 rows of 3584: 105.7 -> 99.7) ...
+  if (best.split == 1 && best.waves <= 5 && cost(best).rows_busiest == R_best) {
+    const KsChoice two = {best.waves == 3 ? 6 : best.waves == 4 ? 8 : 12, 2};
+    if (cost(two).fits) return two;
+  }
   // ... and on a first read of X they also beat the single group on small dense batches as
   // long as no compute unit gets more rows than with the model's pick (eight samples of 2880
-  // tokens: 34.7-35.5 us against 38.6 for 6 waves in one group; with 32 pivots or thousands
-  // of tiles the single group stays ahead: 45.6 against 59.5, 276 against 324 us).
+  // tokens: 32.8-34.4 us against 39.1 for 6 waves in one group; five of 5000 tokens in tiles of 128
+  // rows: 36.2 against 32.2; with 32 pivots the single group stays ahead too: 45.6 against 59.5 us).
   if (first_read && best.split == 1 && NB == 1 && g.cu == nullptr) {
     const Cost picked = cost(best);
-    if (picked.rows_busiest <= 128) {
+    if (picked.rows_busiest <= 96) {
       // (of the two, the one that loads the busiest unit less; equal: the 32-row tiles, two
       // workgroups of which share a unit: 34.7 against 35.5-36.3 us on the headline batch)
       KsChoice alt = best;
