@@ -376,6 +376,20 @@ __device__ __forceinline__ void add_piece_l1_l2(const u32x4& v, double& a, doubl
   }
 }
 
+// The same for the N pieces of load_pieces; runs past the row's end are left out.
+template <int DT, bool L2, int N>
+__device__ __forceinline__ void add_pieces_l1_l2(const u32x4 (&v)[N], int t0, int pieces, double& a,
+                                                 double& b) {
+  if (t0 + N * kWave <= pieces) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) add_piece_l1_l2<DT, L2>(v[u], a, b);
+  } else {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (t0 + u * kWave < pieces) add_piece_l1_l2<DT, L2>(v[u], a, b);
+  }
+}
+
 template <int DT>
 __device__ __forceinline__ void row_l1_l2_f64(const void* row, int D, int lane, double& l1,
                                               double& l2) {
@@ -385,8 +399,7 @@ __device__ __forceinline__ void row_l1_l2_f64(const void* row, int D, int lane, 
   for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
     u32x4 v[8];
     load_pieces<8, false>(v, p, t0, pieces, lane);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) add_piece_l1_l2<DT, true>(v[u], a, b);
+    add_pieces_l1_l2<DT, true>(v, t0, pieces, a, b);
   }
   l1 = wave_sum(a);
   l2 = wave_sum(b);

@@ -453,6 +453,9 @@ dart_status launch_prepare(Plan& p, void* ws, hipStream_t st, const int* seq_cu 
 // 64 elements, in the pass and with the launch: 1000 samples 13.4 and 16.3 us, 4096 34.3 and 34.5, 8192
 // 60.6 and 58.2, 65536 485 and 400).
 constexpr int kPrepareInPass = 2048;
+// Rows of at most 64 pieces: eight to a wave (156 000 rows of 512 bytes: 40 us
+// with one, 17).
+constexpr long kShortRowBytes = kWave * 16;
 dart_status launch_row_l1(Plan& p, const void* C, int Dc, long ldc, float* l1, bool keep_cached,
                           void* ws, hipStream_t st, double* l2sq = nullptr) {
   double* l1d = at<double>(ws, p.o_scr_f64);
@@ -461,6 +464,20 @@ dart_status launch_row_l1(Plan& p, const void* C, int Dc, long ldc, float* l1, b
   const bool fill = p.g.cu != nullptr && p.g.B <= kPrepareInPass;
   if (!fill) DART_TRY(launch_prepare(p, ws, st));
   const PrepareArgs prep = prepare_args(p, ws);
+  if (l2sq == nullptr && p.g.span == nullptr && (long)Dc * p.esz <= kShortRowBytes) {
+    const dim3 grid((unsigned)round_up8((rows + 31) / 32) + (fill ? kXcds : 0));
+#define DART_LAUNCH_SHORT(DT, PREP)                                                              \
+  DART_LAUNCH((k_short_row_l1<DT, 8, PREP>), grid, dim3(256), 0, st, C, Dc, ldc, rows, l1, l1d,  \
+              p.g, prep)
+    if (p.g.dtype == kBF16) {
+      if (fill) DART_LAUNCH_SHORT(kBF16, true); else DART_LAUNCH_SHORT(kBF16, false);
+    } else {
+      if (fill) DART_LAUNCH_SHORT(kF32, true); else DART_LAUNCH_SHORT(kF32, false);
+    }
+#undef DART_LAUNCH_SHORT
+    DART_LAUNCH_CHECK();
+    return DART_OK;
+  }
   const int blocks = (int)round_up8((rows + 3) / 4) + (fill ? kXcds : 0);
   // The 256 MB memory-side cache serves the score kernel's second pass if this pass leaves
   // the rows there: measured 31 instead of 38 us on that kernel for 0.7 us more on this one

@@ -100,8 +100,7 @@ __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int 
   for (int t0 = 0; t0 < pieces; t0 += kWave * 8) {
     u32x4 v[8];
     load_pieces<8, !KEEP>(v, rp, t0, pieces, lane);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) add_piece_l1_l2<DT, L2SQ>(v[u], a, b);
+    add_pieces_l1_l2<DT, L2SQ>(v, t0, pieces, a, b);
   }
   a = wave_sum(a);
   if (L2SQ) b = wave_sum(b);
@@ -109,6 +108,65 @@ __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int 
     l1[row] = (float)a;
     l1d[row] = a;
     if (L2SQ) l2sq[row] = b;
+  }
+}
+
+// Short rows (at most 64 pieces, criterion rows as a rule): R rows per wave, a load of each in flight,
+// because the reduction and the wave's start cost more than such a row takes to read.
+// The R sums are reduced together: lanes exchange half of their rows at every step, so that it takes
+// R + 2 additions instead of 6 R; a row's tree is the same in every place.  PREP: as above.
+template <int DT, int R, bool PREP>
+__global__ __launch_bounds__(256) void k_short_row_l1(const void* __restrict__ C, int Dc, long ldc,
+                                                      int rows, float* __restrict__ l1,
+                                                      double* __restrict__ l1d, Geo g,
+                                                      PrepareArgs prep) {
+  static_assert(R == 8, "three halvings leave a row per eight lanes");
+  if (PREP && blockIdx.x < kXcds) {
+    if (blockIdx.x == 0) prepare_body<256>(g, prep);
+    return;
+  }
+  const unsigned bid = blockIdx.x - (PREP ? kXcds : 0), blocks = gridDim.x - (PREP ? kXcds : 0);
+  const int lane = threadIdx.x & 63;
+  const long row0 = (xcd_contiguous(bid, blocks) * 4 + (threadIdx.x >> 6)) * R;
+  if (row0 >= rows) return;
+  const int esz = DT == kBF16 ? 2 : 4;
+  const int pieces = Dc * esz / 16;
+  const bool in = lane < pieces;
+  u32x4 v[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const long row = row0 + r < rows ? row0 + r : rows - 1;
+    v[r] = __builtin_nontemporal_load(
+        reinterpret_cast<const u32x4*>(static_cast<const unsigned char*>(C) + row * ldc * esz) + (in ? lane : 0));
+  }
+  double a[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    double unused = 0.0;
+    a[r] = 0.0;
+    add_piece_l1_l2<DT, false>(v[r], a[r], unused);
+    a[r] = in ? a[r] : 0.0;
+  }
+  // lanes 32.. go on with rows 4..7, then the lanes with bit 16 with the upper two, bit 8 the upper one
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    const double keep = lane & 32 ? a[4 + h] : a[h], give = lane & 32 ? a[h] : a[4 + h];
+    a[h] = keep + lane_xor<32>(give, lane);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const double keep = lane & 16 ? a[2 + h] : a[h], give = lane & 16 ? a[h] : a[2 + h];
+    a[h] = keep + lane_xor<16>(give, lane);
+  }
+  const double keep = lane & 8 ? a[1] : a[0], give = lane & 8 ? a[0] : a[1];
+  double s = keep + lane_xor<8>(give, lane);
+  s += lane_xor<4>(s, lane);
+  s += lane_xor<2>(s, lane);
+  s += lane_xor<1>(s, lane);
+  const long row = row0 + (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+  if ((lane & 7) == 0 && row < rows) {
+    l1[row] = (float)s;
+    l1d[row] = s;
   }
 }
 
