@@ -319,6 +319,32 @@ __device__ __forceinline__ int wave_sum(int v) {
   DART_WAVE_BUTTERFLY(v, DART_OP_ADD);
   return v;
 }
+// Over a row of 16 lanes, and over all 64, for operations in which neither order nor repetition
+// counts (integers): rotations where the butterfly needs exact partners, a step without a select.
+#define DART_ROW_REDUCE(v, OP)                \
+  v = OP(v, dpp_move<kDppXor1>(v, v));        \
+  v = OP(v, dpp_move<kDppXor2>(v, v));        \
+  v = OP(v, dpp_move<kDppRor4>(v, v));        \
+  v = OP(v, dpp_move<kDppRor8>(v, v));
+#define DART_ALL_REDUCE(v, OP)                                        \
+  {                                                                   \
+    DART_ROW_REDUCE(v, OP)                                            \
+    const auto a_ = __builtin_amdgcn_permlane16_swap(v, v, false, false); \
+    v = OP(a_[0], a_[1]);                                             \
+    const auto b_ = __builtin_amdgcn_permlane32_swap(v, v, false, false); \
+    v = OP(b_[0], b_[1]);                                             \
+  }
+// (functions, not macros: an exchange that is written out again in the arm of a conditional runs with
+// some lanes off)
+__device__ __forceinline__ uint32_t least(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint32_t greatest(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__device__ __forceinline__ uint32_t row_min_u32(uint32_t v) { DART_ROW_REDUCE(v, least) return v; }
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t v) { DART_ROW_REDUCE(v, greatest) return v; }
+__device__ __forceinline__ int row_sum(int v) { DART_ROW_REDUCE(v, DART_OP_ADD) return v; }
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) { DART_ALL_REDUCE(v, least) return v; }
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) { DART_ALL_REDUCE(v, greatest) return v; }
+#undef DART_ALL_REDUCE
+#undef DART_ROW_REDUCE
 __device__ __forceinline__ float wave_min(float v) {
   DART_WAVE_BUTTERFLY(v, fminf);
   return v;

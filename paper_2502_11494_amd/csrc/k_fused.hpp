@@ -284,7 +284,10 @@ __device__ __forceinline__ void fused_gather_item(const Geo& g, const Sample& sm
 // parameters.  (The largest score-item layout, NB = 4, is smaller than the selection's.)
 union FusedShared {
   PivotShared<kSelPerThread> piv;
-  SelectShared<kFuThreads> sel;
+  struct {
+    SelectShared<kFuThreads> sel;
+    OrderShared<kFuThreads> os;
+  } ord;
   RetainShared ret;
   KSplitShared<1, FusedScoreCfg<1>::KS, kFuWaves> sc1;
   KSplitShared<2, FusedScoreCfg<2>::KS, kFuWaves> sc2;
@@ -361,7 +364,7 @@ __device__ __attribute__((noinline)) void fused_do_score(int b_in, int i_in) {
 __device__ __attribute__((noinline)) void fused_do_order(int b_in, int i_in) {
   DART_FUSED_PARAMS(b_in, i_in);
   DART_FUSED_PREFETCH_BEGIN();
-  order_scores_body<kFuThreads, true>(g, b, idx, a.S, a.lists, fu_sh.sel);
+  order_scores_body<kFuThreads, true>(g, b, idx, a.S, a.lists, fu_sh.ord.sel, fu_sh.ord.os);
   stores_done();
   DART_FUSED_PREFETCH_END();
 }

@@ -8,6 +8,162 @@
 
 namespace dart {
 
+// What makes a value-linear histogram between the lowest and the highest score too coarse are the few scores
+// far above the rest (tokens like the pivot), and those are never wanted.  The threads' lowest scores
+// bound the want-th lowest from above: if they form at least `want` groups, the highest of the groups'
+// minima is reached by `want` scores (of the second lowest of every thread: by twice as many as there
+// are threads).  So the range ends there, every wanted score lies in it, and of its 1024 buckets one holds
+// a few keys: the bucket that completes `want` ends the selection, prefix sums give every bucket's
+// place, and a key finds its rank among the keys of its own bucket (five barriers; collect_sorted's
+// way with its two histograms has twelve: lists of multi-crop 7.4 us, now 5.4, of sixteen 576-token images
+// 5.8 and 4.9, of video 10.9 and 7.5, of 32 packed samples of up to 16384 tokens 25 and 18).  If a bucket holds more than kOrderRefine keys the range is cut to the selected
+// buckets and counted once more; more than kOrderCrowd then (many equal scores), or scores that
+// are not numbers, leave the list to collect_sorted.
+constexpr int kOrderRefine = 24, kOrderCrowd = 64;
+template <int THREADS>
+struct OrderShared {
+  uint32_t lo[THREADS / kWave], hi[THREADS / kWave];
+  int total[THREADS / kWave];
+  int last, count, crowded;
+};
+
+// v[e] belongs to index tid + e*THREADS; put(position, key) receives the `want` lowest (value, index) keys.
+// False (on every thread, nothing put): not done, see above.
+template <int THREADS, int PER, typename Put>
+__device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int want, int tid,
+                                             SelectShared<THREADS, PER>& sh, OrderShared<THREADS>& os,
+                                             const Put& put) {
+  constexpr int kWaves = THREADS / kWave, kOwn = kSelBuckets / THREADS;  // (1 or 2 buckets per thread)
+  const int lane = tid & 63, w = tid >> 6;
+  const int ne = __builtin_amdgcn_readfirstlane((n + THREADS - 1) / THREADS);
+  const uint32_t none = mono_of(INFINITY);
+  float low = INFINITY;
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (e < ne && tid + e * THREADS < n) low = fminf(low, v[e]);
+  const uint32_t lowest = mono_of(low);
+  uint32_t top = lowest;
+  const int holders = n < THREADS ? n : THREADS;  // threads with a score: the first ones
+  if (want <= holders) {
+    // groups of 1, 2, 4, 8 or 16 neighbouring threads, as large as leaves `want` of them
+    if (holders >= 2 * want) top = least(top, dpp_move<kDppXor1>(top, top));
+    if (holders >= 4 * want) top = least(top, dpp_move<kDppXor2>(top, top));
+    if (holders >= 8 * want) top = least(top, lane_xor<4>((int)top, lane));
+    if (holders >= 16 * want) top = least(top, dpp_move<kDppRor8>(top, top));
+  } else {
+    const bool second = 2 * (n - THREADS < THREADS ? n - THREADS : THREADS) >= want;
+    float next = second ? INFINITY : -INFINITY;
+    low = INFINITY;
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if (e < ne && tid + e * THREADS < n) {
+        next = second ? fminf(next, fmaxf(low, v[e])) : fmaxf(next, v[e]);
+        low = fminf(low, v[e]);
+      }
+    top = mono_of(next);
+  }
+  top = top == none ? 0u : top;  // no score (or no second one): not one of them
+  const uint32_t wave_lo = wave_min_u32(lowest), wave_hi = wave_max_u32(top);
+  if (lane == 0) {
+    os.lo[w] = wave_lo;
+    os.hi[w] = wave_hi;
+  }
+#pragma unroll
+  for (int q = 0; q < kOwn; ++q) sh.hist[tid + q * THREADS] = 0;
+  if (tid == 0) {
+    os.count = -1;
+    os.crowded = 0;
+  }
+  __syncthreads();
+  const float lo = mono_inv(row_min_u32(os.lo[lane % kWaves]));
+  float hi = mono_inv(row_max_u32(os.hi[lane % kWaves]));
+  float scale = hi > lo ? (float)kSelBuckets / (hi - lo) : 0.f;
+  auto bucket = [&](float x) -> int { return (int)fminf((x - lo) * scale, (float)(kSelBuckets - 1)); };
+  int c, last;
+  for (int limit = kOrderRefine;; limit = kOrderCrowd) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if (e < ne && tid + e * THREADS < n && v[e] <= hi) atomicAdd(&sh.hist[bucket(v[e])], 1);
+    __syncthreads();
+    int h[kOwn], mine = 0;
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      h[q] = sh.hist[tid * kOwn + q];
+      mine += h[q];
+    }
+    int run = wave_excl_scan(mine, lane);
+    if (lane == 63) os.total[w] = run + mine;
+    __syncthreads();
+    run += row_sum(lane % kWaves < w && (lane & 15) < kWaves ? os.total[lane % kWaves] : 0);
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      const int before = run;
+      sh.hist[tid * kOwn + q] = before;  // where the bucket's keys start
+      run += h[q];
+      if (before < want && h[q] > limit) os.crowded = limit;
+      if (before < want && run >= want) {
+        os.last = tid * kOwn + q;
+        os.count = run;
+      }
+    }
+    __syncthreads();
+    c = __builtin_amdgcn_readfirstlane(os.count);
+    last = __builtin_amdgcn_readfirstlane(os.last);
+    const int crowded = __builtin_amdgcn_readfirstlane(os.crowded);
+    if (c < 0 || crowded == kOrderCrowd) return false;  // (block-uniform, as all of these)
+    if (crowded == 0 || limit == kOrderCrowd) break;
+    // (a little more than the selected buckets: their upper end is rounded)
+    hi = fminf(hi, lo + ((float)last + 1.01f) / scale);
+    scale = hi > lo ? (float)kSelBuckets / (hi - lo) : 0.f;
+    __syncthreads();  // everyone has read the three words
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) sh.hist[tid + q * THREADS] = 0;
+    if (tid == 0) os.count = -1;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int j = tid + e * THREADS;
+    if (e < ne && j < n && v[e] <= hi) {
+      const int d = bucket(v[e]);
+      if (d <= last)
+        sh.buf[atomicAdd(&sh.hist[d], 1)] = ((unsigned long long)mono_of(v[e]) << 32) | (unsigned)j;
+    }
+  }
+  __syncthreads();
+  // a cell up to the last bucket's now holds the end of its bucket's keys = the start of the next
+  for (int t = tid; t < c; t += THREADS) {
+    const unsigned long long key = sh.buf[t];
+    const int d = bucket(mono_inv((uint32_t)(key >> 32)));
+    int at = d > 0 ? sh.hist[d - 1] : 0;
+    const int end = sh.hist[d];
+    for (int u = at; u < end; ++u) at += sh.buf[u] < key ? 1 : 0;
+    if (at < want) put(at, key);
+  }
+  return true;
+}
+
+// A list that order_lowest leaves, by collect_sorted.  (A function of its own: inlined, its sorting
+// networks cost the kernel 70 to 136 spilled registers at 16 scores per thread.)
+template <int THREADS, bool COH, int PER>
+__device__ __attribute__((noinline)) void order_crowded(const float* row, int n, int want,
+                                                        unsigned long long* out,
+                                                        SelectShared<THREADS, PER>& sh) {
+  const int tid = threadIdx.x;
+  n = __builtin_amdgcn_readfirstlane(n);
+  want = __builtin_amdgcn_readfirstlane(want);
+  float v[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int j = tid + e * THREADS;
+    v[e] = ld_dev<COH>(&row[j < n ? j : n - 1]) + 0.0f;
+  }
+  int first = 0;  // keys of the first sorted run (all of them unless the sort was split)
+  collect_sorted<THREADS, true, PER>(v, n, want, tid, sh, &first);
+  for (int t = tid; t < want; t += THREADS)
+    st_dev<COH>(&out[t], t < first ? sh.buf[t] : sh.buf[THREADS + (t - first)]);
+}
+
 // The list of stage i of sample b, by one workgroup of THREADS (1024) threads.
 // S: pivot-major scores.  lists: 64-bit (score image << 32 | index) entries; the
 // region of sample b starts at P*row0(b) and holds the stage lists back to back
@@ -16,7 +172,8 @@ namespace dart {
 template <int THREADS, bool COH, int PER = kSelPerThread>
 __device__ __forceinline__ void order_scores_body(const Geo& g, int b, int i, const float* S,
                                                   unsigned long long* lists,
-                                                  SelectShared<THREADS, PER>& sh) {
+                                                  SelectShared<THREADS, PER>& sh,
+                                                  OrderShared<THREADS>& os) {
   constexpr int kSelThreads = THREADS;
   const int tid = threadIdx.x;
   const Sample sm = sample_of(g, b);
@@ -35,15 +192,16 @@ __device__ __forceinline__ void order_scores_body(const Geo& g, int b, int i, co
   }
 #pragma unroll
   for (int e = 0; e < PER; ++e) v[e] += 0.0f;  // -0 and +0 compare equal
-  int first = 0;  // keys of the first sorted run (all of them unless the sort was split)
-  collect_sorted<THREADS, true, PER>(v, n, want, tid, sh, &first);
   // offset of this stage's list = sum of the earlier stages' lengths: lane s of every wave
   // computes stage s's length, a wave scan adds them up (no loop over the stages)
   const int len_v = (tid & 63) < g.P ? sp.stage_len(n, tid & 63) : 0;
   const int off_v = wave_excl_scan(len_v, tid & 63);
   unsigned long long* out = lists + (long)g.P * sm.row0 + __builtin_amdgcn_readfirstlane(__shfl(off_v, i, kWave));
-  for (int t = tid; t < want; t += kSelThreads)
-    st_dev<COH>(&out[t], t < first ? sh.buf[t] : sh.buf[kSelThreads + (t - first)]);
+  if (order_lowest<THREADS, PER>(v, n, want, tid, sh, os, [&](int at, unsigned long long key) {
+        st_dev<COH>(&out[at], key);
+      }))
+    return;
+  order_crowded<THREADS, COH, PER>(row, n, want, out, sh);
 }
 
 // grid: B*P blocks of THREADS (1024); block (b, i), the samples from the longest to the
@@ -52,9 +210,10 @@ template <int THREADS, int PER>
 __global__ __launch_bounds__(THREADS) void k_order_scores(
     Geo g, const float* __restrict__ S, unsigned long long* __restrict__ lists) {
   __shared__ SelectShared<THREADS, PER> sh;
+  __shared__ OrderShared<THREADS> os;
   const int slot = blockIdx.x / g.P;
   const int b = g.by_size ? g.by_size[slot] : slot;
-  order_scores_body<THREADS, false, PER>(g, b, blockIdx.x % g.P, S, lists, sh);
+  order_scores_body<THREADS, false, PER>(g, b, blockIdx.x % g.P, S, lists, sh, os);
 }
 
 }  // namespace dart
