@@ -847,9 +847,11 @@ dart_status reduce_impl(const dart_desc* desc, const void* X, const void* crit, 
   if (random) p.g.mode = kGiven;
   if (p.g.mode == kGiven) crit = nullptr;
   DART_TRY(check_crit(p, X, crit, crit_D, crit_ld));
+  // (the first columns of X, or every other row, begin at the same address and are another matrix)
+  const bool own_crit = crit == X && crit_D == p.g.D && crit_ld == p.g.ld;
   DART_TRY(check_ws(p, ws, ws_bytes));
   // (the norm pass reads the criterion, not X, or there is none: the caller brought the norms)
-  if (crit != X || l1_given) DART_TRY(replan_first_read(p));
+  if (!own_crit || l1_given) DART_TRY(replan_first_read(p));
   hipStream_t st = static_cast<hipStream_t>(stream);
   // profiled calls: the kernels launched from here on belong to stage k
   struct StageGuard {
@@ -868,10 +870,10 @@ dart_status reduce_impl(const dart_desc* desc, const void* X, const void* crit, 
   // norm pass 1-3 % up to 264 MB and 5 % at 1.7 GB, where it runs at the memory's speed and
   // the gain of the score pass does not pay for it; the tighter error bound also saves the
   // retained-set kernel 10 % on near-duplicate video frames)
-  p.norms_given = p.g.mode != kGiven && p.g.Pin > 0 && crit == X &&
+  p.norms_given = p.g.mode != kGiven && p.g.Pin > 0 && own_crit &&
                   !l1_given && (double)p.g.total_N * p.g.ld * p.esz <= 1e9;
   // (the one-launch path computes its own norms: not for profiled calls or the caller's norms)
-  const bool fused = p.fusable && crit == X && events == nullptr && !l1_given && p.g.total_N > 0 &&
+  const bool fused = p.fusable && own_crit && events == nullptr && !l1_given && p.g.total_N > 0 &&
                      fused_enabled();
   // a norm pass fills the ragged offsets on the side (as part of its stage)
   const bool norm_pass = !fused && p.g.mode != kGiven && p.g.Pin > 0 && !l1_given;
@@ -892,7 +894,7 @@ dart_status reduce_impl(const dart_desc* desc, const void* X, const void* crit, 
   } else {
     // pivots chosen among the tokens (none if all of them come from outside) ...
     if (norm_pass)
-      DART_TRY(launch_row_l1(p, crit, crit_D, crit_ld, l1, crit == X, ws, st,
+      DART_TRY(launch_row_l1(p, crit, crit_D, crit_ld, l1, own_crit, ws, st,
                              p.norms_given ? at<double>(ws, p.o_l2) : nullptr));
     stage(1);
     // ... with the norms and marks of those from outside

@@ -154,7 +154,7 @@ __device__ __forceinline__ void select_pivots_body(
       const int j = sh.cand[u];
       double a, q;
       row_l1_l2_f64<DT>(Cb + (long)j * ldc * esz, Dc, lane, a, q);
-      if (C != X) {
+      if (C != X || Dc != g.D || ldc != g.ld) {
         double unused;
         row_l1_l2_f64<DT>(Xb + (long)j * g.ld * esz, g.D, lane, unused, q);
       }
