@@ -114,7 +114,8 @@ __global__ __launch_bounds__(256) void k_row_l1(const void* __restrict__ C, int 
 // Short rows (at most 64 pieces, criterion rows as a rule): R rows per wave, a load of each in flight,
 // because the reduction and the wave's start cost more than such a row takes to read.
 // The R sums are reduced together: lanes exchange half of their rows at every step, so that it takes
-// R + 2 additions instead of 6 R; a row's tree is the same in every place.  PREP: as above.
+// R + 2 additions instead of 6 R, in the order of wave_sum: the same bits as row_l1_l2_f64, which sums
+// such rows where the samples are spans or the norms the caller's.  PREP: as above.
 template <int DT, int R, bool PREP>
 __global__ __launch_bounds__(256) void k_short_row_l1(const void* __restrict__ C, int Dc, long ldc,
                                                       int rows, float* __restrict__ l1,
@@ -147,24 +148,24 @@ __global__ __launch_bounds__(256) void k_short_row_l1(const void* __restrict__ C
     add_piece_l1_l2<DT, false>(v[r], a[r], unused);
     a[r] = in ? a[r] : 0.0;
   }
-  // lanes 32.. go on with rows 4..7, then the lanes with bit 16 with the upper two, bit 8 the upper one
+  // odd lanes go on with rows 4..7, then the lanes with bit 1 with the upper two, bit 2 the upper one
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
-    const double keep = lane & 32 ? a[4 + h] : a[h], give = lane & 32 ? a[h] : a[4 + h];
-    a[h] = keep + lane_xor<32>(give, lane);
+    const double keep = lane & 1 ? a[4 + h] : a[h], give = lane & 1 ? a[h] : a[4 + h];
+    a[h] = keep + lane_xor<1>(give, lane);
   }
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const double keep = lane & 16 ? a[2 + h] : a[h], give = lane & 16 ? a[h] : a[2 + h];
-    a[h] = keep + lane_xor<16>(give, lane);
+    const double keep = lane & 2 ? a[2 + h] : a[h], give = lane & 2 ? a[h] : a[2 + h];
+    a[h] = keep + lane_xor<2>(give, lane);
   }
-  const double keep = lane & 8 ? a[1] : a[0], give = lane & 8 ? a[0] : a[1];
-  double s = keep + lane_xor<8>(give, lane);
-  s += lane_xor<4>(s, lane);
-  s += lane_xor<2>(s, lane);
-  s += lane_xor<1>(s, lane);
-  const long row = row0 + (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
-  if ((lane & 7) == 0 && row < rows) {
+  const double keep = lane & 4 ? a[1] : a[0], give = lane & 4 ? a[0] : a[1];
+  double s = keep + lane_xor<4>(give, lane);
+  s += lane_xor<8>(s, lane);
+  s += lane_xor<16>(s, lane);
+  s += lane_xor<32>(s, lane);
+  const long row = row0 + (lane & 1) * 4 + ((lane >> 1) & 1) * 2 + ((lane >> 2) & 1);
+  if (lane < R && row < rows) {
     l1[row] = (float)s;
     l1d[row] = s;
   }

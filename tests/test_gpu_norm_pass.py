@@ -73,3 +73,32 @@ def test_scores_stored_at_any_alignment(n, P):
     assert np.max(np.abs(out[0] - exact)) <= D.score_tolerance(D.DART_BF16)
     for o in out[1:]:
         np.testing.assert_array_equal(o.view(np.uint32), out[0].view(np.uint32))
+
+
+@pytest.mark.parametrize("width", [32, 60, 128, 256])
+def test_every_entry_ranks_by_the_same_sums(width):
+    """fp32 rows that are permutations of one: their sums differ in the last bits of fp64 only, by the
+    order of the additions, which is the same whether the samples are packed, spans or come with norms."""
+    n, P = 400, 24
+    print(f"[case] permuted rows of {width}", flush=True)
+    g = torch.Generator().manual_seed(width)
+    row = torch.randn(width, generator=g) * torch.exp2(torch.randint(-34, 4, (width,), generator=g).float())
+    row[0] = 13.7
+    C = torch.stack([row[torch.randperm(width, generator=g)] for _ in range(n)])
+    assert len(set(C.double().abs().cumsum(1)[:, -1].tolist())) > 1  # (in whatever order)
+    Cd, X = C.cuda(), torch.randn((n, 64), generator=g).cuda()
+    kw = dict(crit=Cd, crit_D=width, crit_ld=width)
+    zero = torch.zeros(1, dtype=torch.int32, device="cuda")
+    cu = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    packed, _ = select(X, Cd, D.DART_F32, 1, n, P)
+    ragged, _ = select(X, Cd, D.DART_F32, 1, n, P, cu)
+    desc = D.make_desc(1, 64, P, D.DART_F32, K=P, cu_seqlens=cu, total_N=n, max_N=n, span_start=zero, X_rows=n)
+    spans = torch.full((P,), -1, dtype=torch.int32, device="cuda")
+    D.dart_select_pivots(desc, X, spans, D.alloc_workspace(desc), **kw)
+    desc = D.make_desc(1, 64, P, D.DART_F32, N=n, K=P)
+    given = torch.full((P,), -1, dtype=torch.int32, device="cuda")
+    D.dart_reduce_with_norms(desc, X, torch.empty((P, 64), device="cuda"),
+                             torch.empty(P, dtype=torch.int32, device="cuda"), D.alloc_workspace(desc),
+                             C.double().abs().sum(1).float().cuda(), 1e-6, piv_out=given, **kw)
+    for other in (ragged[0], spans.cpu().numpy(), given.cpu().numpy()):
+        np.testing.assert_array_equal(packed[0], other)
