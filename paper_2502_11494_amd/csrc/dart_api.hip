@@ -148,34 +148,40 @@ KsChoice choose_score_tiles(const Geo& g, int units, bool first_read) {
     if (cost(four).fits) return four;
   }
   // ... a unit that gets one tile of at most 5 waves has too few loads in flight: two groups on a tile
-  // of about the same height (score pass of eight samples of 2100 tokens 20.8 -> 19.5 us, first read 28.0
-  // -> 24.2; whole call on eight spans, 15249 rows of 3584: 105.7 -> 99.7) ...
+  // of about the same height (score pass of eight samples of 2100 tokens in tiles of 96 rows of two groups
+  // and of 80 rows of one: 20.7 and 21.6 us, with 32 pivots 21.6 and 23.8, with 64 31.5 and 38.1, on a
+  // first read 30.6 and 32.5; eight of 2560, whose 80-row tiles fill the units: 24.3 and 23.9, 23.3 and
+  // 24.8, 32.5 and 38.5; eight of 2048, 64 rows: 19.9 and 21.4; whole call on eight spans, 15249 rows of
+  // 3584: 105.7 -> 99.7) ...
+  KsChoice pick = best;
   if (best.split == 1 && best.waves <= 5 && cost(best).rows_busiest == R_best) {
     const KsChoice two = {best.waves == 3 ? 6 : best.waves == 4 ? 8 : 12, 2};
-    if (cost(two).fits) return two;
+    if (cost(two).fits) pick = two;
   }
-  // ... and on a first read of X they also beat the single group on small dense batches as
-  // long as no compute unit gets more rows than with the model's pick (eight samples of 2880
-  // tokens: 32.8-34.4 us against 39.1 for 6 waves in one group; five of 5000 tokens in tiles of 128
-  // rows: 36.2 against 32.2; with 32 pivots the single group stays ahead too: 45.6 against 59.5 us).
+  // ... and on a first read of X they also beat one and two groups on small dense batches as
+  // long as no compute unit gets more rows: up to 96 (score pass of eight samples of 2048 tokens, 32-row
+  // tiles of four groups and 64-row tiles of two: 23.7 and 28.4 us, of 2560 31.2 and 32 to 37, of 3000
+  // 32.6 and 34.5 in one group, the headline batch 32.8-34.4 and 39.1), and up to 128 where the tiles
+  // leave no unit idle (eight of 4096 43.8 and 53.1, sixteen of 2000 42.3 and 43.3; but eight of 3600
+  // 40.8 and 37.6, five of 5000 36.2 and 32.2).  With 32 pivots fewer groups stay ahead: 31.4 and 28.8
+  // on eight of 2048, 59.5 and 45.6 on eight of 2880.
   if (first_read && best.split == 1 && NB == 1 && g.cu == nullptr) {
-    const Cost picked = cost(best);
-    if (picked.rows_busiest <= 96) {
+    const Cost picked = cost(pick);
+    const bool full = (double)g.total_N / units >= 0.95 * picked.rows_busiest;
+    if (picked.rows_busiest <= (full ? 128 : 96)) {
       // (of the two, the one that loads the busiest unit less; equal: the 32-row tiles, two
       // workgroups of which share a unit: 34.7 against 35.5-36.3 us on the headline batch)
-      KsChoice alt = best;
       double alt_rows = picked.rows_busiest + 1;
       for (const KsChoice& c : {KsChoice{8, 4}, KsChoice{12, 4}}) {
         const Cost k = cost(c);
         if (k.fits && k.rows_busiest <= picked.rows_busiest && k.rows_busiest < alt_rows) {
           alt_rows = k.rows_busiest;
-          alt = c;
+          pick = c;
         }
       }
-      return alt;
     }
   }
-  return best;
+  return pick;
 }
 
 // Tiles of the fp32 score kernels: rows 2 (k_scores_f32_rows), 4 (k_scores_f32_t4, 4 * groups pivots

@@ -294,3 +294,21 @@ def test_score_tile_shape_follows_the_batch_and_the_override():
     assert L.dart_score_tile_shape(C.byref(desc), C.byref(w), None) == D.DART_ERR_NULL
     assert L.dart_score_tile_shape(None, C.byref(w), C.byref(w)) == D.DART_ERR_NULL
     assert w.value == 7  # nothing is written on an error
+
+
+@pytest.mark.parametrize("B,N,P,after_norms,first", [
+    (8, 2048, 16, (8, 2), (8, 4)),    # one 64-row tile a unit
+    (8, 2560, 16, (12, 2), (8, 4)),   # 80 rows a unit: two groups take 96
+    (8, 2100, 16, (12, 2), (8, 4)),
+    (4, 3584, 16, (8, 2), (8, 4)),
+    (8, 3000, 16, (6, 1), (8, 4)),    # 94 rows a unit of tiles of 96
+    (8, 4096, 16, (8, 1), (8, 4)),    # 128 rows on every unit
+    (16, 2000, 16, (8, 1), (8, 4)),
+    (8, 3600, 16, (8, 1), (8, 1)),    # 128 rows on some
+    (8, 2048, 32, (8, 2), (8, 2)),    # more than 16 pivots: as after a norm pass
+    (8, 2100, 64, (12, 2), (12, 2)),
+])
+def test_score_tiles_of_batches_of_few_tiles(B, N, P, after_norms, first):
+    desc = D.make_desc(B, 4096, P, D.DART_BF16, N=N, K=P)
+    assert D.dart_score_tile_shape(desc) == after_norms
+    assert D.dart_score_tile_shape_first_read(desc) == first
