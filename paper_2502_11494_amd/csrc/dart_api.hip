@@ -99,10 +99,14 @@ constexpr size_t kKsLdsLimit = 150 * 1024;  // of the 160 KB of a compute unit
 // memory-side cache.
 KsChoice choose_score_tiles(const Geo& g, int units, bool first_read) {
   const int NB = g.Ppad / 16;
-  // Thousands of tiles spread evenly by themselves, and short ones end together (whole call on 292 000
-  // packed rows of 3584: 808 us with 64-row tiles, 827 with the model's 144; 131 000 rows, score pass: 154
-  // and 162).
-  if (NB == 1 && g.total_N >= 512L * units) return {4, 1};
+  // Thousands of tiles spread evenly by themselves, and short ones end together.  Packed batches: from
+  // 131 000 rows on (whole call with 64-row tiles and with the model's, rows of 1024 to 8192: sixteen
+  // samples, 131 000 rows, 150 and 155 us to 835 and 862; 200 of 800 tokens 194 and 197 to 990 and 1031;
+  // 32 samples, 290 000 rows of 3584, 793 and 804).  Dense ones, whose tiles the model can make fill the
+  // units, from 197 000 (64 of 4096 tokens 155.6 and 156.5 to 619 and 626, 230 of 1500 520 and 532 at
+  // 2048; at most 0.7 % behind, on 512 of 576); below, the model's are up to 2.5 % ahead (48 of 2880 335
+  // and 341 at 3584, 738 and 756 at 8192).
+  if (NB == 1 && g.total_N >= (g.cu ? 512L : 768L) * units) return {4, 1};
   const double rowbytes = (double)g.D * 2;
   const int chunks = (g.D + kKsCH - 1) / kKsCH;
   struct Cost {

@@ -312,3 +312,18 @@ def test_score_tiles_of_batches_of_few_tiles(B, N, P, after_norms, first):
     desc = D.make_desc(B, 4096, P, D.DART_BF16, N=N, K=P)
     assert D.dart_score_tile_shape(desc) == after_norms
     assert D.dart_score_tile_shape_first_read(desc) == first
+
+
+@pytest.mark.parametrize("Dm", [1024, 8192])
+def test_score_tiles_of_batches_of_many_tiles(Dm):
+    def shape(B, N=0, total=0, P=16):
+        desc = D.make_desc(B, Dm, P, D.DART_BF16, N=N, K=P, total_N=total, max_N=16384 if total else 0)
+        if total:
+            desc.cu_seqlens = 0x1000  # never dereferenced on the host
+        assert D.dart_score_tile_shape_first_read(desc) == D.dart_score_tile_shape(desc)
+        return D.dart_score_tile_shape(desc)
+
+    assert shape(16, total=512 * 256) == (4, 1) and shape(16, total=512 * 256 - 1) == (11, 1)
+    assert shape(96, N=2048) == (4, 1)           # 768 rows a unit
+    assert shape(48, N=2880) == (12, 1) and shape(16, N=9216) == (12, 1) and shape(64, N=2048) == (8, 1)
+    assert shape(32, total=234356, P=32) != (4, 1)
