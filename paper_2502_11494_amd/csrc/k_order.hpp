@@ -16,15 +16,25 @@ namespace dart {
 // a few keys: the bucket that completes `want` ends the selection, prefix sums give every bucket's
 // place, and a key finds its rank among the keys of its own bucket (five barriers; collect_sorted's
 // way with its two histograms has twelve: lists of multi-crop 7.4 us, now 5.4, of sixteen 576-token images
-// 5.8 and 4.9, of video 10.9 and 7.5, of 32 packed samples of up to 16384 tokens 25 and 18).  If a bucket holds more than kOrderRefine keys the range is cut to the selected
-// buckets and counted once more; more than kOrderCrowd then (many equal scores), or scores that
-// are not numbers, leave the list to collect_sorted.
-constexpr int kOrderRefine = 24, kOrderCrowd = 64;
+// 5.8 and 4.9, of video 10.9 and 7.5, of 32 packed samples of up to 16384 tokens 25 and 18).
+// Scores far below the rest (rows of zeros, say) crowd the others into a few buckets all the same.  If a
+// selected bucket holds more than kOrderRefine keys, the selected ones are counted once more, in buckets of
+// their own number: a coarse bucket is divided into as many parts as its share of the keys.  What still
+// shares a bucket then has equal scores as a rule (copies of a row): up to kOrderTies such groups of any
+// size are ranked by a bit per index.  Groups of more than kOrderCrowd different scores, more groups, and
+// scores that are not numbers leave the list to collect_sorted.  (Ordering and retained set on given scores,
+// 0.5 % of them zeros below a narrow rest, by collect_sorted, by cutting the range at the selected buckets
+// first, and this way: eight samples of 2880 24.1, 28.2 and 17.0 us, four of 9216 60, 73 and 27.6, of 16384
+// 107, 122 and 33; a tenth of the tokens equal 20.1, 23.8 and 17.4, 41, 50 and 27.9, 63, 76 and 33.5; two
+// clusters, where the cut is enough, 18.9, 16.0 and 16.6, 27.1, 24.8 and 26.0, 33, 28.9 and 30.0.)
+constexpr int kOrderRefine = 24, kOrderCrowd = 64, kOrderTies = 8;
 template <int THREADS>
 struct OrderShared {
   uint32_t lo[THREADS / kWave], hi[THREADS / kWave];
   int total[THREADS / kWave];
-  int last, count, crowded;
+  int parts[kSelBuckets];  // of a coarse bucket: its first fine bucket and, << 16, how many it has
+  int tie_from[kOrderTies], tie_to[kOrderTies];
+  int last, count, crowded, mixed;
 };
 
 // v[e] belongs to index tid + e*THREADS; put(position, key) receives the `want` lowest (value, index) keys.
@@ -73,19 +83,30 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
   if (tid == 0) {
     os.count = -1;
     os.crowded = 0;
+    os.mixed = 0;
   }
   __syncthreads();
   const float lo = mono_inv(row_min_u32(os.lo[lane % kWaves]));
-  float hi = mono_inv(row_max_u32(os.hi[lane % kWaves]));
-  float scale = hi > lo ? (float)kSelBuckets / (hi - lo) : 0.f;
-  auto bucket = [&](float x) -> int { return (int)fminf((x - lo) * scale, (float)(kSelBuckets - 1)); };
-  int c, last;
-  for (int limit = kOrderRefine;; limit = kOrderCrowd) {
+  const float hi = mono_inv(row_max_u32(os.hi[lane % kWaves]));
+  const float scale = hi > lo ? (float)kSelBuckets / (hi - lo) : 0.f;
+  // (both monotone in x; a product that is no number, of an infinite range, counts as the highest)
+  auto coarse = [&](float x) -> int { return (int)fminf((x - lo) * scale, (float)(kSelBuckets - 1)); };
+  auto fine = [&](float x, int d) -> int {
+    const int p = os.parts[d], first = p & 0xffff, more = (p >> 16) - 1;
+    return more <= 0 ? first : first + (int)fminf(fmaf(x - lo, scale, -(float)d) * (float)(more + 1), (float)more);
+  };
+  int h[kOwn], before_own, c, end_bucket;
+  // Counts the keys of every bucket (of(e): that of the thread's e-th score if it is selected, else
+  // kSelBuckets); c: keys up to end_bucket, which completes `want` (-1: none does).  Returns how many of
+  // these buckets hold more than `limit`.
+  auto tally = [&](auto of, int limit, bool note) -> int {
 #pragma unroll
-    for (int e = 0; e < PER; ++e)
-      if (e < ne && tid + e * THREADS < n && v[e] <= hi) atomicAdd(&sh.hist[bucket(v[e])], 1);
+    for (int e = 0; e < PER; ++e) {
+      const int d = of(e);
+      if (d < kSelBuckets) atomicAdd(&sh.hist[d], 1);
+    }
     __syncthreads();
-    int h[kOwn], mine = 0;
+    int mine = 0;
 #pragma unroll
     for (int q = 0; q < kOwn; ++q) {
       h[q] = sh.hist[tid * kOwn + q];
@@ -95,12 +116,19 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
     if (lane == 63) os.total[w] = run + mine;
     __syncthreads();
     run += row_sum(lane % kWaves < w && (lane & 15) < kWaves ? os.total[lane % kWaves] : 0);
+    before_own = run;
 #pragma unroll
     for (int q = 0; q < kOwn; ++q) {
       const int before = run;
       sh.hist[tid * kOwn + q] = before;  // where the bucket's keys start
       run += h[q];
-      if (before < want && h[q] > limit) os.crowded = limit;
+      if (before < want && h[q] > limit) {
+        const int t = atomicAdd(&os.crowded, 1);
+        if (note && t < kOrderTies) {
+          os.tie_from[t] = before;
+          os.tie_to[t] = run;
+        }
+      }
       if (before < want && run >= want) {
         os.last = tid * kOwn + q;
         os.count = run;
@@ -108,37 +136,117 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
     }
     __syncthreads();
     c = __builtin_amdgcn_readfirstlane(os.count);
-    last = __builtin_amdgcn_readfirstlane(os.last);
-    const int crowded = __builtin_amdgcn_readfirstlane(os.crowded);
-    if (c < 0 || crowded == kOrderCrowd) return false;  // (block-uniform, as all of these)
-    if (crowded == 0 || limit == kOrderCrowd) break;
-    // (a little more than the selected buckets: their upper end is rounded)
-    hi = fminf(hi, lo + ((float)last + 1.01f) / scale);
-    scale = hi > lo ? (float)kSelBuckets / (hi - lo) : 0.f;
-    __syncthreads();  // everyone has read the three words
+    end_bucket = __builtin_amdgcn_readfirstlane(os.last);
+    return __builtin_amdgcn_readfirstlane(os.crowded);
+  };
+  auto scatter = [&](auto of) {
 #pragma unroll
-    for (int q = 0; q < kOwn; ++q) sh.hist[tid + q * THREADS] = 0;
-    if (tid == 0) os.count = -1;
-    __syncthreads();
-  }
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int j = tid + e * THREADS;
-    if (e < ne && j < n && v[e] <= hi) {
-      const int d = bucket(v[e]);
-      if (d <= last)
-        sh.buf[atomicAdd(&sh.hist[d], 1)] = ((unsigned long long)mono_of(v[e]) << 32) | (unsigned)j;
+    for (int e = 0; e < PER; ++e) {
+      const int d = of(e);
+      if (d <= end_bucket)
+        sh.buf[atomicAdd(&sh.hist[d], 1)] =
+            ((unsigned long long)mono_of(v[e]) << 32) | (unsigned)(tid + e * THREADS);
     }
+    __syncthreads();
+  };
+  // a cell up to the last bucket's now holds the end of its bucket's keys = the start of the next
+  auto rank = [&](auto bucket, int longest) {
+    for (int t = tid; t < c; t += THREADS) {
+      const unsigned long long key = sh.buf[t];
+      const int d = bucket(mono_inv((uint32_t)(key >> 32)));
+      int at = d > 0 ? sh.hist[d - 1] : 0;
+      const int end = sh.hist[d];
+      if (end - at > longest) continue;
+      for (int u = at; u < end; ++u) at += sh.buf[u] < key ? 1 : 0;
+      if (at < want) put(at, key);
+    }
+  };
+  auto coarse_of = [&](int e) -> int {
+    return e < ne && tid + e * THREADS < n && v[e] <= hi ? coarse(v[e]) : kSelBuckets;
+  };
+  const int crowded = tally(coarse_of, kOrderRefine, false);
+  if (c < 0) return false;  // (block-uniform, as all of these)
+  if (crowded == 0) {
+    scatter(coarse_of);
+    rank(coarse, kOrderRefine);
+    return true;
+  }
+  // of a coarse bucket whose keys are the before-th to the run-th of c: the fine buckets of that share
+  const int last = end_bucket;
+  const float share = (float)kSelBuckets / (float)c;
+#pragma unroll
+  for (int q = 0; q < kOwn; ++q) {
+    const int first = (int)fminf((float)before_own * share, (float)(kSelBuckets - 1));
+    before_own += h[q];
+    const int next = (int)fminf((float)before_own * share, (float)(kSelBuckets - 1));
+    os.parts[tid * kOwn + q] = first | ((next - first) << 16);
+  }
+  __syncthreads();  // everyone has read the words, too
+#pragma unroll
+  for (int q = 0; q < kOwn; ++q) sh.hist[tid + q * THREADS] = 0;
+  if (tid == 0) {
+    os.count = -1;
+    os.crowded = 0;
   }
   __syncthreads();
-  // a cell up to the last bucket's now holds the end of its bucket's keys = the start of the next
-  for (int t = tid; t < c; t += THREADS) {
-    const unsigned long long key = sh.buf[t];
-    const int d = bucket(mono_inv((uint32_t)(key >> 32)));
-    int at = d > 0 ? sh.hist[d - 1] : 0;
-    const int end = sh.hist[d];
-    for (int u = at; u < end; ++u) at += sh.buf[u] < key ? 1 : 0;
-    if (at < want) put(at, key);
+  auto divided = [&](float x) -> int {
+    const int d = coarse(x);
+    return d <= last ? fine(x, d) : kSelBuckets;
+  };
+  // (all of a thread's buckets before it counts the first: each takes an access to LDS)
+  int slot[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int d = coarse_of(e);
+    const int f = fine(v[e], d < kSelBuckets ? d : 0);
+    slot[e] = d <= last ? f : kSelBuckets;
+  }
+  auto slot_of = [&](int e) -> int { return slot[e]; };
+  const int ties = tally(slot_of, kOrderCrowd, true);
+  if (c < 0 || ties > kOrderTies) return false;
+  scatter(slot_of);
+  for (int s = 0; s < ties; ++s) {
+    const int from = os.tie_from[s], to = os.tie_to[s];
+    const uint32_t value = (uint32_t)(sh.buf[from] >> 32);
+    for (int t = from + tid; t < to; t += THREADS)
+      if ((uint32_t)(sh.buf[t] >> 32) != value) os.mixed = 1;
+  }
+  if (ties > 0) {
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(os.mixed) != 0) return false;
+  }
+  rank(divided, kOrderCrowd);
+  // equal scores: a bit per index, and for every 32 of them how many come before
+  constexpr int kWords = kMaxN / 32;
+  static_assert(2 * kWords <= kSelBuckets, "bits and counts take the buckets' place");
+  for (int s = 0; s < ties; ++s) {
+    const int from = os.tie_from[s], to = os.tie_to[s];
+    __syncthreads();
+    for (int t = tid; t < kWords; t += THREADS) sh.hist[t] = 0;
+    __syncthreads();
+    for (int t = from + tid; t < to; t += THREADS) {
+      const uint32_t j = (uint32_t)sh.buf[t];
+      atomicOr(&sh.hist[j >> 5], (int)(1u << (j & 31)));
+    }
+    __syncthreads();
+    if (w == 0) {
+      constexpr int kOf = kWords / kWave;
+      int mine = 0;
+      for (int q = 0; q < kOf; ++q) mine += __popc(sh.hist[lane * kOf + q]);
+      int run = wave_excl_scan(mine, lane);
+      for (int q = 0; q < kOf; ++q) {
+        sh.hist[kWords + lane * kOf + q] = run;
+        run += __popc(sh.hist[lane * kOf + q]);
+      }
+    }
+    __syncthreads();
+    for (int t = from + tid; t < to; t += THREADS) {
+      const unsigned long long key = sh.buf[t];
+      const uint32_t j = (uint32_t)key;
+      const int at = from + sh.hist[kWords + (j >> 5)] +
+                     __popc((uint32_t)sh.hist[j >> 5] & ((1u << (j & 31)) - 1u));
+      if (at < want) put(at, key);
+    }
   }
   return true;
 }
