@@ -314,8 +314,13 @@ __device__ __forceinline__ void order_scores_body(const Geo& g, int b, int i, co
 
 // grid: B*P blocks of THREADS (1024); block (b, i), the samples from the longest to the
 // shortest where g.by_size says so.  PER*THREADS >= the longest sample.
+// (Samples of at most 4096 tokens: eight waves to a SIMD, so that two workgroups share a compute unit.  Without
+// the bound the call of order_crowded takes 102 scalar registers, which leaves seven: lists of 32 samples
+// of 2880 tokens, 16 pivots, 7.8 us and 6.2 with it, of 512 of 1500, 8 pivots, 45.6 and 31.8.  Longer ones
+// have no room in LDS, or spill.)
 template <int THREADS, int PER>
-__global__ __launch_bounds__(THREADS) void k_order_scores(
+__global__ __launch_bounds__(THREADS)
+__attribute__((amdgpu_waves_per_eu(PER <= 4 ? 8 : 4))) void k_order_scores(
     Geo g, const float* __restrict__ S, unsigned long long* __restrict__ lists) {
   __shared__ SelectShared<THREADS, PER> sh;
   __shared__ OrderShared<THREADS> os;
