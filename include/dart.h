@@ -195,10 +195,9 @@ DART_API dart_status dart_score_tile_shape_first_read(const dart_desc* desc, int
  * draw order; crit is ignored and l1_out is not written.
  * Output piv[b*P + i] = index, local to sample b, of its i-th pivot, ordered by
  * (L1 norm descending, index ascending) -- ascending norm for DART_PIVOT_MIN_L1.
- * Norms are accumulated in fp32 and every token whose fp32 norm could still
- * reach the top P within the rounding bound is re-evaluated in fp64, so the
- * order is that of the exact norms.  l1_out (optional, float[total_N]) receives
- * the fp32 L1 norm of every criterion row. */
+ * Norms are summed in fp64, in an order that depends on the row's length alone,
+ * and ranked by these sums; rows of equal bytes tie.  l1_out (optional,
+ * float[total_N]) receives the L1 norm of every criterion row, rounded once to fp32. */
 DART_API dart_status dart_select_pivots(const dart_desc* desc, const void* X, const void* crit,
                                int32_t crit_D, int64_t crit_ld, int32_t* piv, float* l1_out,
                                void* ws, size_t ws_bytes, void* stream);

@@ -553,18 +553,25 @@ dart_status launch_select_pivots(const Plan& p, const void* X, const void* C, in
   const float tau = (float)(std::max(l1_rel_err, 0.0) + 1.2e-7);
   double* l1d = at<double>(ws, p.o_scr_f64);
   // 1024 threads: a 256-thread variant measured slower even for short samples
-#define DART_LAUNCH_PIVOTS_AS(DT, PER, EXACT)                                                    \
-  DART_LAUNCH((k_select_pivots<DT, PER, EXACT>), dim3(p.g.B), dim3(1024), 0, st, p.g, X, C, Dc,  \
-              ldc, l1, piv, pl2, l1d, l2sq, tau)
+  // (up to 4096 tokens: samples longer than that by the hundred take milliseconds elsewhere)
+  const bool two = p.g.B > compute_units();
+#define DART_LAUNCH_PIVOTS_AS(DT, PER, EXACT, TWO)                                               \
+  DART_LAUNCH((k_select_pivots<DT, PER, EXACT, TWO>), dim3(p.g.B), dim3(1024), 0, st, p.g, X, C, \
+              Dc, ldc, l1, piv, pl2, l1d, l2sq, tau)
+#define DART_LAUNCH_PIVOTS_DT(DT, PER)                                                           \
+  do {                                                                                           \
+    if (l1_rel_err >= 0) DART_LAUNCH_PIVOTS_AS(DT, PER, false, false);                           \
+    else if (two && PER <= 4) DART_LAUNCH_PIVOTS_AS(DT, PER, true, (PER <= 4));                  \
+    else DART_LAUNCH_PIVOTS_AS(DT, PER, true, false);                                            \
+  } while (0)
 #define DART_LAUNCH_PIVOTS(PER)                                                                  \
   do {                                                                                           \
-    if (p.g.dtype == kBF16 && l1_rel_err < 0) DART_LAUNCH_PIVOTS_AS(kBF16, PER, true);           \
-    else if (p.g.dtype == kBF16) DART_LAUNCH_PIVOTS_AS(kBF16, PER, false);                       \
-    else if (l1_rel_err < 0) DART_LAUNCH_PIVOTS_AS(kF32, PER, true);                             \
-    else DART_LAUNCH_PIVOTS_AS(kF32, PER, false);                                                \
+    if (p.g.dtype == kBF16) DART_LAUNCH_PIVOTS_DT(kBF16, PER);                                   \
+    else DART_LAUNCH_PIVOTS_DT(kF32, PER);                                                       \
   } while (0)
   DART_FOR_VALUES_PER_THREAD(values_per_thread(p.g.max_N), DART_LAUNCH_PIVOTS);
 #undef DART_LAUNCH_PIVOTS
+#undef DART_LAUNCH_PIVOTS_DT
 #undef DART_LAUNCH_PIVOTS_AS
   DART_LAUNCH_CHECK();
   return DART_OK;
@@ -794,7 +801,7 @@ dart_status launch_fused(Plan& p, const void* X, const int64_t* pos, void* Y, in
   a.score_start = sstart;
   a.gather_start = gstart;
   a.status = at<int>(ws, p.o_status);
-  a.tau_l1 = (float)l1_rel_bound(p.g.dtype, p.g.D);
+  a.tau_l1 = (float)l1_rel_bound_bf16(p.g.D);
   a.two_tau = (float)(2.0 * 1.01 * score_abs_bound(p.g.dtype, kNormsF32Squares));
   a.keep_cached = (double)p.g.total_N * p.g.ld * p.esz <= 224e6 ? 1 : 0;
   a.spin_limit = 1 << 20;
@@ -875,11 +882,14 @@ dart_status reduce_impl(const dart_desc* desc, const void* X, const void* crit, 
   int* piv = piv_out ? piv_out : at<int>(ws, p.o_piv);
   float* S = S_out ? S_out : at<float>(ws, p.o_S);
   float* l1 = at<float>(ws, p.o_l1);
-  // hidden states as their own criterion: the norm pass also leaves the squared token norms,
-  // which saves the score pass its Gram products (measured: the extra arithmetic costs the
-  // norm pass 1-3 % up to 264 MB and 5 % at 1.7 GB, where it runs at the memory's speed and
-  // the gain of the score pass does not pay for it; the tighter error bound also saves the
-  // retained-set kernel 10 % on near-duplicate video frames)
+  // hidden states as their own criterion: the norm pass also leaves the squared token norms.  Selection takes
+  // the pivots' from there instead of summing their rows again (fp32, whole call with and without: one
+  // 576-token image 35.2 and 36.7 us, two samples of 9216 with 32 pivots 196 and 204; the fp32 score kernels
+  // sum their own), the bf16 score pass saves its Gram products, and the tighter error bound
+  // the retained-set kernel 10 % on near-duplicate video frames.  Above 1 GB the norm pass runs at the
+  // memory's speed and takes up to 2 % longer with them, the 64-row tiles up to 4 % (100 samples of 2880
+  // of 3584, 16 pivots: 766 us with, 756 without; 32 of 8000 of 2048: 392 and 394; with 32 or 48 pivots the
+  // call would be 1-3 % faster with them there too: 24 of 9216 of 3584 612 and 620).
   p.norms_given = p.g.mode != kGiven && p.g.Pin > 0 && own_crit &&
                   !l1_given && (double)p.g.total_N * p.g.ld * p.esz <= 1e9;
   // (the one-launch path computes its own norms: not for profiled calls or the caller's norms)

@@ -199,7 +199,8 @@ __device__ __forceinline__ T lds_uniform(const T& src) {
 
 // ---- the items ---------------------------------------------------------------------------
 
-// Norm item: L1 norm (fp32, the order of k_row_l1) and squared Euclidean norm (fp64 over fp32
+// Norm item: L1 norm (fp32 sums, where k_row_l1's are fp64: the selection sums its candidates' rows
+// again in fp64) and squared Euclidean norm (fp64 over fp32
 // piece sums) of the token rows [r0, r0 + 64) of one sample; a wave takes 4 rows in turn.
 __device__ __forceinline__ void fused_norm_item(const Geo& g, const Sample& sm, int r0,
                                                 const FusedArgs& a) {
@@ -231,7 +232,7 @@ __device__ __forceinline__ void fused_norm_item(const Geo& g, const Sample& sm, 
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        acc += piece_abs_sum<kBF16>(v[u]);
+        acc += piece_abs_sum_bf16(v[u]);
         sq += (double)piece_sq_sum_bf16(v[u]);
       }
     }

@@ -8,21 +8,14 @@
 namespace dart {
 
 // (fp32 sums of a piece: the one-launch kernel's)
-// Sum of |x| over one 16-byte piece, as a fixed pairwise tree (3 roundings for
-// 8 bf16 values, 2 for 4 floats).  |x| of a bf16 widened to fp32 is exact.
-template <int DT>
-__device__ __forceinline__ float piece_abs_sum(const u32x4& v) {
-  if (DT == kBF16) {
-    float a0 = fabsf(bf16_lo(v.x)) + fabsf(bf16_hi(v.x));
-    float a1 = fabsf(bf16_lo(v.y)) + fabsf(bf16_hi(v.y));
-    float a2 = fabsf(bf16_lo(v.z)) + fabsf(bf16_hi(v.z));
-    float a3 = fabsf(bf16_lo(v.w)) + fabsf(bf16_hi(v.w));
-    return (a0 + a1) + (a2 + a3);
-  } else {
-    float a0 = fabsf(__uint_as_float(v.x)) + fabsf(__uint_as_float(v.y));
-    float a1 = fabsf(__uint_as_float(v.z)) + fabsf(__uint_as_float(v.w));
-    return a0 + a1;
-  }
+// Sum of |x| over one 16-byte piece of bf16 values, as a fixed pairwise tree (3 roundings).
+// |x| of a bf16 widened to fp32 is exact.
+__device__ __forceinline__ float piece_abs_sum_bf16(const u32x4& v) {
+  float a0 = fabsf(bf16_lo(v.x)) + fabsf(bf16_hi(v.x));
+  float a1 = fabsf(bf16_lo(v.y)) + fabsf(bf16_hi(v.y));
+  float a2 = fabsf(bf16_lo(v.z)) + fabsf(bf16_hi(v.z));
+  float a3 = fabsf(bf16_lo(v.w)) + fabsf(bf16_hi(v.w));
+  return (a0 + a1) + (a2 + a3);
 }
 
 // Sum of x^2 over one 16-byte piece of bf16 values: the squares are exact in fp32 (8-bit
@@ -38,12 +31,9 @@ __device__ __forceinline__ float piece_sq_sum_bf16(const u32x4& v) {
 // Relative bound on |fp32 norm - exact norm| for norms summed in fp32 (the one-launch kernel):
 // piece tree, then one add per piece a lane owns, then the 6-step butterfly, each rounding at most
 // 2^-24 relative on a sum of non-negative terms.
-inline double l1_rel_bound(int dtype, int Dc) {
-  int per_piece = dtype == kBF16 ? 8 : 4;
-  int pieces = Dc / per_piece;
-  int chain = (pieces + kWave - 1) / kWave;
-  int tree = dtype == kBF16 ? 3 : 2;
-  return (double)(tree + chain + 6 + 1) * 5.9604644775390625e-08;
+inline double l1_rel_bound_bf16(int Dc) {
+  const int chain = (Dc / 8 + kWave - 1) / kWave;
+  return (double)(3 + chain + 6 + 1) * 5.9604644775390625e-08;
 }
 
 // grid: ceil(rows / 4) blocks of 256 threads, rounded up to a multiple of 8; wave w of the grid

@@ -218,13 +218,13 @@ __device__ __forceinline__ void select_pivots_body(
 }
 
 // grid: B blocks of kPivThreads: block b selects the pivots of sample b.
-// (Two to a compute unit, with 64 registers, up to 4096 tokens: selection of 512 samples of 1500 tokens
-// 8.0 us with the 68 registers the compiler takes by itself and 5.8 this way, of 300 of 2000 7.2 and 4.9.
-// Where candidates' rows are summed, 64 registers spill eight: multi-crop with given norms, whole call, 71.4
-// and 72.9.)
-template <int DT, int PER, bool EXACT>
+// TWO: 64 registers, so that two workgroups share a compute unit (selection of 512 samples of 1500 tokens 8.0 us
+// with the 68 registers the compiler takes by itself and 5.8 this way, of 300 of 2000 7.2 and 4.9).  Eight of
+// them are spilled where rows are summed, so only for more samples than there are units: eight samples of
+// 2880 with a separate criterion 5.0 us without and 5.6 with it.
+template <int DT, int PER, bool EXACT, bool TWO>
 __global__ __launch_bounds__(kPivThreads)
-__attribute__((amdgpu_waves_per_eu(EXACT && PER <= 4 ? 8 : 4))) void k_select_pivots(
+__attribute__((amdgpu_waves_per_eu(TWO ? 8 : 4))) void k_select_pivots(
     Geo g, const void* __restrict__ X, const void* __restrict__ C, int Dc, long ldc,
     const float* __restrict__ l1, int* __restrict__ piv, double* __restrict__ pl2,
     double* __restrict__ l1d, const double* __restrict__ l2sq, float tau) {
