@@ -157,21 +157,26 @@ KsChoice choose_score_tiles(const Geo& g, int units, bool first_read) {
   // first read 30.6 and 32.5; eight of 2560, whose 80-row tiles fill the units: 24.3 and 23.9, 23.3 and
   // 24.8, 32.5 and 38.5; eight of 2048, 64 rows: 19.9 and 21.4; whole call on eight spans, 15249 rows of
   // 3584: 105.7 -> 99.7) ...
+  // On a first read the 96-row ones stay (eight samples of 2100 and 2560 tokens with rows of 2048: 15.7 and
+  // 16.8 us against 18.3 and 19.5 in one group, 18.6 and 19.3 in four; of 8192 57.9 and 60.2, 63.6 and
+  // 65.4, 66.5 and 62.4; of 4096 as fast as four but for sixteen of 1280, 36.7 and 31.0) ...
   KsChoice pick = best;
   if (best.split == 1 && best.waves <= 5 && cost(best).rows_busiest == R_best) {
     const KsChoice two = {best.waves == 3 ? 6 : best.waves == 4 ? 8 : 12, 2};
     if (cost(two).fits) pick = two;
+    if (best.waves == 5) return pick;
   }
-  // ... and on a first read of X they also beat one and two groups on small dense batches as
+  // ... and the others give way to four groups on small dense batches as
   // long as no compute unit gets more rows: up to 96 (score pass of eight samples of 2048 tokens, 32-row
-  // tiles of four groups and 64-row tiles of two: 23.7 and 28.4 us, of 2560 31.2 and 32 to 37, of 3000
-  // 32.6 and 34.5 in one group, the headline batch 32.8-34.4 and 39.1), and up to 128 where the tiles
-  // leave no unit idle (eight of 4096 43.8 and 53.1, sixteen of 2000 42.3 and 43.3; but eight of 3600
-  // 40.8 and 37.6, five of 5000 36.2 and 32.2).  With 32 pivots fewer groups stay ahead: 31.4 and 28.8
-  // on eight of 2048, 59.5 and 45.6 on eight of 2880.
+  // tiles of four groups and 64-row tiles of two: 23.7 and 28.4 us, rows of 8192 53.1 and 54.4; of 3000
+  // tokens 32.6 and 34.5 in one group, rows of 8192 64.6 and 72.5; the headline batch 32.8-34.4 and 39.1),
+  // and up to 128 where the tiles leave no unit idle and rows are long (eight of 4096 43.8 and 53.1, rows of
+  // 8192 96 and 106; sixteen of 2000 42.3 and 43.3, rows of 8192 95 and 103, but of 2048 25.2 and 23.0, of 1024
+  // 17.0 and 13.7; eight of 3600 40.8 and 37.6, five of 5000 36.2 and 32.2).  With 32 pivots fewer groups
+  // stay ahead: 31.4 and 28.8 on eight of 2048, 59.5 and 45.6 on eight of 2880.
   if (first_read && best.split == 1 && NB == 1 && g.cu == nullptr) {
     const Cost picked = cost(pick);
-    const bool full = (double)g.total_N / units >= 0.95 * picked.rows_busiest;
+    const bool full = (double)g.total_N / units >= 0.95 * picked.rows_busiest && chunks >= 32;
     if (picked.rows_busiest <= (full ? 128 : 96)) {
       // (of the two, the one that loads the busiest unit less; equal: the 32-row tiles, two
       // workgroups of which share a unit: 34.7 against 35.5-36.3 us on the headline batch)

@@ -298,8 +298,8 @@ def test_score_tile_shape_follows_the_batch_and_the_override():
 
 @pytest.mark.parametrize("B,N,P,after_norms,first", [
     (8, 2048, 16, (8, 2), (8, 4)),    # one 64-row tile a unit
-    (8, 2560, 16, (12, 2), (8, 4)),   # 80 rows a unit: two groups take 96
-    (8, 2100, 16, (12, 2), (8, 4)),
+    (8, 2560, 16, (12, 2), (12, 2)),  # 80 rows a unit: two groups take 96
+    (8, 2100, 16, (12, 2), (12, 2)),
     (4, 3584, 16, (8, 2), (8, 4)),
     (8, 3000, 16, (6, 1), (8, 4)),    # 94 rows a unit of tiles of 96
     (8, 4096, 16, (8, 1), (8, 4)),    # 128 rows on every unit
@@ -327,3 +327,9 @@ def test_score_tiles_of_batches_of_many_tiles(Dm):
     assert shape(96, N=2048) == (4, 1)           # 768 rows a unit
     assert shape(48, N=2880) == (12, 1) and shape(16, N=9216) == (12, 1) and shape(64, N=2048) == (8, 1)
     assert shape(32, total=234356, P=32) != (4, 1)
+
+
+def test_first_read_of_short_rows_keeps_one_group_at_128_rows():
+    shapes = [D.dart_score_tile_shape_first_read(D.make_desc(8, Dm, 16, D.DART_BF16, N=4096, K=16))
+              for Dm in (1024, 2048, 3968, 3976, 8192)]
+    assert shapes == [(8, 1), (8, 1), (8, 1), (8, 4), (8, 4)]
