@@ -34,7 +34,7 @@ struct OrderShared {
   int total[THREADS / kWave];
   int parts[kSelBuckets];  // of a coarse bucket: its first fine bucket and, << 16, how many it has
   int tie_from[kOrderTies], tie_to[kOrderTies];
-  int last, count, crowded, mixed;
+  int last[2], count[2], crowded[2], mixed;  // (of the first and the second count)
 };
 
 // v[e] belongs to index tid + e*THREADS; put(position, key) receives the `want` lowest (value, index) keys.
@@ -81,8 +81,8 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
 #pragma unroll
   for (int q = 0; q < kOwn; ++q) sh.hist[tid + q * THREADS] = 0;
   if (tid == 0) {
-    os.count = -1;
-    os.crowded = 0;
+    os.count[0] = os.count[1] = -1;
+    os.crowded[0] = os.crowded[1] = 0;
     os.mixed = 0;
   }
   __syncthreads();
@@ -99,7 +99,7 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
   // Counts the keys of every bucket (of(e): that of the thread's e-th score if it is selected, else
   // kSelBuckets); c: keys up to end_bucket, which completes `want` (-1: none does).  Returns how many of
   // these buckets hold more than `limit`.
-  auto tally = [&](auto of, int limit, bool note) -> int {
+  auto tally = [&](auto of, int limit, int second) -> int {
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
       const int d = of(e);
@@ -123,21 +123,21 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
       sh.hist[tid * kOwn + q] = before;  // where the bucket's keys start
       run += h[q];
       if (before < want && h[q] > limit) {
-        const int t = atomicAdd(&os.crowded, 1);
-        if (note && t < kOrderTies) {
+        const int t = atomicAdd(&os.crowded[second], 1);
+        if (second && t < kOrderTies) {
           os.tie_from[t] = before;
           os.tie_to[t] = run;
         }
       }
       if (before < want && run >= want) {
-        os.last = tid * kOwn + q;
-        os.count = run;
+        os.last[second] = tid * kOwn + q;
+        os.count[second] = run;
       }
     }
     __syncthreads();
-    c = __builtin_amdgcn_readfirstlane(os.count);
-    end_bucket = __builtin_amdgcn_readfirstlane(os.last);
-    return __builtin_amdgcn_readfirstlane(os.crowded);
+    c = __builtin_amdgcn_readfirstlane(os.count[second]);
+    end_bucket = __builtin_amdgcn_readfirstlane(os.last[second]);
+    return __builtin_amdgcn_readfirstlane(os.crowded[second]);
   };
   auto scatter = [&](auto of) {
 #pragma unroll
@@ -164,7 +164,7 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
   auto coarse_of = [&](int e) -> int {
     return e < ne && tid + e * THREADS < n && v[e] <= hi ? coarse(v[e]) : kSelBuckets;
   };
-  const int crowded = tally(coarse_of, kOrderRefine, false);
+  const int crowded = tally(coarse_of, kOrderRefine, 0);
   if (c < 0) return false;  // (block-uniform, as all of these)
   if (crowded == 0) {
     scatter(coarse_of);
@@ -180,13 +180,7 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
     before_own += h[q];
     const int next = (int)fminf((float)before_own * share, (float)(kSelBuckets - 1));
     os.parts[tid * kOwn + q] = first | ((next - first) << 16);
-  }
-  __syncthreads();  // everyone has read the words, too
-#pragma unroll
-  for (int q = 0; q < kOwn; ++q) sh.hist[tid + q * THREADS] = 0;
-  if (tid == 0) {
-    os.count = -1;
-    os.crowded = 0;
+    sh.hist[tid * kOwn + q] = 0;  // (its own cells: nobody else has looked at them)
   }
   __syncthreads();
   auto divided = [&](float x) -> int {
@@ -202,7 +196,7 @@ __device__ __forceinline__ bool order_lowest(const float (&v)[PER], int n, int w
     slot[e] = d <= last ? f : kSelBuckets;
   }
   auto slot_of = [&](int e) -> int { return slot[e]; };
-  const int ties = tally(slot_of, kOrderCrowd, true);
+  const int ties = tally(slot_of, kOrderCrowd, 1);
   if (c < 0 || ties > kOrderTies) return false;
   scatter(slot_of);
   for (int s = 0; s < ties; ++s) {
